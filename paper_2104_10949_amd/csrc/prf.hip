@@ -14,13 +14,25 @@
 // Rotation distributes over XOR, so with T0 and T2 both in memory a column costs one
 // rotation: (T0[a] ^ T2[c]) ^ rotl8(T0[b] ^ T2[d]).  The last round uses the S-box
 // byte of T0.  Each table sits in LDS once per bank (64 copies, 64 KiB each, 128 KiB
-// per block of 16 waves): lane i reads entry x of table t at byte 65536 t + 256 x + 4 i,
+// per block of up to 16 waves): lane i reads entry x of table t at byte 65536 t + 256 x + 4 i,
 // always from bank i, so the data-dependent lookups of a wave never collide, and the
 // whole address is ONE byte permute of (state word, lane constant).  Round keys are
 // expanded on the host and passed by value.
+//
+// Two rounds shared by 256 counters.  In counter mode 256 consecutive block indices differ
+// in one input byte, so of the first round only one lookup differs between them, and of the second
+// the four lookups that this one column feeds; the rest of both rounds is one constant
+// per column and is computed once per run of 256 counters ("group") and stream (counter-mode
+// caching, Bernstein and Schwabe, "New AES software speed records", 2008).  A block is
+// 5 + 7*16 + 16 = 133 lookups instead of 160.
+//
+// Bound: the vector ALU (about 290 instructions per AES block, 128 of them lookup addresses), with the LDS close
+// behind (133 lookups of two cycles each, one LDS for four SIMDs).  Measured: the truncation step with both streams on
+// 2^23 words 167 -> 129 us (of that 30 us by the shared rounds and short-call launch shape, 8 us by keys in
+// registers and three-input xors); a call of 2^15 words 10.2 -> 6.8 us (all compute units instead of 17, tables read
+// from device memory and filled 16 bytes at a time).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <string.h>
 
 #include "prf.h"
 
@@ -31,13 +43,13 @@ namespace {
 typedef uint32_t u32;
 typedef uint64_t u64;
 
-// ---- host: tables and key schedule ------------------------------------------
+// ---- tables (built by the compiler) and key schedule (host) --------------------
 // S-box via discrete logarithms to the generator 3 of GF(2^8)*, then the affine map.
 struct AesTables {
-    uint8_t sbox[256];
-    u32 t0[256];
-    AesTables() {
-        uint8_t exp3[256], log3[256];
+    uint8_t sbox[256] = {};
+    u32 t0[256] = {};
+    constexpr AesTables() {
+        uint8_t exp3[256] = {}, log3[256] = {};
         uint8_t x = 1;
         for (int i = 0; i < 255; ++i) {
             exp3[i] = x;
@@ -61,14 +73,12 @@ struct AesTables {
     }
 };
 
-const AesTables& tables() {
-    static const AesTables t;
-    return t;
-}
+constexpr AesTables host_tables{};
+__device__ const AesTables device_tables{};   // (device memory: passed as an argument it would be read over the host link)
 
 // Round keys as 44 little-endian column words.
 void expand_key(const uint8_t key[16], u32 rk[44]) {
-    const uint8_t* sb = tables().sbox;
+    const uint8_t* sb = host_tables.sbox;
     for (int i = 0; i < 4; ++i)
         rk[i] = (u32)key[4 * i] | ((u32)key[4 * i + 1] << 8) | ((u32)key[4 * i + 2] << 16) | ((u32)key[4 * i + 3] << 24);
     u32 rcon = 1;
@@ -85,12 +95,15 @@ void expand_key(const uint8_t key[16], u32 rk[44]) {
     }
 }
 
+// Round keys of the streams of a launch: F(self, .), F(prev, .) if the launch forms alpha, then the mask stream.
 struct PrfKeys {
-    u32 self[44], prev[44], mask[44];
+    u32 rk[3][44];
 };
 
 // ---- device ------------------------------------------------------------------
-constexpr int PRF_THREADS = 1024;
+constexpr int PRF_MAX_WAVES = 16;      // waves of a block; its tables leave room for one block per compute unit
+constexpr int PRF_MAX_GROUPS = 512;    // groups of 256 counters whose constants a block can hold
+constexpr int PRF_MAX_CHUNKS = 4 * (PRF_MAX_GROUPS - 1);   // chunks of 64 counters, the first anywhere in its group
 
 // LDS byte address of a table entry: byte 0 = 4 * (lane % 64) and byte 2 = table number
 // come from the lane constant `lc` = 4 * lane | 0x0100, byte 1 = byte `B` of the state word.
@@ -103,9 +116,12 @@ __device__ __forceinline__ u32 lut(const char* __restrict__ tbl, u32 state, u32 
 
 __device__ __forceinline__ u32 rotl8(u32 v) { return __builtin_amdgcn_alignbit(v, v, 24); }
 
+// a ^ b ^ c in one instruction (truth table 0x96); the compiler leaves two xors
+__device__ __forceinline__ u32 xor3(u32 a, u32 b, u32 c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+
 // one output column of a full round: bytes 0..3 taken from state words a, b, c, d
 __device__ __forceinline__ u32 column(const char* tbl, u32 lc, u32 a, u32 b, u32 c, u32 d, u32 rk) {
-    return (lut<0, 0>(tbl, a, lc) ^ lut<2, 1>(tbl, c, lc)) ^ rotl8(lut<1, 0>(tbl, b, lc) ^ lut<3, 1>(tbl, d, lc)) ^ rk;
+    return xor3(lut<0, 0>(tbl, a, lc), lut<2, 1>(tbl, c, lc), rk) ^ rotl8(lut<1, 0>(tbl, b, lc) ^ lut<3, 1>(tbl, d, lc));
 }
 
 // one output word of the last round: S-box bytes (byte 1 of T0) of byte 0 of a, 1 of b, 2 of c, 3 of d
@@ -117,53 +133,77 @@ __device__ __forceinline__ u32 last_column(const char* tbl, u32 lc, u32 a, u32 b
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u) ^ rk;
 }
 
-// NS independent encryptions side by side, round by round.  The round loop is NOT unrolled and the round keys
-// are indexed by the loop counter, so that they are fetched by scalar loads as the rounds go (one round ahead):
-// keeping two or three whole key schedules in scalar registers does not fit and would be spilled into vector lanes.
-template <int NS>
-__device__ __forceinline__ void aes_blocks(const char* __restrict__ tbl, u32 lc, const u32* const (&rk)[NS],
-                                           const u32 (&in)[NS][4], u32 (&out)[NS][4]) {
-    u32 s[NS][4], k[NS][4];
-#pragma unroll
-    for (int e = 0; e < NS; ++e) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            s[e][c] = in[e][c] ^ rk[e][c];
-            k[e][c] = rk[e][4 + c];
-        }
-    }
-#pragma unroll 3
-    for (int r = 1; r < 10; ++r) {
-        u32 nk[NS][4];
-#pragma unroll
-        for (int e = 0; e < NS; ++e)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) nk[e][c] = rk[e][4 * (r + 1) + c];
-#pragma unroll
-        for (int e = 0; e < NS; ++e) {
-            const u32 n0 = column(tbl, lc, s[e][0], s[e][1], s[e][2], s[e][3], k[e][0]);
-            const u32 n1 = column(tbl, lc, s[e][1], s[e][2], s[e][3], s[e][0], k[e][1]);
-            const u32 n2 = column(tbl, lc, s[e][2], s[e][3], s[e][0], s[e][1], k[e][2]);
-            const u32 n3 = column(tbl, lc, s[e][3], s[e][0], s[e][1], s[e][2], k[e][3]);
-            s[e][0] = n0; s[e][1] = n1; s[e][2] = n2; s[e][3] = n3;
-        }
-#pragma unroll
-        for (int e = 0; e < NS; ++e)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) k[e][c] = nk[e][c];
-    }
-#pragma unroll
-    for (int e = 0; e < NS; ++e) {
-        out[e][0] = last_column(tbl, lc, s[e][0], s[e][1], s[e][2], s[e][3], k[e][0]);
-        out[e][1] = last_column(tbl, lc, s[e][1], s[e][2], s[e][3], s[e][0], k[e][1]);
-        out[e][2] = last_column(tbl, lc, s[e][2], s[e][3], s[e][0], s[e][1], k[e][2]);
-        out[e][3] = last_column(tbl, lc, s[e][3], s[e][0], s[e][1], s[e][2], k[e][3]);
-    }
+// What a group of 256 counters shares of rounds 1 and 2: column 0 after round 1 without the lookup of the counter's
+// byte 0, and the four columns after round 2 without the lookup that each takes from that column.
+__device__ __forceinline__ void group_constants(const char* __restrict__ tbl, u32 lc, const u32* __restrict__ rk,
+                                                u64 first_block, u64 nonce, u32& c1, uint4& c2) {
+    const u32 s0 = (u32)first_block ^ rk[0], s1 = (u32)(first_block >> 32) ^ rk[1], s2 = (u32)nonce ^ rk[2],
+              s3 = (u32)(nonce >> 32) ^ rk[3];
+    c1 = lut<2, 1>(tbl, s2, lc) ^ rotl8(lut<1, 0>(tbl, s1, lc) ^ lut<3, 1>(tbl, s3, lc)) ^ rk[4];
+    const u32 n1 = column(tbl, lc, s1, s2, s3, s0, rk[5]);
+    const u32 n2 = column(tbl, lc, s2, s3, s0, s1, rk[6]);
+    const u32 n3 = column(tbl, lc, s3, s0, s1, s2, rk[7]);
+    c2.x = lut<2, 1>(tbl, n2, lc) ^ rotl8(lut<1, 0>(tbl, n1, lc) ^ lut<3, 1>(tbl, n3, lc)) ^ rk[8];
+    c2.y = lut<0, 0>(tbl, n1, lc) ^ lut<2, 1>(tbl, n3, lc) ^ rotl8(lut<1, 0>(tbl, n2, lc)) ^ rk[9];
+    c2.z = lut<0, 0>(tbl, n2, lc) ^ rotl8(lut<1, 0>(tbl, n3, lc) ^ lut<3, 1>(tbl, n1, lc)) ^ rk[10];
+    c2.w = lut<0, 0>(tbl, n3, lc) ^ lut<2, 1>(tbl, n1, lc) ^ rotl8(lut<3, 1>(tbl, n2, lc)) ^ rk[11];
 }
 
-struct T0Table {
-    u32 v[256];
+// Round keys 3..10 of the streams of a launch and the byte that meets the counter's byte 0, fetched once per wave and
+// kept in registers over all of its chunks: those of the first stream in scalar registers, those of the others in
+// vector registers (96 keys do not fit the scalar file, and keys fetched as the rounds go are scalar loads whose
+// out-of-order completion makes every wait for a lookup a wait for all of them).
+template <int NS>
+struct RoundKeys {
+    u32 k0[NS], k[NS][8][4];
+    __device__ __forceinline__ void load(const PrfKeys& keys) {
+#pragma unroll
+        for (int e = 0; e < NS; ++e) {
+            k0[e] = keys.rk[e][0];
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    k[e][r][c] = keys.rk[e][12 + 4 * r + c];
+                    if (e > 0) asm volatile("" : "+v"(k[e][r][c]));
+                }
+        }
+    }
 };
+
+// NS independent encryptions side by side, round by round, of counter byte 0 = `byte0` in the group with constants
+// c1, c2.
+template <int NS>
+__device__ __forceinline__ void aes_blocks(const char* __restrict__ tbl, u32 lc, const RoundKeys<NS>& key, u32 byte0,
+                                           const u32 (&c1)[NS], const uint4 (&c2)[NS], u32 (&out)[NS][4]) {
+    u32 s[NS][4];
+#pragma unroll
+    for (int e = 0; e < NS; ++e) {
+        const u32 t = c1[e] ^ lut<0, 0>(tbl, byte0 ^ key.k0[e], lc);
+        s[e][0] = c2[e].x ^ lut<0, 0>(tbl, t, lc);
+        s[e][1] = c2[e].y ^ rotl8(lut<3, 1>(tbl, t, lc));
+        s[e][2] = c2[e].z ^ lut<2, 1>(tbl, t, lc);
+        s[e][3] = c2[e].w ^ rotl8(lut<1, 0>(tbl, t, lc));
+    }
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+#pragma unroll
+        for (int e = 0; e < NS; ++e) {
+            const u32 n0 = column(tbl, lc, s[e][0], s[e][1], s[e][2], s[e][3], key.k[e][r][0]);
+            const u32 n1 = column(tbl, lc, s[e][1], s[e][2], s[e][3], s[e][0], key.k[e][r][1]);
+            const u32 n2 = column(tbl, lc, s[e][2], s[e][3], s[e][0], s[e][1], key.k[e][r][2]);
+            const u32 n3 = column(tbl, lc, s[e][3], s[e][0], s[e][1], s[e][2], key.k[e][r][3]);
+            s[e][0] = n0; s[e][1] = n1; s[e][2] = n2; s[e][3] = n3;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < NS; ++e) {
+        out[e][0] = last_column(tbl, lc, s[e][0], s[e][1], s[e][2], s[e][3], key.k[e][7][0]);
+        out[e][1] = last_column(tbl, lc, s[e][1], s[e][2], s[e][3], s[e][0], key.k[e][7][1]);
+        out[e][2] = last_column(tbl, lc, s[e][2], s[e][3], s[e][0], s[e][1], key.k[e][7][2]);
+        out[e][3] = last_column(tbl, lc, s[e][3], s[e][0], s[e][1], s[e][2], key.k[e][7][3]);
+    }
+}
 
 // floor(v / 2^d) of v read as a two's-complement integer
 __device__ __forceinline__ u64 asr64(u64 v, int d) { return (u64)((int64_t)v >> d); }
@@ -172,50 +212,82 @@ __device__ __forceinline__ u64 asr64(u64 v, int d) { return (u64)((int64_t)v >> 
 //   out = asr64((z ? z : 0) + (msg ? msg : 0) + [ALPHA] (F(self, j) - F(prev, j)), d)  -/+  [MASK] F(mask, j)
 // (alpha under `nonce`, the mask stream under `mask_nonce`; the mask is subtracted unless add_mask), or, for
 // binary shares (xor_mode, ALPHA only):  out = (z ? z : 0) ^ F(self, j) ^ F(prev, j).
-// One thread handles one AES block = two consecutive words of each stream.
+// One thread handles one AES block = two consecutive words of each stream; a wave takes chunks of 64 consecutive
+// blocks, aligned to 64, of the workgroup's run of `per_wg` chunks.  `pairs`: first is even and z, msg and out are
+// 16-byte aligned, so that a thread's two words are one access.
 template <bool ALPHA, bool MASK>
-__global__ __launch_bounds__(PRF_THREADS) void prf_combine_kernel(const u64* z, const u64* msg,
+__global__ __launch_bounds__(64 * PRF_MAX_WAVES) void prf_combine_kernel(const u64* z, const u64* msg,
                                                           u64* out, size_t n, u64 first, u64 nonce,
                                                           u64 mask_nonce, int d, bool add_mask, bool xor_mode,
-                                                          const PrfKeys keys, const T0Table table) {
+                                                          bool pairs, u32 per_wg, const PrfKeys keys) {
+    constexpr int NS = (ALPHA ? 2 : 0) + (MASK ? 1 : 0);
     __shared__ __attribute__((aligned(16))) u32 tables[2 * 256 * 64];  // T0 then T2, one copy per bank
-    {
-        // thread t fills 16 of the 64 copies of entry t % 256 in both tables; consecutive threads
-        // start at consecutive banks
-        const int e = threadIdx.x & 255, q = threadIdx.x >> 8;
-        const u32 v0 = table.v[e], v2 = (v0 << 16) | (v0 >> 16);
+    __shared__ uint4 group_c2[NS][PRF_MAX_GROUPS];
+    __shared__ u32 group_c1[NS][PRF_MAX_GROUPS];
+    // 16 bytes, i.e. four of the 64 copies, of an entry of both tables per thread and trip
 #pragma unroll 4
-        for (int c = 0; c < 16; ++c) {
-            const int copy = q * 16 + ((c + e) & 15);
-            tables[e * 64 + copy] = v0;
-            tables[256 * 64 + e * 64 + copy] = v2;
-        }
+    for (u32 i = threadIdx.x; i < 256 * 16; i += blockDim.x) {
+        const u32 v0 = device_tables.t0[i >> 4], v2 = (v0 << 16) | (v0 >> 16);
+        reinterpret_cast<uint4*>(tables)[i] = uint4{v0, v0, v0, v0};
+        reinterpret_cast<uint4*>(tables)[256 * 16 + i] = uint4{v2, v2, v2, v2};
     }
     __syncthreads();
     const char* tbl = reinterpret_cast<const char*>(tables);
-    const u32 lc = ((threadIdx.x & 63) << 2) | 0x0100u;
+    const u32 lane = threadIdx.x & 63;
+    const u32 lc = (lane << 2) | 0x0100u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = blockDim.x >> 6;
     const u64 b_first = first >> 1, b_last = (first + n - 1) >> 1;  // n >= 1
-    const u64 nblocks = b_last - b_first + 1;
-    for (u64 bi = (u64)blockIdx.x * PRF_THREADS + threadIdx.x; bi < nblocks; bi += (u64)gridDim.x * PRF_THREADS) {
-        const u64 block = b_first + bi;
-        u64 w0 = 0, w1 = 0, r0 = 0, r1 = 0;
-        constexpr int NS = (ALPHA ? 2 : 0) + (MASK ? 1 : 0);
-        u32 in[NS][4], ct[NS][4];
-        const u32* rk[NS];
-        if constexpr (ALPHA) {
-            rk[0] = keys.self;
-            rk[1] = keys.prev;
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                in[e][0] = (u32)block; in[e][1] = (u32)(block >> 32); in[e][2] = (u32)nonce; in[e][3] = (u32)(nonce >> 32);
+    const u64 ch_last = b_last >> 6;
+    const u64 ch0 = (b_first >> 6) + (u64)blockIdx.x * per_wg;      // the workgroup's chunks: ch0 .. ch_end - 1
+    const u64 ch_end = ch0 + per_wg <= ch_last + 1 ? ch0 + per_wg : ch_last + 1;
+    const u64 g0 = ch0 >> 2;
+    if (ch0 < ch_end) {   // uniform over the workgroup
+        const u32 groups = (u32)(((ch_end - 1) >> 2) - g0) + 1;     // at most PRF_MAX_GROUPS: see the launcher
+        const u32 jobs = NS * ((groups + 63) / 64);
+        for (u32 job = wave; job < jobs; job += waves) {
+            const u32 e = job % NS, g = job / NS * 64 + lane;
+            if (g < groups) {
+                u32 c1;
+                uint4 c2;
+                group_constants(tbl, lc, keys.rk[e], (g0 + g) << 8, MASK && e == NS - 1 ? mask_nonce : nonce, c1, c2);
+                group_c1[e][g] = c1;
+                group_c2[e][g] = c2;
             }
         }
-        if constexpr (MASK) {
-            rk[NS - 1] = keys.mask;
-            in[NS - 1][0] = (u32)block; in[NS - 1][1] = (u32)(block >> 32);
-            in[NS - 1][2] = (u32)mask_nonce; in[NS - 1][3] = (u32)(mask_nonce >> 32);
+    }
+    __syncthreads();
+    RoundKeys<NS> key;
+    key.load(keys);
+    for (u64 ch = ch0 + wave; ch < ch_end; ch += waves) {
+        const u32 g = (u32)((ch >> 2) - g0);
+        u32 c1[NS], ct[NS][4];
+        uint4 c2[NS];
+#pragma unroll
+        for (int e = 0; e < NS; ++e) {
+            c1[e] = group_c1[e][g];
+            c2[e] = group_c2[e][g];
         }
-        aes_blocks<NS>(tbl, lc, rk, in, ct);
+        const u64 block = ch * 64 + lane;
+        const u64 j0 = 2 * block, j1 = j0 + 1;  // word indices
+        const bool in0 = j0 >= first && j0 - first < n, in1 = j1 >= first && j1 - first < n;
+        // the operands are requested ahead of the encryption
+        u64 z0 = 0, z1 = 0;
+        if (pairs && in0 && in1) {
+            const size_t j = j0 - first;
+            if (z) {
+                const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(z + j);
+                z0 = v.x; z1 = v.y;
+            }
+            if (msg) {
+                const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(msg + j);
+                z0 += v.x; z1 += v.y;
+            }
+        } else {
+            if (in0) z0 = (z ? z[j0 - first] : 0) + (msg ? msg[j0 - first] : 0);
+            if (in1) z1 = (z ? z[j1 - first] : 0) + (msg ? msg[j1 - first] : 0);
+        }
+        aes_blocks<NS>(tbl, lc, key, ((u32)(ch & 3) << 6) | lane, c1, c2, ct);
+        u64 w0 = 0, w1 = 0, r0 = 0, r1 = 0;
         if constexpr (ALPHA) {
             const u64 a0 = ((u64)ct[0][1] << 32) | ct[0][0], a1 = ((u64)ct[0][3] << 32) | ct[0][2];
             const u64 b0 = ((u64)ct[1][1] << 32) | ct[1][0], b1 = ((u64)ct[1][3] << 32) | ct[1][2];
@@ -227,16 +299,13 @@ __global__ __launch_bounds__(PRF_THREADS) void prf_combine_kernel(const u64* z, 
             r1 = ((u64)ct[NS - 1][3] << 32) | ct[NS - 1][2];
             if (!add_mask) { r0 = 0 - r0; r1 = 0 - r1; }
         }
-        const u64 j0 = 2 * block, j1 = j0 + 1;  // word indices
-        if (j0 >= first && j0 - first < n) {
-            const size_t j = j0 - first;
-            const u64 zj = z ? z[j] : 0;
-            out[j] = xor_mode ? zj ^ w0 : asr64(zj + (msg ? msg[j] : 0) + w0, d) + r0;
-        }
-        if (j1 >= first && j1 - first < n) {
-            const size_t j = j1 - first;
-            const u64 zj = z ? z[j] : 0;
-            out[j] = xor_mode ? zj ^ w1 : asr64(zj + (msg ? msg[j] : 0) + w1, d) + r1;
+        const u64 v0 = xor_mode ? z0 ^ w0 : asr64(z0 + w0, d) + r0;
+        const u64 v1 = xor_mode ? z1 ^ w1 : asr64(z1 + w1, d) + r1;
+        if (pairs && in0 && in1) {
+            *reinterpret_cast<ulonglong2*>(out + (j0 - first)) = ulonglong2{v0, v1};
+        } else {
+            if (in0) out[j0 - first] = v0;
+            if (in1) out[j1 - first] = v1;
         }
     }
 }
@@ -253,26 +322,27 @@ hipError_t launch_prf_combine(const uint64_t* z, const uint64_t* msg, uint64_t* 
     if (xor_mode && (mask || msg || d != 0)) return hipErrorInvalidValue;
     PrfKeys keys = {};
     if (alpha) {
-        expand_key(key_self, keys.self);
-        expand_key(key_prev, keys.prev);
+        expand_key(key_self, keys.rk[0]);
+        expand_key(key_prev, keys.rk[1]);
     }
-    if (mask) expand_key(key_mask, keys.mask);
-    T0Table table;
-    memcpy(table.v, tables().t0, sizeof(table.v));
-    // 128 KiB of tables per block: one block of 16 waves per compute unit, grid-stride beyond two rounds
-    const size_t nblocks = (n + 1) / 2 + 1;
-    size_t grid = (nblocks + PRF_THREADS - 1) / PRF_THREADS;
-    if (grid > 256 * 2) grid = 256 * 2;
-    const dim3 g((unsigned)grid), b(PRF_THREADS);
-    if (alpha && mask)
-        hipLaunchKernelGGL((prf_combine_kernel<true, true>), g, b, 0, stream, z, msg, out, n, (u64)first, (u64)nonce,
-                           (u64)mask_nonce, d, add_mask, xor_mode, keys, table);
-    else if (alpha)
-        hipLaunchKernelGGL((prf_combine_kernel<true, false>), g, b, 0, stream, z, msg, out, n, (u64)first, (u64)nonce,
-                           (u64)mask_nonce, d, add_mask, xor_mode, keys, table);
-    else
-        hipLaunchKernelGGL((prf_combine_kernel<false, true>), g, b, 0, stream, z, msg, out, n, (u64)first, (u64)nonce,
-                           (u64)mask_nonce, d, add_mask, xor_mode, keys, table);
+    if (mask) expand_key(key_mask, keys.rk[alpha ? 2 : 0]);
+    const uintptr_t bases = (uintptr_t)z | (uintptr_t)msg | (uintptr_t)out;
+    const bool pairs = first % 2 == 0 && bases % 16 == 0;
+    // The tables take a compute unit's LDS, so one workgroup runs per compute unit.  Short calls spread over all of
+    // them, with eight waves at least, which fill the tables faster than one wave would; longer ones take 16 waves
+    // and a run of chunks each.
+    const u64 chunks = (((first + n - 1) >> 1) >> 6) - ((first >> 1) >> 6) + 1;
+    const u64 per_cu = (chunks + 255) / 256;
+    const u64 waves = per_cu < 8 ? 8 : (per_cu < PRF_MAX_WAVES ? per_cu : PRF_MAX_WAVES);
+    const u64 per_wg = per_cu < PRF_MAX_CHUNKS ? per_cu : PRF_MAX_CHUNKS;
+    const dim3 g((unsigned)((chunks + per_wg - 1) / per_wg)), b((unsigned)(64 * waves));
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, g, b, 0, stream, z, msg, out, n, (u64)first, (u64)nonce, (u64)mask_nonce, d, add_mask,
+                           xor_mode, pairs, (u32)per_wg, keys);
+    };
+    if (alpha && mask) launch(prf_combine_kernel<true, true>);
+    else if (alpha) launch(prf_combine_kernel<true, false>);
+    else launch(prf_combine_kernel<false, true>);
     return hipGetLastError();
 }
 

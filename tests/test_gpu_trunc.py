@@ -40,6 +40,34 @@ def test_prf_words_match_the_oracle(cg, ro, n, first):
     assert not first_mismatch(got, ro.prf_words(K1, 77, first, n))
 
 
+# a wave takes 64 blocks = 128 words, 256 blocks = 512 words share the constants of the first two rounds, a workgroup
+# takes 8 waves up to 262144 words, then 9 to 16, then runs of chunks: around each of these, and where the block index
+# carries into byte 1, byte 2 and its upper word
+@pytest.mark.parametrize("n,first", [(127, 1), (128, 0), (129, 383), (514, 511), (1500, 2 ** 17 - 700), (3000, 2 ** 33 - 1001),
+                                     (262144, 6), (262145, 127), (300001, 2 ** 25 - 150001), (524288, 510), (560003, 12)])
+def test_prf_streams_at_the_edges_of_their_work_split(cg, ro, wl, n, first):
+    say(f"prf streams at work-split edges n={n} first={first}")
+    z, m = wl.draw_ring((n + 1,), 911), wl.draw_ring((n + 1,), 912)
+    dz, dm = cg.to_device(z), cg.to_device(m)
+    assert not first_mismatch(cg.to_host(cg.cg_prf_words(K1, 77, first, n)), ro.prf_words(K1, 77, first, n))
+    for s in (0, 1):   # 16-byte aligned and not
+        zs, ms = z[s:s + n], m[s:s + n]
+        got = cg.to_host(cg.cg_trunc1_local(dz[s:s + n], dm[s:s + n], K1, K0, 31, first, 16, K1, 32))
+        assert not first_mismatch(got, ro.trunc1_local(zs, ms, K1, K0, 31, first, 16, K1, 32))
+        got = cg.to_host(cg.cg_breshare(dz[s:s + n], K1, K0, 31, first))
+        assert not first_mismatch(got, ro.breshare(zs, K1, K0, 31, first))
+
+
+def test_prf_stream_longer_than_one_run_per_compute_unit(cg, ro):
+    # a workgroup holds the constants of 512 groups: more than 256 * 2044 chunks need more workgroups than compute units
+    per_wg = 2044 * 128
+    n = 256 * per_wg + 3 * 128 + 5
+    say(f"cg_prf_words n={n}")
+    got = cg.cg_prf_words(K1, 77, 130, n)
+    for at in (0, per_wg - 300, 255 * per_wg - 300, 256 * per_wg - 300, n - 600):
+        assert not first_mismatch(cg.to_host(got[at:at + 600]), ro.prf_words(K1, 77, 130 + at, 600))
+
+
 @pytest.mark.parametrize("d", [0, 1, 16, 20, 63])
 @pytest.mark.parametrize("n,first", [(1, 0), (2, 1), (257, 5), (100003, 8)])
 def test_local_step_matches_the_oracle(cg, ro, wl, n, first, d):
