@@ -166,7 +166,7 @@ def test_relu_assembled_from_sign_bit_and_products(cg, ro, wl):
         assert not first_mismatch(cg.to_host(got), want)
 
 
-@pytest.mark.parametrize("m", [1, 2, 7, 8, 9, 64, 1001])
+@pytest.mark.parametrize("m", [1, 2, 7, 8, 9, 15, 16, 17, 64, 65, 1001])
 def test_bit_planes_and_unpack(cg, ro, wl, m):
     from tests.gpu_util import first_mismatch as fm
     n = 64 * m
