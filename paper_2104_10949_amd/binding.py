@@ -133,6 +133,10 @@ def _ptr(t: torch.Tensor) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
+        # the raw handle of torch.cuda.current_stream(), without the object around it (it costs more than the launch
+        # of a short call takes the GPU)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
