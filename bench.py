@@ -583,12 +583,14 @@ def main() -> int:
     big = max(range(len(layers)), key=lambda i: layers[i].mnk)
     big_tops = 2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * layers[big].mnk / (per_layer_ms[big] * 1e-3) / 1e12
     roofline = {
-        "bound": "mfma", "kernel": "share_gemm_kernel (int8 MFMA, i32 accumulate)",
+        "bound": "mfma", "kernel": "share_gemm_kernel / rns_gemm_kernel (int8 MFMA, i32 accumulate)",
         "achieved": round(achieved_tops, 2), "peak": INT8_PEAK_TOPS, "unit": "TOP/s",
         "frac": round(achieved_tops / INT8_PEAK_TOPS, 4),
         "launches_per_step": launches,
         "avg_launch_ms": round(kernel_ms_sum / launches, 5),
         "ops_per_launch": int8_ops_per_step / launches,
+        # layers that take the residue route (through scratch memory) execute half of the digit form's products
+        "ops_counted": "digit form, 144 int8 operations per (m, n, k), whatever the route executes",
         "largest_layer": {"name": layers[big].name, "gemm": list(layers[big].gemm),
                           "ms": round(per_layer_ms[big], 5), "achieved": round(big_tops, 2),
                           "frac": round(big_tops / INT8_PEAK_TOPS, 4)},

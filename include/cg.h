@@ -114,19 +114,25 @@ CG_API cg_status cg_share_matmul_t(const uint64_t *x_i, const uint64_t *x_ip1,
 
 /*
  * The same product with caller-supplied scratch memory (device memory, 16-byte
- * aligned, at least cg_share_matmul_workspace_bytes(M, N, K) bytes, not
- * overlapping any operand).  With scratch memory each share tensor is split
+ * aligned, cg_share_matmul_workspace_bytes(M, N, K) bytes for the fastest route,
+ * not overlapping any operand).  Large products go through residues: every word is
+ * reduced once modulo 18 or 19 numbers of eight bits, one int8 product per modulus
+ * follows, and a last pass puts the words together; this takes 18 or 19 bytes per
+ * operand word and per output.  Other products, and a call whose scratch memory holds
+ * the digits (8 bytes per operand word, rows padded to a multiple of 32 words) but
+ * not the residues, take the digit route: each share tensor is split
  * into its eight signed-byte digits ONCE, by a streaming pass that writes the
  * digits there, instead of once per output tile that needs it inside the product
  * kernel; the product kernel then only moves bytes.  Result and argument rules
  * are those of cg_share_matmul, bit for bit.  The scratch contents are
- * undefined afterwards and carry no state between calls.  When the digit route
- * does not apply (odd K, a pointer that is only 8-byte aligned, K above 2^20,
+ * undefined afterwards and carry no state between calls.  When the residues do
+ * not pay or do not fit and the digit route does not apply (odd K, a pointer that is only 8-byte aligned, K above 2^20,
  * or a left operand of so few rows, at most 64, that the plain call's kernel for
  * such products is the faster one) the call
  * computes exactly as cg_share_matmul and does not touch the scratch memory;
- * cg_share_matmul_workspace_bytes then returns 0 (as it does for invalid sizes).
- * CG_ERR_WORKSPACE if workspace_bytes is too small, CG_ERR_NULL / CG_ERR_ALIGN /
+ * cg_share_matmul_workspace_bytes returns 0 where no route uses scratch memory (and
+ * for invalid sizes).
+ * CG_ERR_WORKSPACE if workspace_bytes is too small for the digits, CG_ERR_NULL / CG_ERR_ALIGN /
  * CG_ERR_ALIAS for a missing, misaligned or overlapping workspace.
  */
 CG_API size_t cg_share_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K);
@@ -136,7 +142,7 @@ CG_API size_t cg_share_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K);
  * memory is expected to be the faster one on MI355X, the conversion pass included; 0
  * when the plain call is, or when the sizes are invalid.  A measured rule of thumb
  * for callers that have scratch memory and want to pick per layer: large products
- * whose operands are small against M*N*K gain (square products about 15 %), skinny
+ * whose operands are small against M*N*K gain (4096^3 about a third), skinny
  * or short ones lose.  Same for cg_share_conv2d_prefers_workspace below.
  */
 CG_API int cg_share_matmul_prefers_workspace(int64_t M, int64_t N, int64_t K);

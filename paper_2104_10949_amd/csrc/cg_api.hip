@@ -9,6 +9,7 @@
 #include "cg.h"
 #include "prf.h"
 #include "share_gemm.h"
+#include "share_gemm_rns.h"
 
 namespace {
 
@@ -637,6 +638,8 @@ struct Plan {
     int64_t x_rows, x_k;  // left operand seen as [x_rows, x_k] words for the plane conversion
     u64 xp_bytes, wp_bytes;  // bytes of one left / right plane tensor
     u64 x_bytes, w_bytes, z_bytes;
+    bool rns_pays;    // the residue route applies and is the faster one, given its scratch memory
+    cg::RnsParams rns;
 };
 
 u64 round_up(u64 v, u64 a) { return (v + a - 1) / a * a; }
@@ -653,8 +656,41 @@ bool planes_pay(const Plan& pl) {
     return 0.17 * 144.0 * mnk / 2.45e15 > 1.15 * (32.0 * words / 6.5e12 + 5.0e-6);
 }
 
-u64 plan_workspace_bytes(const Plan& pl) {
+u64 planes_workspace_bytes(const Plan& pl) {
     return pl.planes_ok ? 2 * round_up(pl.xp_bytes, 256) + 2 * round_up(pl.wp_bytes, 256) : 0;
+}
+
+// What a caller is asked to bring: enough for the faster route.  Less is accepted as long as the digit route fits.
+u64 plan_workspace_bytes(const Plan& pl) {
+    const u64 planes = planes_workspace_bytes(pl), rns = pl.rns_pays ? cg::rns_workspace_bytes(pl.rns) : 0;
+    return rns > planes ? rns : planes;
+}
+
+// Residue route for a plan whose left operand is [x_rows, words] (gathered over a window if `conv`): set up pl.rns
+// and decide whether it pays.
+void plan_rns(Plan* pl, int64_t x_rows, int64_t words, bool conv) {
+    const cg::GemmParams& p = pl->p;
+    cg::RnsParams& r = pl->rns;
+    pl->rns_pays = false;
+    if (x_rows >= (int64_t)1 << 30) return;
+    r.x_a = p.x_a; r.x_b = p.x_b; r.w_a = p.w_a; r.w_b = p.w_b; r.z = p.z;
+    r.M = p.M; r.N = p.N;
+    r.words = (int)words; r.x_rows = (int)x_rows; r.conv = conv;
+    r.H = p.H; r.W = p.W; r.Ho = p.Ho; r.Wo = p.Wo; r.sh = p.sh; r.sw = p.sw; r.ph = p.ph; r.pw = p.pw;
+    r.kh = conv ? p.kh : 1; r.kw = conv ? p.kw : 1;
+    if (!cg::rns_plan(&r)) return;
+    // Both routes in seconds, from measurements on MI355X.  Plain kernel: 144 operations per (m, n, k) of its 128 x 64
+    // tiles at 2.6e15 a second, 1.15 times that with 8-byte loads, and 8 microseconds; 0.93 of it where the digit planes
+    // pay.  Residues: 16 + 2 * nmod bytes per word pair converted at 5.2 TB/s, 2 * nmod + 8 per output combined at
+    // 8.5 TB/s, 1.5 microseconds per step of the product, and 12 microseconds for three launches that do not fill the
+    // chip at both ends.  They must win by a margin to be preferred.
+    const double up_m = (double)((p.M + (int64_t)127) / 128 * 128), up_n = (double)((p.N + (int64_t)63) / 64 * 64);
+    double best = 144.0 * up_m * up_n * (double)p.K / 2.6e15 * (pl->planes_ok ? 1.0 : 1.15) + 8.0e-6;
+    if (planes_pay(*pl)) best *= 0.93;
+    const double pairs = ((double)r.x_rows + (double)p.N * r.kh * r.kw) * r.slices * 64.0;
+    const double rns = pairs * (16.0 + 2.0 * r.nmod) / 5.2e12 + (double)r.r_plane * (2.0 * r.nmod + 8.0) / 8.5e12 +
+                       1.5e-6 * r.product_cost + 12.0e-6;
+    pl->rns_pays = rns < 0.9 * best;
 }
 
 cg_status plan_matmul(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t* y_i, const uint64_t* y_ip1,
@@ -699,6 +735,7 @@ cg_status plan_matmul(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t
     pl.x_rows = M; pl.x_k = K;
     pl.xp_bytes = cg::planes_bytes(M, K); pl.wp_bytes = cg::planes_bytes(N, K);
     pl.x_bytes = (u64)mk * 8; pl.w_bytes = (u64)nk * 8; pl.z_bytes = (u64)mn * 8;
+    if (!trans_x && !trans_y && !long_rows && !cg::share_gemm_small_applies(p)) plan_rns(&pl, M, K, false);
     *out = pl;
     return CG_OK;
 }
@@ -795,6 +832,7 @@ cg_status plan_conv2d(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t
     pl.xp_bytes = cg::planes_bytes(pl.x_rows, pl.x_k);
     pl.wp_bytes = cg::planes_bytes(d->Cout, K);
     pl.x_bytes = (u64)x_el * 8; pl.w_bytes = (u64)w_el * 8; pl.z_bytes = (u64)z_el * 8;
+    plan_rns(&pl, d->B * d->H * d->W, d->Cin, !pointwise);
     *out = pl;
     return CG_OK;
 }
@@ -1007,17 +1045,20 @@ cg_status run_direct(const Plan& pl, void* stream) {
     return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
 }
 
+bool workspace_overlaps(const Plan& pl, const void* workspace, u64 need) {
+    const cg::GemmParams& q = pl.p;
+    return overlap(workspace, need, q.x_a, pl.x_bytes) || overlap(workspace, need, q.x_b, pl.x_bytes) ||
+           overlap(workspace, need, q.w_a, pl.w_bytes) || overlap(workspace, need, q.w_b, pl.w_bytes) ||
+           overlap(workspace, need, q.z, pl.z_bytes);
+}
+
 // Digit-plane route: four conversions into the caller's scratch memory, then the contraction.
 cg_status run_planes(Plan& pl, void* workspace, size_t workspace_bytes, void* stream) {
     if (!workspace) return CG_ERR_NULL;
     if (!aligned(workspace, 16)) return CG_ERR_ALIGN;
-    const u64 need = plan_workspace_bytes(pl);
+    const u64 need = planes_workspace_bytes(pl);
     if (workspace_bytes < need) return CG_ERR_WORKSPACE;
-    const cg::GemmParams& q = pl.p;
-    if (overlap(workspace, need, q.x_a, pl.x_bytes) || overlap(workspace, need, q.x_b, pl.x_bytes) ||
-        overlap(workspace, need, q.w_a, pl.w_bytes) || overlap(workspace, need, q.w_b, pl.w_bytes) ||
-        overlap(workspace, need, q.z, pl.z_bytes))
-        return CG_ERR_ALIAS;
+    if (workspace_overlaps(pl, workspace, need)) return CG_ERR_ALIAS;
     char* ws = static_cast<char*>(workspace);
     char* xp_a = ws;
     char* xp_b = xp_a + round_up(pl.xp_bytes, 256);
@@ -1031,6 +1072,20 @@ cg_status run_planes(Plan& pl, void* workspace, size_t workspace_bytes, void* st
     if (e != hipSuccess) return CG_ERR_DEVICE;
     e = cg::launch_share_gemm(pl.p, pl.planes_conv ? cg::A_PLANES_CONV : cg::A_PLANES, cg::B_PLANES, s);
     return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
+}
+
+// With scratch memory: the residue route where it pays and the memory holds it, else the digit planes, else the plain
+// kernel.
+cg_status run_with_workspace(Plan& pl, void* workspace, size_t workspace_bytes, void* stream) {
+    if (pl.rns_pays && workspace && aligned(workspace, 16)) {
+        const u64 need = cg::rns_workspace_bytes(pl.rns);
+        if (workspace_bytes >= need && !workspace_overlaps(pl, workspace, need)) {
+            const hipError_t e = cg::launch_share_gemm_rns(pl.rns, workspace, static_cast<hipStream_t>(stream));
+            return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
+        }
+    }
+    if (!pl.planes_ok) return run_direct(pl, stream);
+    return run_planes(pl, workspace, workspace_bytes, stream);
 }
 
 }  // namespace
@@ -1093,8 +1148,7 @@ cg_status cg_share_matmul_ws(const uint64_t* x_i, const uint64_t* x_ip1, const u
                              void* workspace, size_t workspace_bytes, void* stream) {
     Plan pl;
     if (cg_status st = plan_matmul(x_i, x_ip1, y_i, y_ip1, z_i, M, N, K, true, &pl)) return st;
-    if (!pl.planes_ok) return run_direct(pl, stream);
-    return run_planes(pl, workspace, workspace_bytes, stream);
+    return run_with_workspace(pl, workspace, workspace_bytes, stream);
 }
 
 }  // extern "C"
@@ -1134,7 +1188,7 @@ cg_status cg_share_matmul_static(const uint64_t* x_i, const uint64_t* x_ip1, con
     Plan pl;
     if (cg_status st = plan_matmul(x_i, x_ip1, y_i, y_ip1, z_i, M, N, K, true, &pl)) return st;
     if (!pl.planes_ok) return run_direct(pl, stream);
-    if (plan_workspace_bytes(pl) > (u64)CG_STATIC_SCRATCH_BYTES) return CG_ERR_WORKSPACE;
+    if (planes_workspace_bytes(pl) > (u64)CG_STATIC_SCRATCH_BYTES) return CG_ERR_WORKSPACE;
     void* ptr = nullptr;
     if (cg_status st = static_scratch(&ptr)) return st;
     return run_planes(pl, ptr, (size_t)CG_STATIC_SCRATCH_BYTES, stream);
@@ -1150,13 +1204,13 @@ cg_status cg_share_conv2d(const uint64_t* x_i, const uint64_t* x_ip1, const uint
 int cg_share_matmul_prefers_workspace(int64_t M, int64_t N, int64_t K) {
     Plan pl;
     if (plan_matmul(nullptr, nullptr, nullptr, nullptr, nullptr, M, N, K, false, &pl) != CG_OK) return 0;
-    return planes_pay(pl) ? 1 : 0;
+    return pl.rns_pays || planes_pay(pl) ? 1 : 0;
 }
 
 int cg_share_conv2d_prefers_workspace(const cg_conv2d_desc* d) {
     Plan pl;
     if (plan_conv2d(nullptr, nullptr, nullptr, nullptr, nullptr, d, false, &pl) != CG_OK) return 0;
-    return planes_pay(pl) ? 1 : 0;
+    return pl.rns_pays || planes_pay(pl) ? 1 : 0;
 }
 
 size_t cg_share_conv2d_workspace_bytes(const cg_conv2d_desc* d) {
@@ -1170,8 +1224,7 @@ cg_status cg_share_conv2d_ws(const uint64_t* x_i, const uint64_t* x_ip1, const u
                              void* workspace, size_t workspace_bytes, void* stream) {
     Plan pl;
     if (cg_status st = plan_conv2d(x_i, x_ip1, w_i, w_ip1, z_i, d, true, &pl)) return st;
-    if (!pl.planes_ok) return run_direct(pl, stream);
-    return run_planes(pl, workspace, workspace_bytes, stream);
+    return run_with_workspace(pl, workspace, workspace_bytes, stream);
 }
 
 cg_status cg_share_conv2d_dgrad(const uint64_t* g_i, const uint64_t* g_ip1, const uint64_t* w_i,

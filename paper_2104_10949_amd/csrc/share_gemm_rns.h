@@ -1,0 +1,42 @@
+// Internal interface of the residue route (share_gemm_rns.hip): one party's product through residues modulo
+// 18 or 19 pairwise coprime numbers of eight bits.
+#ifndef CG_SHARE_GEMM_RNS_H
+#define CG_SHARE_GEMM_RNS_H
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "share_gemm.h"
+
+namespace cg {
+
+// Longest contraction, in words, for which the exact product stays within the range of the first 18 moduli, and of
+// all 19 (there the bound is the 32-bit accumulator: 2 * K products of at most 2^14).
+constexpr int64_t RNS_K_18 = 5500;
+constexpr int64_t RNS_K_MAX = 65000;
+
+struct RnsParams {
+    const uint64_t *x_a, *x_b, *w_a, *w_b;   // shares: left rows of `words` words, right rows of taps * words words
+    uint64_t* z;                             // [M, N] row-major
+    char *xp, *wp, *rp;                      // residues of the left operand, of the right one, of the result
+    uint64_t x_plane, w_plane, r_plane;      // bytes per modulus
+    int M, N;
+    int words, slices;                       // words of a row per tap, and the 64-word slices they take
+    int x_rows;                              // rows of the left operand (pixels); row x_rows of a plane is zero
+    int conv;                                // the left operand's rows are gathered tap by tap
+    int H, W, Ho, Wo, kh, kw, sh, sw, ph, pw;
+    int nmod;
+    int tile, tiles_m, tiles_n;              // square tiles of 256 or 128
+    double product_cost;                     // modelled time of the product, in steps of a 256 x 256 tile
+    FastDiv div_slices, div_taps, div_howo, div_wo, div_tiles, div_group, div_blocks_n;
+};
+
+// Fills every size of p that follows from M, N, words, x_rows and the window; false where the route does not apply
+// (an operand's plane beyond a buffer view, K beyond RNS_K_MAX).
+bool rns_plan(RnsParams* p);
+// Bytes of scratch memory: xp, wp and rp one after the other, each from a multiple of 256 on.
+uint64_t rns_workspace_bytes(const RnsParams& p);
+hipError_t launch_share_gemm_rns(RnsParams p, void* workspace, hipStream_t stream);
+
+}  // namespace cg
+#endif

@@ -1,0 +1,160 @@
+"""The residue route of the workspace entry points (share_gemm_rns.hip) against the oracle, bit for bit.
+
+The route is taken where it is the faster one and the scratch memory holds it: cg_*_workspace_bytes then asks for more
+than the digit planes take.  Every output is compared with the plain kernel's, rows of it with the oracle's.
+"""
+import numpy as np
+import pytest
+
+from tests.gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def cg():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2104_10949_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.fixture(scope="module")
+def ro():
+    from oracle import ring_oracle
+    return ring_oracle
+
+
+@pytest.fixture(scope="module")
+def wl():
+    from paper_2104_10949_amd import workloads
+    return workloads
+
+
+def digit_plane_bytes(x_rows, x_k, N, K):
+    rows16 = lambda R, k: (R + 15) // 16 * 16 * ((k + 31) // 32) * 256
+    return 2 * rows16(x_rows, x_k) + 2 * rows16(N, K)
+
+
+def poisoned(nbytes):
+    return torch.full((nbytes // 8 + 2,), 0x5A5A5A5A5A5A5A5A, dtype=torch.int64, device="cuda")
+
+
+def sampled(n):   # edges of tiles and a few others
+    return sorted({i for i in (0, 1, 15, 16, 127, 128, 255, 256, n // 2, n - 17, n - 2, n - 1) if 0 <= i < n})
+
+
+# the small tile, the large one, multiples of nothing, the longest K of 18 moduli and the first of 19
+SHAPES = [(1150, 1145, 3001), (1023, 2047, 3001), (2048, 2048, 2048), (3001, 2047, 2050), (2048, 2048, 5500),
+          (1290, 1283, 5501), (1800, 2040, 9002)]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_matmul(cg, ro, wl, M, N, K):
+    say(f"residue route matmul M={M} N={N} K={K}")
+    need = cg.cg_share_matmul_workspace_bytes(M, N, K)
+    assert cg.cg_share_matmul_prefers_workspace(M, N, K) and need > digit_plane_bytes(M, K, N, K)
+    ops = [wl.draw_ring((r, K), 9100 + i) for i, r in enumerate((M, M, N, N))]
+    dev = [cg.to_device(a) for a in ops]
+    plain = cg.cg_share_matmul(*dev)
+    got = cg.cg_share_matmul_ws(*dev, poisoned(need))
+    assert torch.equal(got, plain)
+    rows = sampled(M)
+    want = ro.party_matmul(ops[0][rows], ops[1][rows], ops[2], ops[3])
+    assert np.array_equal(cg.to_host(got[rows]), want)
+
+
+@pytest.mark.parametrize("x_word,w_word", [(0x8080808080808080, 0x8080808080808080), (0x7F7F7F7F7F7F7F7F, 0x8080808080808080),
+                                           (0x7F7F7F7F7F7F7F7F, 0x7F7F7F7F7F7F7F7F), (0x8000000000000000, 0x8000000000000000),
+                                           (0, 0), (1, 0xFFFFFFFFFFFFFFFF)])
+@pytest.mark.parametrize("K", [5500, 9000])
+def test_largest_integers(cg, x_word, w_word, K):
+    """w_b = 0, so both terms of every product are x_word * w_word: with the words of the largest signed-digit value and
+    the longest K of 18 moduli the integer is as near to half the moduli's product as it gets."""
+    M, N = 2048, 2048
+    say(f"residue route constant words {x_word:016x} {w_word:016x} K={K}")
+    signed = lambda w: w - (1 << 64) if w >> 63 else w
+    x = torch.full((M, K), signed(x_word), dtype=torch.int64, device="cuda")
+    w = torch.full((N, K), signed(w_word), dtype=torch.int64, device="cuda")
+    need = cg.cg_share_matmul_workspace_bytes(M, N, K)
+    assert need > digit_plane_bytes(M, K, N, K)
+    got = cg.cg_share_matmul_ws(x, x, w, torch.zeros_like(w), poisoned(need))
+    want = signed(2 * K * x_word * w_word % (1 << 64))
+    assert bool((got == want).all())
+
+
+CONVS = [((32, 16, 16, 256), (256, 3, 3, 256), 1, 1), ((32, 32, 32, 256), (128, 3, 3, 256), 1, 1),
+         ((9, 27, 25, 200), (500, 3, 3, 200), 1, 1), ((12, 40, 38, 192), (520, 5, 5, 192), 2, 2)]
+
+
+@pytest.mark.parametrize("xs,ws,stride,pad", CONVS)
+def test_conv(cg, ro, wl, xs, ws, stride, pad):
+    say(f"residue route conv x={xs} w={ws} stride={stride} pad={pad}")
+    st, pd = (stride, stride), (pad, pad)
+    need = cg.cg_share_conv2d_workspace_bytes(xs, ws, st, pd)
+    K = ws[1] * ws[2] * ws[3]
+    assert cg.cg_share_conv2d_prefers_workspace(xs, ws, st, pd)
+    assert need > digit_plane_bytes(xs[0] * xs[1] * xs[2], xs[3], ws[0], K)
+    ops = [wl.draw_ring(s, 9200 + i) for i, s in enumerate((xs, xs, ws, ws))]
+    dev = [cg.to_device(a) for a in ops]
+    plain = cg.cg_share_conv2d(*dev, stride=st, pad=pd)
+    got = cg.cg_share_conv2d_ws(*dev, poisoned(need), stride=st, pad=pd)
+    assert torch.equal(got, plain)
+    last = ops[0][-1:], ops[1][-1:]
+    want = ro.party_conv2d(*last, ops[2][:40], ops[3][:40], st, pd)
+    assert np.array_equal(cg.to_host(got[-1:, :, :, :40].contiguous()), want)
+
+
+def test_scratch_of_the_digit_planes_is_still_enough(cg, wl):
+    """A caller that brings no more than the digit planes take, or memory the route cannot use, gets the same words."""
+    M, N, K = 2000, 2040, 2044
+    say("residue route with the digit planes' scratch memory")
+    planes, need = digit_plane_bytes(M, K, N, K), cg.cg_share_matmul_workspace_bytes(M, N, K)
+    assert need > planes
+    dev = [cg.to_device(wl.draw_ring((r, K), 9300 + i)) for i, r in enumerate((M, M, N, N))]
+    want = cg.cg_share_matmul(*dev)
+    for nbytes in (planes, need - 16, need):
+        buf = torch.full((nbytes // 8 + 64,), 7, dtype=torch.int64, device="cuda")
+        got = cg.cg_share_matmul_ws(*dev, buf[:nbytes // 8])
+        assert torch.equal(got, want)
+        assert bool((buf[nbytes // 8:] == 7).all())
+
+
+def test_operands_at_odd_words(cg, wl):
+    """Bases that are 8-byte aligned only, K even: word loads and stores, and the digit planes do not apply."""
+    M, N, K = 1408, 1400, 3004
+    say("residue route, operands at odd words")
+    at_odd = lambda shape: torch.empty(shape[0] * shape[1] + 1, dtype=torch.int64, device="cuda")[1:].view(shape)
+    dev = []
+    for i, r in enumerate((M, M, N, N)):
+        dev.append(at_odd((r, K)))
+        dev[-1].copy_(cg.to_device(wl.draw_ring((r, K), 9500 + i)))
+    z = at_odd((M, N))
+    want = cg.cg_share_matmul(*dev)
+    cg.cg_share_matmul_ws(*dev, poisoned(cg.cg_share_matmul_workspace_bytes(M, N, K + 1)), z_i=z)
+    assert torch.equal(z, want)
+
+
+def test_captured(cg, wl):
+    """Three launches and no other node: replays with other operands in the same buffers give their products."""
+    M, N, K = 1150, 1145, 3001
+    say("residue route in a HIP graph")
+    dev = [torch.empty((r, K), dtype=torch.int64, device="cuda") for r in (M, M, N, N)]
+    ws = poisoned(cg.cg_share_matmul_workspace_bytes(M, N, K))
+    z = torch.empty((M, N), dtype=torch.int64, device="cuda")
+    fill = lambda seed: [d.copy_(cg.to_device(wl.draw_ring(tuple(d.shape), seed + i))) for i, d in enumerate(dev)]
+    fill(9400)
+    cg.cg_share_matmul_ws(*dev, ws, z_i=z)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cg.cg_share_matmul_ws(*dev, ws, z_i=z)
+    for seed in (9410, 9420, 9430):
+        fill(seed)
+        want = cg.cg_share_matmul(*dev)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(z, want)
