@@ -35,9 +35,21 @@ INT8_PEAK_TOPS = 5000.0  # MI355X dense int8 MFMA, published: 5.0 POP/s (2 ops p
 HBM_PEAK_GBS = 8000.0    # MI355X HBM3E, published: 8 TB/s
 LAST_LEVEL_CACHE_BYTES = 256 << 20
 DIGIT_MACS_PER_RING_MAC_TRIPLE = 72  # 2 ring products x 36 signed-byte digit pairs per (m, n, k)
+
+
+def ws_macs_per_triple(ws_bytes, x_rows, x_k, N, K):
+    """int8 products per (m, n, k) of the route an *_ws call with the full scratch memory takes: the digit planes (or no
+    scratch memory) 72; the residues, which ask for more than the planes' bytes, 2 per modulus, 18 of them up to K = 5500."""
+    rows16 = lambda R, k: (R + 15) // 16 * 16 * ((k + 31) // 32) * 256
+    if ws_bytes <= 2 * rows16(x_rows, x_k) + 2 * rows16(N, K):
+        return DIGIT_MACS_PER_RING_MAC_TRIPLE
+    return 36 if K <= 5500 else 38
+
+
 WORKLOAD_CONFIG = 4
 # HBM bytes per share_gemm_kernel launch on the config-4 step, from the two rocprofv3 --pmc runs summarised in
-# profiles/share_gemm_config4_hbm_traffic.txt (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000 by the 1 GiB copy calibration).
+# profiles/share_gemm_config4_hbm_traffic.txt, taken with the digit planes on every layer that uses scratch memory
+# (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000 by the 1 GiB copy calibration).
 PROFILED_TRAFFIC_CONFIG4 = {"read_bytes_per_launch": 65.8e6, "write_bytes_per_launch": 22.6e6,
                             "algorithmic_bytes_per_launch": 61.0e6,
                             "conversion_pass_per_scratch_route_layer": {"read_bytes": 47.8e6, "write_bytes": 43.5e6},
@@ -111,6 +123,7 @@ def measure_rows(torch, cg, wl, headline_config):
         z = torch.empty((M, N), dtype=torch.int64, device="cuda")
         ws = torch.empty(cg.cg_share_matmul_workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda")
         ops_per = 2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * M * N * K
+        ws_ops_per = 2.0 * ws_macs_per_triple(ws.numel(), M, K, N, K) * M * N * K
         ms = _timed(torch, lambda: cg.cg_share_matmul(*ops, z_i=z), warm=2, iters=8)
         ms_ws = _timed(torch, lambda: cg.cg_share_matmul_ws(*ops, ws, z_i=z), warm=2, iters=8)
         rows.append({"gemm": [M, N, K], "cg_share_matmul_ms": round(ms, 4),
@@ -118,7 +131,7 @@ def measure_rows(torch, cg, wl, headline_config):
                      "int8_tops": round(ops_per / (ms * 1e-3) / 1e12, 1),
                      "frac_of_peak": round(ops_per / (ms * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4),
                      "cg_share_matmul_ws_ms": round(ms_ws, 4),
-                     "ws_frac_of_peak": round(ops_per / (ms_ws * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4)})
+                     "ws_frac_of_peak": round(ws_ops_per / (ms_ws * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4)})
         if (M, N, K) == (4096, 4096, 4096):
             # the same launches on all-zero shares: control flow and memory traffic do not depend on the data,
             # the power the matrix cores draw does (share words are uniformly random, the worst case), so the gap
@@ -131,7 +144,7 @@ def measure_rows(torch, cg, wl, headline_config):
                 "cg_share_matmul_ms": round(ms0, 4),
                 "frac_of_peak": round(ops_per / (ms0 * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4),
                 "cg_share_matmul_ws_ms": round(ms0_ws, 4),
-                "ws_frac_of_peak": round(ops_per / (ms0_ws * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4)}
+                "ws_frac_of_peak": round(ws_ops_per / (ms0_ws * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4)}
         del ops, z, ws
     out["largest_gemm_shapes"] = rows
     # ---- the other convolution configurations: one step = all their layers, same method as the headline step
@@ -578,10 +591,16 @@ def main() -> int:
             dst.copy_(src)  # reads n*8 bytes, writes n*8 bytes
         torch.cuda.synchronize()
 
-    int8_ops_per_step = 2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * total_mnk
+    def ops_of(L) -> float:   # int8 operations that the timed route of one launch executes
+        macs = DIGIT_MACS_PER_RING_MAC_TRIPLE
+        if prefers_ws(L):
+            x_rows, x_k = (L.B * L.H * L.W, L.Cin) if L.kind == "conv" else (L.M, L.K)
+            macs = ws_macs_per_triple(ws_bytes(L), x_rows, x_k, L.gemm[1], L.gemm[2])
+        return 2.0 * macs * L.mnk
+    int8_ops_per_step = sum(ops_of(L) * L.repeat for L in layers)
     achieved_tops = int8_ops_per_step / (kernel_ms_sum * 1e-3) / 1e12
     big = max(range(len(layers)), key=lambda i: layers[i].mnk)
-    big_tops = 2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * layers[big].mnk / (per_layer_ms[big] * 1e-3) / 1e12
+    big_tops = ops_of(layers[big]) / (per_layer_ms[big] * 1e-3) / 1e12
     roofline = {
         "bound": "mfma", "kernel": "share_gemm_kernel / rns_gemm_kernel (int8 MFMA, i32 accumulate)",
         "achieved": round(achieved_tops, 2), "peak": INT8_PEAK_TOPS, "unit": "TOP/s",
@@ -589,20 +608,19 @@ def main() -> int:
         "launches_per_step": launches,
         "avg_launch_ms": round(kernel_ms_sum / launches, 5),
         "ops_per_launch": int8_ops_per_step / launches,
-        # layers that take the residue route (through scratch memory) execute half of the digit form's products
-        "ops_counted": "digit form, 144 int8 operations per (m, n, k), whatever the route executes",
+        "ops_counted": "those of the route taken: 144 per (m, n, k) with digits, 72 or 76 with residues",
         "largest_layer": {"name": layers[big].name, "gemm": list(layers[big].gemm),
                           "ms": round(per_layer_ms[big], 5), "achieved": round(big_tops, 2),
                           "frac": round(big_tops / INT8_PEAK_TOPS, 4)},
         # every layer whose M*N*K equals the largest one's (several layers of the VGG-shaped stack tie)
         "largest_layers": [{"name": L.name, "gemm": list(L.gemm), "ms": round(ms, 5),
-                            "frac": round(2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * L.mnk / (ms * 1e-3) / 1e12
+                            "frac": round(ops_of(L) / (ms * 1e-3) / 1e12
                                           / INT8_PEAK_TOPS, 4)}
                            for L, ms in zip(layers, per_layer_ms) if L.mnk == layers[big].mnk],
         # the same layers as one figure: their int8 ops over their summed time
         "largest_layers_together": (lambda ties: {
             "layers": len(ties), "ms": round(sum(ms for _, ms in ties), 5),
-            "frac": round(sum(2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * L.mnk for L, _ in ties)
+            "frac": round(sum(ops_of(L) for L, _ in ties)
                           / (sum(ms for _, ms in ties) * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4)})(
             [(L, ms) for L, ms in zip(layers, per_layer_ms) if L.mnk == layers[big].mnk]),
         "traffic": PROFILED_TRAFFIC_CONFIG4 if args.config == WORKLOAD_CONFIG else None,
@@ -610,7 +628,7 @@ def main() -> int:
     # Per layer: measured time against t_roof = max(int8 ops / peak, algorithmic bytes / HBM peak) and the larger term.
     per_layer = []
     for L, ms in zip(layers, per_layer_ms):
-        t_mfma = 2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * L.mnk / (INT8_PEAK_TOPS * 1e12)
+        t_mfma = ops_of(L) / (INT8_PEAK_TOPS * 1e12)
         t_hbm = L.algorithmic_bytes / 8e12
         per_layer.append({"name": L.name, "gemm": list(L.gemm), "repeat": L.repeat, "us": round(ms * 1e3, 2),
                           "t_roof_us": round(max(t_mfma, t_hbm) * 1e6, 2), "bound": "mfma" if t_mfma >= t_hbm else "hbm",
@@ -637,7 +655,7 @@ def main() -> int:
     if args.layers:
         for L, ms in zip(layers, per_layer_ms):
             m, n, k = L.gemm
-            tops = 2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * L.mnk / (ms * 1e-3) / 1e12
+            tops = ops_of(L) / (ms * 1e-3) / 1e12
             print(f"{L.name:28s} M={m:7d} N={n:5d} K={k:5d} x{L.repeat}  {ms * 1e3:9.1f} us  "
                   f"{3.0 * L.mnk / (ms * 1e-3):.3e} ringMAC/s  {tops:7.1f} TOP/s ({100 * tops / INT8_PEAK_TOPS:4.1f}%)  "
                   f"{L.algorithmic_bytes / (ms * 1e-3) / 1e9:7.0f} GB/s", file=sys.stderr)
