@@ -729,13 +729,14 @@ cg_status plan_matmul(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t
         if (!trans_y) pl.bmode = cg::B_WIDE;
     }
     // (a product of few rows is a few microseconds on the kernel of its own: converting its operands first would
-    // cost more than the product)
-    pl.planes_ok = vec && !trans_x && !trans_y && !long_rows && !cg::share_gemm_small_applies(p);
+    // cost more than the product; other small ones keep the digit route for callers that ask for it)
+    const bool few_rows = M <= 64 && cg::share_gemm_small_applies(p);
+    pl.planes_ok = vec && !trans_x && !trans_y && !long_rows && !few_rows;
     pl.planes_conv = false;
     pl.x_rows = M; pl.x_k = K;
     pl.xp_bytes = cg::planes_bytes(M, K); pl.wp_bytes = cg::planes_bytes(N, K);
     pl.x_bytes = (u64)mk * 8; pl.w_bytes = (u64)nk * 8; pl.z_bytes = (u64)mn * 8;
-    if (!trans_x && !trans_y && !long_rows && !cg::share_gemm_small_applies(p)) plan_rns(&pl, M, K, false);
+    if (!trans_x && !trans_y && !long_rows && !few_rows) plan_rns(&pl, M, K, false);
     *out = pl;
     return CG_OK;
 }

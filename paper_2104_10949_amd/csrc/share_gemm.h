@@ -108,7 +108,7 @@ static const int MAX_TILE_ROWS = 256;
 
 hipError_t launch_share_gemm(const GemmParams& p, int amode, int bmode, hipStream_t stream);
 
-// Products with few rows on the left (share_gemm_small.hip): row-major operands that A_LINEAR_VEC / B_VEC
+// Products with few rows on the left or few blocks of z (share_gemm_small.hip): row-major operands that A_LINEAR_VEC / B_VEC
 // address (K even, 16-byte aligned bases, lda == K).  `applies` says whether the launcher takes p.
 bool share_gemm_small_applies(const GemmParams& p);
 hipError_t launch_share_gemm_small(const GemmParams& p, hipStream_t stream);

@@ -1,5 +1,5 @@
 // The party's local product (CryptGPU Sec. III-B, "Multiplication" and "Convolutions and matrix
-// multiplication") for a left operand of few rows: fully connected layers at small batch.
+// multiplication") for a left operand of few rows (fully connected layers at small batch) and for other small ones.
 //
 // Such a product is a few microseconds of matrix work, so what counts is the length of the chain
 // launch -> load -> split -> multiply -> store and how many compute units share it, not the rate of any
@@ -27,9 +27,14 @@ constexpr int SMALL_MAX_SLICES = 511 * SMALL_WAVES;  // a wave's i32 accumulator
 // K = 128 .. 25088): with one 16-row block every shape up to the slice limit (4.4 us against 13 us at K = 128,
 // 281 against 379 us at 8 x 4096 x 25088); with two to four row blocks the right operand is read once per row
 // block, and the tiled kernel wins from about 4600 (16 x 16 block, slice) units on.
-constexpr int SMALL_MAX_ROWS = 64;
+// With more rows the same unit line holds as long as the grid stays below three blocks per compute unit (M = 66 ..
+// 1024, N = 10 .. 512, K = 64 .. 2048, kernel time against share_gemm_kernel): 128 x 128 x 784 14.6 -> 9.6 us,
+// 256 x 256 x 128 11.7 -> 4.5, 1024 x 64 x 512 14.3 -> 9.2, 192 x 64 x 2048 13.5 -> 10.6; beyond, 512 x 512 x 64 9.7 -> 10.9
+// and 1024 x 512 x 64 10.1 -> 20.5 (the fold of each block costs more than its products), and 66 x 256 x 2048 (5120
+// units) 14.5 -> 15.6.
 constexpr int SMALL_ONE_BLOCK_ROWS = 16;
 constexpr int64_t SMALL_MAX_UNITS = 4608;
+constexpr int64_t SMALL_MANY_ROWS = 64, SMALL_MANY_ROWS_TILES = 768;
 // K is split over blocks as well until the grid has this many blocks (one block per compute unit fits)
 constexpr int64_t SMALL_TARGET_BLOCKS = 256;
 
@@ -184,14 +189,16 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void share_gemm_small_kernel(cons
 
 }  // namespace
 
-// Row-major operands with 16-byte loads (K even, 16-byte aligned bases), few rows on the left, and a K whose
+// Row-major operands with 16-byte loads (K even, 16-byte aligned bases), few blocks of z, and a K whose
 // slices, shared out over a block's waves, fit one fold.
 bool share_gemm_small_applies(const GemmParams& p) {
     const int64_t nk = (p.K + 31) / 32;
-    if (p.lda != p.K || nk > SMALL_MAX_SLICES || p.M > SMALL_MAX_ROWS) return false;
+    if (p.lda != p.K || nk > SMALL_MAX_SLICES) return false;
     if ((p.N + 15) / 16 > (1 << 20)) return false;   // grid size in threads stays below 2^32
     if (p.M <= SMALL_ONE_BLOCK_ROWS) return true;
-    return (int64_t)((p.M + 15) / 16) * ((p.N + 15) / 16) * nk <= SMALL_MAX_UNITS;
+    const int64_t tiles = ((int64_t)p.M + 15) / 16 * (((int64_t)p.N + 15) / 16);
+    if (p.M > SMALL_MANY_ROWS && tiles > SMALL_MANY_ROWS_TILES) return false;
+    return tiles * nk <= SMALL_MAX_UNITS;
 }
 
 hipError_t launch_share_gemm_small(const GemmParams& p, hipStream_t stream) {
