@@ -23,5 +23,13 @@ hipError_t launch_prf_combine(const uint64_t* z, const uint64_t* msg, uint64_t* 
                               const uint8_t* key_mask, uint64_t mask_nonce, bool add_mask, hipStream_t stream,
                               bool xor_mode = false);
 
+// How a call on the words first .. first + n - 1 is shared out (n >= 1): `blocks` workgroups of `waves` waves, each with
+// a run of `per_wg` chunks of 64 AES blocks.
+struct PrfSplit {
+    uint64_t blocks;
+    uint32_t waves, per_wg;
+};
+PrfSplit prf_split(uint64_t first, size_t n);
+
 }  // namespace cg
 #endif

