@@ -224,6 +224,9 @@ __global__ __launch_bounds__(64 * PRF_MAX_WAVES) void prf_combine_kernel(const u
     __shared__ __attribute__((aligned(16))) u32 tables[2 * 256 * 64];  // T0 then T2, one copy per bank
     __shared__ uint4 group_c2[NS][PRF_MAX_GROUPS];
     __shared__ u32 group_c1[NS][PRF_MAX_GROUPS];
+    // The keys first: their way from the argument buffer passes while the tables are filled.
+    RoundKeys<NS> key;
+    key.load(keys);
     // 16 bytes, i.e. four of the 64 copies, of an entry of both tables per thread and trip
 #pragma unroll 4
     for (u32 i = threadIdx.x; i < 256 * 16; i += blockDim.x) {
@@ -256,8 +259,6 @@ __global__ __launch_bounds__(64 * PRF_MAX_WAVES) void prf_combine_kernel(const u
         }
     }
     __syncthreads();
-    RoundKeys<NS> key;
-    key.load(keys);
     for (u64 ch = ch0 + wave; ch < ch_end; ch += waves) {
         const u32 g = (u32)((ch >> 2) - g0);
         u32 c1[NS], ct[NS][4];
@@ -313,8 +314,9 @@ __global__ __launch_bounds__(64 * PRF_MAX_WAVES) void prf_combine_kernel(const u
 }  // namespace
 
 // The tables take a compute unit's LDS, so one workgroup runs per compute unit.  Short calls spread over all of them,
-// with eight waves at least, which fill the tables faster than one wave would; longer ones take 16 waves and a run of
-// chunks each.  A run longer than a workgroup has room for is cut so that every compute unit gets the same number of
+// longer ones take a run of chunks each, always with 16 waves, which fill the tables together: 100 words (zero share)
+// 5.67 us with eight waves, 5.53 with 16, 5.35 with the keys requested ahead of the tables (5.37 with one table fill of
+// 16 waves and no shared rounds); from 2^21 words on all three are equal.  A run longer than a workgroup has room for is cut so that every compute unit gets the same number of
 // equal runs: with full runs and a shorter rest, a call of 70 million words (257 .. 511 runs) took the time of two whole rounds, 1208 us
 // where it now takes 648 (zero share).
 PrfSplit prf_split(uint64_t first, size_t n) {
@@ -323,7 +325,7 @@ PrfSplit prf_split(uint64_t first, size_t n) {
     const u64 per_cu = (chunks + CUS - 1) / CUS;
     const u64 rounds = (per_cu + PRF_MAX_CHUNKS - 1) / PRF_MAX_CHUNKS;
     PrfSplit s;
-    s.waves = (u32)(per_cu < 8 ? 8 : (per_cu < PRF_MAX_WAVES ? per_cu : PRF_MAX_WAVES));
+    s.waves = PRF_MAX_WAVES;
     s.per_wg = (u32)((chunks + CUS * rounds - 1) / (CUS * rounds));
     s.blocks = (chunks + s.per_wg - 1) / s.per_wg;
     return s;

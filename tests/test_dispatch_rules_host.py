@@ -57,6 +57,7 @@ def test_prf_runs_are_even_over_the_compute_units(rules):
     for (first, n), (blocks, waves, per_wg) in zip(cases, rules("prf", cases)):
         chunks = (first + n - 1) // 128 - first // 128 + 1
         assert (blocks - 1) * per_wg < chunks <= blocks * per_wg < 2 ** 62, (first, n)
-        assert 1 <= per_wg <= 2044 and 1 <= waves <= 16 and blocks < 2 ** 31, (first, n)
+        assert 1 <= per_wg <= 2044 and blocks < 2 ** 31, (first, n)
+        assert waves == 16, (first, n)   # short calls too: they are little more than the fill of the tables
         slowest = -(-blocks // 256) * per_wg
         assert slowest <= max(1.05 * chunks / 256, chunks / 256 + 1), (first, n, blocks, per_wg)

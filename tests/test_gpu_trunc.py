@@ -41,8 +41,8 @@ def test_prf_words_match_the_oracle(cg, ro, n, first):
 
 
 # a wave takes 64 blocks = 128 words, 256 blocks = 512 words share the constants of the first two rounds, a workgroup
-# takes 8 waves up to 262144 words, then 9 to 16, then runs of chunks: around each of these, and where the block index
-# carries into byte 1, byte 2 and its upper word
+# takes one chunk up to 32768 words, a chunk for each of its 16 waves up to 524288, then runs of chunks: around each of these, and
+# where the block index carries into byte 1, byte 2 and its upper word
 @pytest.mark.parametrize("n,first", [(127, 1), (128, 0), (129, 383), (514, 511), (1500, 2 ** 17 - 700), (3000, 2 ** 33 - 1001),
                                      (262144, 6), (262145, 127), (300001, 2 ** 25 - 150001), (524288, 510), (560003, 12)])
 def test_prf_streams_at_the_edges_of_their_work_split(cg, ro, wl, n, first):
