@@ -27,16 +27,19 @@ constexpr int SMALL_MAX_SLICES = 511 * SMALL_WAVES;  // a wave's i32 accumulator
 // K = 128 .. 25088): with one 16-row block every shape up to the slice limit (4.4 us against 13 us at K = 128,
 // 281 against 379 us at 8 x 4096 x 25088); with two to four row blocks the right operand is read once per row
 // block, and the tiled kernel wins from about 4600 (16 x 16 block, slice) units on.
-// With more rows the same unit line holds as long as the grid stays below three blocks per compute unit (M = 66 ..
-// 1024, N = 10 .. 512, K = 64 .. 2048, kernel time against share_gemm_kernel): 128 x 128 x 784 14.6 -> 9.6 us,
-// 256 x 256 x 128 11.7 -> 4.5, 1024 x 64 x 512 14.3 -> 9.2, 192 x 64 x 2048 13.5 -> 10.6; beyond, 512 x 512 x 64 9.7 -> 10.9
-// and 1024 x 512 x 64 10.1 -> 20.5 (the fold of each block costs more than its products), and 66 x 256 x 2048 (5120
-// units) 14.5 -> 15.6.
+// With more than 64 rows the same unit line holds and the rounds of the chip set a second one (a block fills a compute
+// unit; 1030 shapes with M = 65 .. 12288, N = 10 .. 2448, K = 32 .. 14720, whole calls against share_gemm_kernel).  Up to
+// 256 blocks: 128 x 128 x 784 14.6 -> 9.6 us, 256 x 256 x 128 11.7 -> 4.5, 1024 x 64 x 512 14.3 -> 9.2.  Two rounds: won up to
+// 13 slices (0.95 of the tiled kernel's time at worst, 1.04 at 14).  Three: a single slice is not worth three folds
+// (12288 x 16 x 32 6.6 -> 8.1 us), two and more are (0.91 of the time at 12288 x 16 x 64).  A fourth round never pays (512 x 512 x 64
+// 9.7 -> 10.9).  The tiled kernel needs no clearing launch when it adds to z, so those lines lie lower: 11 slices in two
+// rounds (0.96; 1.11 at 12), 2 and 3 in three (0.92; 1.08 at four).
 constexpr int SMALL_ONE_BLOCK_ROWS = 16;
 constexpr int64_t SMALL_MAX_UNITS = 4608;
-constexpr int64_t SMALL_MANY_ROWS = 64, SMALL_MANY_ROWS_TILES = 768;
-// K is split over blocks as well until the grid has this many blocks (one block per compute unit fits)
-constexpr int64_t SMALL_TARGET_BLOCKS = 256;
+constexpr int SMALL_MANY_ROWS = 64;
+// K is split over blocks as well as long as the grid stays within one round (one block per compute unit fits):
+// 320 x 29 x 3680, 40 blocks of z, split in 7 (280 blocks) 18.5 us, in 6 (240) 10.7
+constexpr int64_t SMALL_ROUND_BLOCKS = 256;
 
 // Sixteen words (eight 16-byte registers, word 2i in v[i].xy and word 2i+1 in v[i].zw) -> eight digit
 // registers: byte 4j + t of d[l] is digit l of word 4j + t.
@@ -197,8 +200,12 @@ bool share_gemm_small_applies(const GemmParams& p) {
     if ((p.N + 15) / 16 > (1 << 20)) return false;   // grid size in threads stays below 2^32
     if (p.M <= SMALL_ONE_BLOCK_ROWS) return true;
     const int64_t tiles = ((int64_t)p.M + 15) / 16 * (((int64_t)p.N + 15) / 16);
-    if (p.M > SMALL_MANY_ROWS && tiles > SMALL_MANY_ROWS_TILES) return false;
-    return tiles * nk <= SMALL_MAX_UNITS;
+    if (tiles * nk > SMALL_MAX_UNITS) return false;
+    if (p.M <= SMALL_MANY_ROWS) return true;
+    const int64_t rounds = (tiles + SMALL_ROUND_BLOCKS - 1) / SMALL_ROUND_BLOCKS;
+    if (rounds == 1) return true;
+    if (rounds == 2) return nk <= (p.z_add ? 11 : 13);
+    return rounds == 3 && nk >= 2 && (nk <= 3 || !p.z_add);
 }
 
 hipError_t launch_share_gemm_small(const GemmParams& p, hipStream_t stream) {
@@ -207,8 +214,8 @@ hipError_t launch_share_gemm_small(const GemmParams& p, hipStream_t stream) {
     // K is split over blocks as well when the blocks of z alone would leave compute units idle, as long as a
     // wave keeps at least two slices
     int64_t ksplit = 1;
-    if (tiles < SMALL_TARGET_BLOCKS) {
-        ksplit = (SMALL_TARGET_BLOCKS + tiles - 1) / tiles;
+    if (tiles < SMALL_ROUND_BLOCKS) {
+        ksplit = SMALL_ROUND_BLOCKS / tiles;
         const int64_t most = nk / (2 * SMALL_WAVES);
         if (ksplit > most) ksplit = most;
         if (ksplit < 1) ksplit = 1;

@@ -12,12 +12,18 @@ PROGRAM = r"""
 #include <stdio.h>
 #include <string.h>
 #include "prf.h"
+#include "share_gemm.h"
 int main(int argc, char** argv) {
-    unsigned long long a[4];
-    char what[16];
-    while (scanf("%15s %llu %llu", what, a, a + 1) == 3) {
-        const cg::PrfSplit s = cg::prf_split(a[0], a[1]);
-        printf("%llu %u %u\n", (unsigned long long)s.blocks, s.waves, s.per_wg);
+    long long a[4];
+    while (scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3) == 4) {
+        if (!strcmp(argv[1], "prf")) {
+            const cg::PrfSplit s = cg::prf_split((uint64_t)a[0], (size_t)a[1]);
+            printf("%llu %u %u\n", (unsigned long long)s.blocks, s.waves, s.per_wg);
+        } else {   // small: M N K accumulate
+            cg::GemmParams p = {};
+            p.M = (int)a[0]; p.N = (int)a[1]; p.K = p.lda = (int)a[2]; p.z_add = (int)a[3];
+            printf("%d\n", cg::share_gemm_small_applies(p) ? 1 : 0);
+        }
     }
 }
 """
@@ -40,8 +46,8 @@ def rules(tmp_path_factory):
                     "-Wl,-rpath," + os.path.join(rocm, "lib"), "-o", exe], check=True)
 
     def ask(what, rows):
-        text = "".join(what + " " + " ".join(str(v) for v in r) + "\n" for r in rows)
-        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=60).stdout
+        text = "".join(" ".join(str(v) for v in (tuple(r) + (0, 0, 0))[:4]) + "\n" for r in rows)
+        out = subprocess.run([exe, what], input=text, capture_output=True, text=True, check=True, timeout=60).stdout
         return [tuple(int(v) for v in line.split()) for line in out.splitlines()]
 
     return ask
@@ -61,3 +67,18 @@ def test_prf_runs_are_even_over_the_compute_units(rules):
         assert waves == 16, (first, n)   # short calls too: they are little more than the fill of the tables
         slowest = -(-blocks // 256) * per_wg
         assert slowest <= max(1.05 * chunks / 256, chunks / 256 + 1), (first, n, blocks, per_wg)
+
+
+# (M, N, K), taken by the plain call, taken by the accumulating call: both sides of every line for more than 64 rows
+SMALL = [((128, 128, 784), 1, 1), ((65, 1, 2), 1, 1), ((80, 16, 28800), 1, 1), ((4096, 16, 576), 1, 1),
+         ((4112, 16, 32), 1, 1), ((4112, 16, 352), 1, 1), ((4112, 16, 354), 1, 0), ((4112, 16, 416), 1, 0), ((4112, 16, 418), 0, 0),
+         ((8192, 16, 32), 1, 1), ((8208, 16, 32), 0, 0), ((8208, 16, 34), 1, 1), ((12288, 16, 32), 0, 0), ((12288, 16, 64), 1, 1),
+         ((12288, 16, 96), 1, 1), ((12288, 16, 98), 1, 0), ((12288, 16, 192), 1, 0), ((12288, 16, 194), 0, 0),
+         ((12289, 16, 64), 0, 0), ((512, 512, 64), 0, 0), ((96, 768, 416), 1, 0), ((64, 768, 512), 1, 1), ((64, 16384, 32), 1, 1),
+         ((64, 1152, 512), 1, 1), ((64, 1168, 512), 0, 0), ((16, 65536, 4096), 1, 1)]
+
+
+def test_small_products_of_more_than_64_rows_by_rounds_of_the_chip(rules):
+    got = rules("small", [s + (0,) for s, _, _ in SMALL])
+    acc = rules("small", [s + (1,) for s, _, _ in SMALL])
+    assert [(s, g[0], a[0]) for (s, _, _), g, a in zip(SMALL, got, acc)] == SMALL

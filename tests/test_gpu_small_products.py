@@ -13,6 +13,8 @@ torch = pytest.importorskip("torch")
 SHAPES = [(65, 1, 2), (66, 17, 34), (128, 128, 784), (127, 129, 62), (1000, 10, 130), (300, 33, 1026), (128, 10, 2048),
           (80, 16, 9000),                        # K split over blocks
           (12288, 16, 64), (12289, 16, 64),      # 768 blocks of z, and one row of them more
+          (8208, 16, 32), (12288, 16, 98), (96, 768, 416), (96, 768, 418),   # lines of three and of two rounds
+          (320, 29, 3680),                       # K split, and the grid still one round
           (96, 768, 512), (96, 769, 512)]        # 4608 (block, slice) units, and beyond
 
 
