@@ -1,6 +1,7 @@
 """The rules that share a call out over the chip, evaluated on the host: the library's own objects are linked into a small
 program that prints what the launchers decide.  No GPU is used."""
 import os
+import re
 import subprocess
 
 import pytest
@@ -82,3 +83,18 @@ def test_small_products_of_more_than_64_rows_by_rounds_of_the_chip(rules):
     got = rules("small", [s + (0,) for s, _, _ in SMALL])
     acc = rules("small", [s + (1,) for s, _, _ in SMALL])
     assert [(s, g[0], a[0]) for (s, _, _), g, a in zip(SMALL, got, acc)] == SMALL
+
+
+def test_residue_kernels_keep_their_accumulators_in_registers(tmp_path):
+    """The product kernels wait for their loads by count: a spilled register's reload waits for all of them, every step."""
+    llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+    fat, elf = str(tmp_path / "fat"), str(tmp_path / "elf")
+    subprocess.run([os.path.join(llvm, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + fat,
+                    os.path.join(CSRC, "share_gemm_rns.o"), "/dev/null"], check=True)
+    subprocess.run([os.path.join(llvm, "clang-offload-bundler"), "--unbundle", "--type=o", "--input=" + fat, "--output=" + elf,
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
+    notes = subprocess.run([os.path.join(llvm, "llvm-readelf"), "--notes", elf], capture_output=True, text=True, check=True).stdout
+    names = re.findall(r"\.name:\s+(\S*rns_gemm\S*)", notes)
+    assert len(names) == 4
+    assert set(re.findall(r"\.vgpr_spill_count:\s+(\d+)", notes)) == {"0"}
+    assert set(re.findall(r"\.private_segment_fixed_size:\s+(\d+)", notes)) == {"0"}
