@@ -680,17 +680,22 @@ void plan_rns(Plan* pl, int64_t x_rows, int64_t words, bool conv) {
     r.kh = conv ? p.kh : 1; r.kw = conv ? p.kw : 1;
     if (!cg::rns_plan(&r)) return;
     // Both routes in seconds, from measurements on MI355X.  Plain kernel: 144 operations per (m, n, k) of its 128 x 64
-    // tiles at 2.6e15 a second, 1.15 times that with 8-byte loads, and 8 microseconds; 0.93 of it where the digit planes
-    // pay.  Residues: 16 + 2 * nmod bytes per word pair converted at 5.2 TB/s, 2 * nmod + 8 per output combined at
-    // 8.5 TB/s, 1.5 microseconds per step of the product, and 12 microseconds for three launches that do not fill the
-    // chip at both ends.  They must win by a margin to be preferred.
+    // tiles at 2.6e15 a second, 1.2 times that with 8-byte loads, 1.3 times with 8-byte gathers (1.2 to 1.8 over 650 layers,
+    // median 1.55), 8 microseconds, and up to 8 more where the tiles are so few that K is split; 0.93 of it where the digit planes
+    // pay.  Residues: 16 + 2 * nmod bytes per word pair converted at 4.9 TB/s (4.0 with 8-byte loads), 2 * nmod + 8 per output
+    // combined at 8.5 TB/s (measured up to 16384 x 16384 outputs), the product as rns_plan models it, and 12
+    // microseconds for three launches that do not fill the chip at both ends.  They must win by a margin to be preferred,
+    // a little more on strided layers, where the model scatters most: of 3400 random layers and 1300 products, none
+    // that is taken was more than 2 % slower than without residues.
     const double up_m = (double)((p.M + (int64_t)127) / 128 * 128), up_n = (double)((p.N + (int64_t)63) / 64 * 64);
-    double best = 144.0 * up_m * up_n * (double)p.K / 2.6e15 * (pl->planes_ok ? 1.0 : 1.15) + 8.0e-6;
+    const double work = 144.0 * up_m * up_n * (double)p.K / 2.6e15 * (pl->planes_ok ? 1.0 : conv ? 1.3 : 1.2);
+    double best = work + 8.0e-6;
+    if (up_m * up_n < 256.0 * 128.0 * 64.0) best += work < 8.0e-6 ? work : 8.0e-6;
     if (planes_pay(*pl)) best *= 0.93;
     const double pairs = ((double)r.x_rows + (double)p.N * r.kh * r.kw) * r.slices * 64.0;
-    const double rns = pairs * (16.0 + 2.0 * r.nmod) / 5.2e12 + (double)r.r_plane * (2.0 * r.nmod + 8.0) / 8.5e12 +
-                       1.5e-6 * r.product_cost + 12.0e-6;
-    pl->rns_pays = rns < 0.9 * best;
+    const double rns = pairs * (16.0 + 2.0 * r.nmod) / (words % 2 == 0 ? 4.9e12 : 4.0e12) +
+                       (double)r.r_plane * (2.0 * r.nmod + 8.0) / 8.5e12 + 1.0e-6 * r.product_us + 12.0e-6;
+    pl->rns_pays = rns < (conv && (p.sh > 1 || p.sw > 1) ? 0.90 : 0.92) * best;
 }
 
 cg_status plan_matmul(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t* y_i, const uint64_t* y_ip1,

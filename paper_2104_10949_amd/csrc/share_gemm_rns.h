@@ -27,7 +27,7 @@ struct RnsParams {
     int H, W, Ho, Wo, kh, kw, sh, sw, ph, pw;
     int nmod;
     int tile, tiles_m, tiles_n;              // square tiles of 256 or 128
-    double product_cost;                     // modelled time of the product, in steps of a 256 x 256 tile
+    double product_us;                       // modelled time of the product
     FastDiv div_slices, div_taps, div_howo, div_wo, div_tiles, div_group, div_blocks_n;
 };
 

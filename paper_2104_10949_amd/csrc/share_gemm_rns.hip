@@ -513,25 +513,34 @@ bool rns_plan(RnsParams* p) {
         return false;
     p->x_plane = x_plane;
     p->w_plane = w_plane;
-    // Tile: the less modelled time in rounds of the chip (one block of the large tile per compute unit, two of the small
-    // one), a round in steps of the large tile, 1.5 microseconds each, plus its fixed part.  Small against large tile,
-    // whole calls: 423 / 369 us at 2048^3, 374 / 342 us at 1023 x 2047 x 3001, but 89 / 122 us at 1000 x 777 x 1531 and
-    // 194 / 249 us on the 3x3 layer 16 x 16 x 256 -> 256 at batch 32, where the large one leaves most of its last round
-    // empty.  A gathered operand is read once per tap, from the L2: the small tile's extra reads cost less there.
-    const struct { int edge, slots; double step, fixed; } shapes[2] = {
-        {256, 256, 1.0, 3.0}, {128, 512, p->conv ? 0.5 : 0.6, 2.0}};
+    // Tile: the less modelled time, in microseconds.  A step is a tap of a slice.  The chip takes 256 of the large tile's
+    // blocks at a time and 512 of the small one's; a part of the time goes with the rounds and a part with the blocks (a
+    // compute unit with one small block runs it faster).  Strided layers leave half of every line they gather unused.
+    // The residues that are read once (those of a matrix, of a filter) come on top.  Small against large tile, whole
+    // calls: 423 / 369 us at 2048^3, 374 / 342 us at 1023 x 2047 x 3001, but 89 / 122 us at 1000 x 777 x 1531; 3x3 layer
+    // 16 x 16 x 256 -> 256 at batch 32 200 / 210 us, the 5x5 one 480 / 468 us.  Coefficients: least squares over whole calls with either
+    // tile forced, 1300 products (M, N 65 .. 16384, K 64 .. 65000) and 1900 layers (1 .. 64 images of 4 x 4 .. 128 x 128, 16 .. 2048
+    // channels, windows of 1 .. 7, strides of 1 .. 3); eight in ten within 6 % for the large tile, 20 % for the small one.
+    struct Shape { int edge, slots; double round_step, block_step, fixed, per_mb; };
+    static const Shape shapes[3][2] = {   // rows of a matrix, patches, patches of a strided layer
+        {{256, 256, 0.96, 0.37, 6.0, 0.012}, {128, 512, 0.31, 0.54, 2.5, 0.075}},
+        {{256, 256, 1.08, 0.27, 5.5, 0.05}, {128, 512, 0.34, 0.48, 1.7, 0.13}},
+        {{256, 256, 1.07, 0.34, 7.4, 0.06}, {128, 512, 0.33, 0.68, 3.0, 0.12}}};
+    const int kind = !p->conv ? 0 : p->sh == 1 && p->sw == 1 ? 1 : 2;
+    const double steps = (double)(taps * p->slices), once_mb = 1.0e-6 * p->nmod * (double)(w_plane + (p->conv ? 0 : x_plane));
     double best = 0.0;
-    for (const auto& t : shapes) {
+    for (const Shape& t : shapes[kind]) {
         const int64_t tiles_m = (p->M + (int64_t)t.edge - 1) / t.edge, tiles_n = (p->N + (int64_t)t.edge - 1) / t.edge;
-        const int64_t rounds = (tiles_m * tiles_n * p->nmod + t.slots - 1) / t.slots;
-        const double cost = (double)rounds * ((double)(taps * p->slices) * t.step + t.fixed);
+        const int64_t blocks = tiles_m * tiles_n * p->nmod, rounds = (blocks + t.slots - 1) / t.slots;
+        const double cost = steps * ((double)rounds * t.round_step + (double)blocks / t.slots * t.block_step) +
+                            (double)rounds * t.fixed + once_mb * t.per_mb;
         if (best != 0.0 && cost >= best) continue;
         best = cost;
         p->tile = t.edge;
         p->tiles_m = (int)tiles_m; p->tiles_n = (int)tiles_n;
     }
     p->r_plane = (uint64_t)p->tiles_m * p->tiles_n * p->tile * p->tile;
-    p->product_cost = best;
+    p->product_us = best;
     p->div_slices = make_fast_div((uint32_t)p->slices);
     p->div_taps = make_fast_div((uint32_t)taps);
     p->div_howo = make_fast_div((uint32_t)(p->conv ? p->Ho * p->Wo : 1));

@@ -14,12 +14,20 @@ PROGRAM = r"""
 #include <string.h>
 #include "prf.h"
 #include "share_gemm.h"
+#include "share_gemm_rns.h"
 int main(int argc, char** argv) {
-    long long a[4];
-    while (scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3) == 4) {
+    long long a[9];
+    while (scanf("%lld %lld %lld %lld %lld %lld %lld %lld %lld", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6, a + 7, a + 8) == 9) {
         if (!strcmp(argv[1], "prf")) {
             const cg::PrfSplit s = cg::prf_split((uint64_t)a[0], (size_t)a[1]);
             printf("%llu %u %u\n", (unsigned long long)s.blocks, s.waves, s.per_wg);
+        } else if (!strcmp(argv[1], "residues")) {   // M N words x_rows gathered kh kw stride_h stride_w
+            cg::RnsParams p = {};
+            p.M = (int)a[0]; p.N = (int)a[1]; p.words = (int)a[2]; p.x_rows = (int)a[3]; p.conv = (int)a[4];
+            p.kh = (int)a[5]; p.kw = (int)a[6]; p.sh = (int)a[7]; p.sw = (int)a[8];
+            p.Ho = p.Wo = 1;
+            const bool fits = cg::rns_plan(&p);
+            printf("%d %d %llu\n", fits ? p.tile : 0, p.nmod, fits ? (unsigned long long)cg::rns_workspace_bytes(p) : 0ull);
         } else {   // small: M N K accumulate
             cg::GemmParams p = {};
             p.M = (int)a[0]; p.N = (int)a[1]; p.K = p.lda = (int)a[2]; p.z_add = (int)a[3];
@@ -47,7 +55,7 @@ def rules(tmp_path_factory):
                     "-Wl,-rpath," + os.path.join(rocm, "lib"), "-o", exe], check=True)
 
     def ask(what, rows):
-        text = "".join(" ".join(str(v) for v in (tuple(r) + (0, 0, 0))[:4]) + "\n" for r in rows)
+        text = "".join(" ".join(str(v) for v in (tuple(r) + (0,) * 9)[:9]) + "\n" for r in rows)
         out = subprocess.run([exe, what], input=text, capture_output=True, text=True, check=True, timeout=60).stdout
         return [tuple(int(v) for v in line.split()) for line in out.splitlines()]
 
@@ -83,6 +91,53 @@ def test_small_products_of_more_than_64_rows_by_rounds_of_the_chip(rules):
     got = rules("small", [s + (0,) for s, _, _ in SMALL])
     acc = rules("small", [s + (1,) for s, _, _ in SMALL])
     assert [(s, g[0], a[0]) for (s, _, _), g, a in zip(SMALL, got, acc)] == SMALL
+
+
+def _residue_row(xs, ws, st, pd):
+    B, H, W, C = xs
+    N, kh, kw, _ = ws
+    rows = kh == kw == 1 and st == (1, 1) and pd == (0, 0)
+    M = B * ((H + 2 * pd[0] - kh) // st[0] + 1) * ((W + 2 * pd[1] - kw) // st[1] + 1)
+    return (M, N, C, B * H * W, int(not rows), kh, kw) + tuple(st)
+
+
+def test_the_residue_tests_reach_every_instantiation(rules):
+    """Tile and number of moduli follow from a model: a change of it must not leave a kernel without a test."""
+    from paper_2104_10949_amd import binding as b
+    from tests import test_gpu_residue as t
+    layers = [(xs, ws, (s, s), (p, p)) for xs, ws, s, p in t.CONVS] + t.GATHERS
+    rows = [(M, N, K, M, 0, 1, 1, 1, 1) for M, N, K in t.SHAPES] + [_residue_row(*l) for l in layers]
+    needs = [b.cg_share_matmul_workspace_bytes(*s) for s in t.SHAPES] + [b.cg_share_conv2d_workspace_bytes(*l) for l in layers]
+    seen = set()
+    for row, need, (tile, nmod, nbytes) in zip(rows, needs, rules("residues", rows)):
+        assert need == nbytes, row   # the route is taken: its bytes are more than the digit planes'
+        seen.add((tile, nmod, row[4]))
+    assert seen == {(tile, nmod, gathered) for tile in (128, 256) for nmod in (18, 19) for gathered in (0, 1)}
+
+
+# Taken or not, and whole calls in microseconds without residues and with them on either tile (256, 128).
+LAYERS = [(((15, 69, 69, 896), (144, 5, 5, 896), (2, 2), (2, 2)), 0, 4096, 3653, 4376),
+          (((4, 101, 101, 1024), (352, 3, 3, 1024), (1, 2), (1, 1)), 1, 3833, 3221, 3344),
+          (((13, 5, 5, 1136), (1008, 7, 7, 1136), (1, 1), (3, 3)), 0, 1309, 1846, 1638),
+          (((20, 13, 13, 1296), (224, 5, 5, 1296), (2, 2), (2, 2)), 0, 608, 776, 689),
+          (((32, 16, 16, 256), (256, 3, 3, 256), (1, 1), (1, 1)), 1, 254, 211, 204),
+          (((32, 8, 8, 512), (512, 3, 3, 512), (1, 1), (1, 1)), 1, 262, 246, 209),
+          (((32, 32, 32, 128), (128, 3, 3, 128), (1, 1), (1, 1)), 1, 266, 356, 237),
+          (((32, 64, 64, 64), (64, 3, 3, 64), (1, 1), (1, 1)), 0, 282, 841, 516),
+          (((32, 64, 64, 64), (128, 3, 3, 64), (1, 1), (1, 1)), 0, 527, 875, 555)]
+PRODUCTS = [((7548, 529, 23105), 1, 6981, 6473, 8531), ((423, 2509, 10029), 0, 859, 823, 903), ((734, 1713, 3433), 1, 326, 282, 314),
+            ((1000, 777, 1531), 0, 113, 117, 95), ((4096, 4096, 4096), 1, 3447, 2190, 2779), ((2048, 2048, 2048), 1, 456, 372, 418),
+            ((2048, 2048, 512), 0, 129, 141, 137), ((1024, 1024, 1024), 0, 83, 94, 84), ((512, 4096, 4096), 0, 469, 478, 521)]
+
+
+def test_residues_and_their_tile_are_chosen_where_they_measured_faster(rules):
+    from paper_2104_10949_amd import binding as b
+    rows = [_residue_row(*l) for l, *_ in LAYERS] + [(M, N, K, M, 0, 1, 1, 1, 1) for (M, N, K), *_ in PRODUCTS]
+    needs = [b.cg_share_conv2d_workspace_bytes(*l) for l, *_ in LAYERS] + [b.cg_share_matmul_workspace_bytes(*p) for p, *_ in PRODUCTS]
+    for (what, taken, without, large, small), need, (tile, _, nbytes) in zip(LAYERS + PRODUCTS, needs, rules("residues", rows)):
+        assert (need == nbytes) == bool(taken), what
+        if taken:
+            assert (large if tile == 256 else small) <= 1.05 * min(without, large, small), what
 
 
 def test_residue_kernels_keep_their_accumulators_in_registers(tmp_path):

@@ -49,7 +49,8 @@ def sampled(n):   # edges of tiles and a few others
 
 # the small tile, the large one, multiples of nothing, the longest K of 18 moduli and the first of 19
 SHAPES = [(1150, 1145, 3001), (1023, 2047, 3001), (2048, 2048, 2048), (3001, 2047, 2050), (2048, 2048, 5500),
-          (1290, 1283, 5501), (1800, 2040, 9002)]
+          (1290, 1283, 5501), (1800, 2040, 9002),
+          (1167, 1361, 3048), (1214, 1361, 957), (770, 1691, 5739)]   # the small tile with 18 and 19 moduli
 
 
 @pytest.mark.parametrize("M,N,K", SHAPES)
@@ -106,6 +107,32 @@ def test_conv(cg, ro, wl, xs, ws, stride, pad):
     last = ops[0][-1:], ops[1][-1:]
     want = ro.party_conv2d(*last, ops[2][:40], ops[3][:40], st, pd)
     assert np.array_equal(cg.to_host(got[-1:, :, :, :40].contiguous()), want)
+
+
+# both tiles with 18 and with 19 moduli on gathered patches: even and odd channel counts, windows, strides and paddings
+# that differ along the axes, 1 x 1 windows with a stride or padding, and the 1 x 1 layer that is a product of rows
+GATHERS = [((2, 25, 51, 180), (384, 3, 5, 180), (1, 2), (0, 1)), ((4, 58, 33, 53), (104, 5, 5, 53), (2, 1), (1, 1)),
+           ((1, 23, 41, 511), (1108, 1, 1, 511), (1, 1), (1, 2)), ((3, 58, 10, 234), (336, 2, 3, 234), (2, 1), (1, 2)),
+           ((6, 12, 60, 249), (66, 5, 5, 249), (2, 1), (3, 0)), ((4, 19, 29, 223), (71, 5, 5, 223), (1, 1), (1, 2)),
+           ((4, 26, 16, 126), (224, 5, 3, 126), (2, 1), (2, 2)), ((5, 40, 29, 63), (223, 5, 3, 63), (2, 1), (0, 1)),
+           ((5, 39, 11, 816), (972, 1, 1, 816), (1, 2), (1, 2)), ((1, 51, 30, 831), (507, 1, 1, 831), (1, 1), (1, 1)),
+           ((4, 13, 59, 226), (138, 5, 5, 226), (1, 1), (0, 1)), ((5, 51, 9, 447), (264, 5, 3, 447), (2, 1), (1, 2)),
+           ((3, 10, 56, 427), (224, 5, 3, 427), (1, 1), (0, 1)), ((4, 43, 45, 697), (976, 1, 1, 697), (1, 1), (0, 0))]
+
+
+@pytest.mark.parametrize("xs,ws,st,pd", GATHERS)
+def test_gathers(cg, ro, wl, xs, ws, st, pd):
+    say(f"residue route conv x={xs} w={ws} stride={st} pad={pd}")
+    assert cg.cg_share_conv2d_prefers_workspace(xs, ws, st, pd)
+    ops = [wl.draw_ring(s, 9250 + i) for i, s in enumerate((xs, xs, ws, ws))]
+    dev = [cg.to_device(a) for a in ops]
+    plain = cg.cg_share_conv2d(*dev, stride=st, pad=pd)
+    got = cg.cg_share_conv2d_ws(*dev, poisoned(cg.cg_share_conv2d_workspace_bytes(xs, ws, st, pd)), stride=st, pad=pd)
+    assert torch.equal(got, plain)
+    n = ws[0]
+    for image, lo in ((0, 0), (xs[0] - 1, n - 40)):
+        want = ro.party_conv2d(ops[0][image:image + 1], ops[1][image:image + 1], ops[2][lo:lo + 40], ops[3][lo:lo + 40], st, pd)
+        assert np.array_equal(cg.to_host(got[image:image + 1, :, :, lo:lo + 40].contiguous()), want)
 
 
 def test_scratch_of_the_digit_planes_is_still_enough(cg, wl):
