@@ -638,8 +638,13 @@ struct Plan {
     int64_t x_rows, x_k;  // left operand seen as [x_rows, x_k] words for the plane conversion
     u64 xp_bytes, wp_bytes;  // bytes of one left / right plane tensor
     u64 x_bytes, w_bytes, z_bytes;
-    bool rns_pays;    // the residue route applies and is the faster one, given its scratch memory
-    cg::RnsParams rns;
+    bool rns_ok;      // the residue route applies as far as the operands' form goes
+};
+
+// Residue route of a plan.
+struct Residues {
+    bool pay;         // the route applies and is the faster one, given its scratch memory
+    cg::RnsParams p;
 };
 
 u64 round_up(u64 v, u64 a) { return (v + a - 1) / a * a; }
@@ -661,24 +666,26 @@ u64 planes_workspace_bytes(const Plan& pl) {
 }
 
 // What a caller is asked to bring: enough for the faster route.  Less is accepted as long as the digit route fits.
-u64 plan_workspace_bytes(const Plan& pl) {
-    const u64 planes = planes_workspace_bytes(pl), rns = pl.rns_pays ? cg::rns_workspace_bytes(pl.rns) : 0;
+u64 plan_workspace_bytes(const Plan& pl, const Residues& res) {
+    const u64 planes = planes_workspace_bytes(pl), rns = res.pay ? cg::rns_workspace_bytes(res.p) : 0;
     return rns > planes ? rns : planes;
 }
 
-// Residue route for a plan whose left operand is [x_rows, words] (gathered over a window if `conv`): set up pl.rns
-// and decide whether it pays.
-void plan_rns(Plan* pl, int64_t x_rows, int64_t words, bool conv) {
-    const cg::GemmParams& p = pl->p;
-    cg::RnsParams& r = pl->rns;
-    pl->rns_pays = false;
-    if (x_rows >= (int64_t)1 << 30) return;
+// Sets up the residue route of a plan and decides whether it pays.  For the entry points that bring scratch memory or ask
+// about it; the others have no use for it and its model is host time.
+Residues plan_residues(const Plan& pl) {
+    Residues res = {};
+    const cg::GemmParams& p = pl.p;
+    const int64_t x_rows = pl.x_rows, words = pl.x_k;
+    const bool conv = pl.planes_conv;   // the left operand is gathered over a window
+    cg::RnsParams& r = res.p;
+    if (!pl.rns_ok || x_rows >= (int64_t)1 << 30) return res;
     r.x_a = p.x_a; r.x_b = p.x_b; r.w_a = p.w_a; r.w_b = p.w_b; r.z = p.z;
     r.M = p.M; r.N = p.N;
     r.words = (int)words; r.x_rows = (int)x_rows; r.conv = conv;
     r.H = p.H; r.W = p.W; r.Ho = p.Ho; r.Wo = p.Wo; r.sh = p.sh; r.sw = p.sw; r.ph = p.ph; r.pw = p.pw;
     r.kh = conv ? p.kh : 1; r.kw = conv ? p.kw : 1;
-    if (!cg::rns_plan(&r)) return;
+    if (!cg::rns_plan(&r)) return res;
     // Both routes in seconds, from measurements on MI355X.  Plain kernel: 144 operations per (m, n, k) of its 128 x 64
     // tiles at 2.6e15 a second, 1.2 times that with 8-byte loads, 1.3 times with 8-byte gathers (1.2 to 1.8 over 650 layers,
     // median 1.55), 8 microseconds, and up to 8 more where the tiles are so few that K is split; 0.93 of it where the digit planes
@@ -688,14 +695,15 @@ void plan_rns(Plan* pl, int64_t x_rows, int64_t words, bool conv) {
     // a little more on strided layers, where the model scatters most: of 3400 random layers and 1300 products, none
     // that is taken was more than 2 % slower than without residues.
     const double up_m = (double)((p.M + (int64_t)127) / 128 * 128), up_n = (double)((p.N + (int64_t)63) / 64 * 64);
-    const double work = 144.0 * up_m * up_n * (double)p.K / 2.6e15 * (pl->planes_ok ? 1.0 : conv ? 1.3 : 1.2);
+    const double work = 144.0 * up_m * up_n * (double)p.K / 2.6e15 * (pl.planes_ok ? 1.0 : conv ? 1.3 : 1.2);
     double best = work + 8.0e-6;
     if (up_m * up_n < 256.0 * 128.0 * 64.0) best += work < 8.0e-6 ? work : 8.0e-6;
-    if (planes_pay(*pl)) best *= 0.93;
+    if (planes_pay(pl)) best *= 0.93;
     const double pairs = ((double)r.x_rows + (double)p.N * r.kh * r.kw) * r.slices * 64.0;
     const double rns = pairs * (16.0 + 2.0 * r.nmod) / (words % 2 == 0 ? 4.9e12 : 4.0e12) +
                        (double)r.r_plane * (2.0 * r.nmod + 8.0) / 8.5e12 + 1.0e-6 * r.product_us + 12.0e-6;
-    pl->rns_pays = rns < (conv && (p.sh > 1 || p.sw > 1) ? 0.90 : 0.92) * best;
+    res.pay = rns < (conv && (p.sh > 1 || p.sw > 1) ? 0.90 : 0.92) * best;
+    return res;
 }
 
 cg_status plan_matmul(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t* y_i, const uint64_t* y_ip1,
@@ -741,7 +749,7 @@ cg_status plan_matmul(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t
     pl.x_rows = M; pl.x_k = K;
     pl.xp_bytes = cg::planes_bytes(M, K); pl.wp_bytes = cg::planes_bytes(N, K);
     pl.x_bytes = (u64)mk * 8; pl.w_bytes = (u64)nk * 8; pl.z_bytes = (u64)mn * 8;
-    if (!trans_x && !trans_y && !long_rows && !few_rows) plan_rns(&pl, M, K, false);
+    pl.rns_ok = !trans_x && !trans_y && !long_rows && !few_rows;
     *out = pl;
     return CG_OK;
 }
@@ -838,7 +846,7 @@ cg_status plan_conv2d(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t
     pl.xp_bytes = cg::planes_bytes(pl.x_rows, pl.x_k);
     pl.wp_bytes = cg::planes_bytes(d->Cout, K);
     pl.x_bytes = (u64)x_el * 8; pl.w_bytes = (u64)w_el * 8; pl.z_bytes = (u64)z_el * 8;
-    plan_rns(&pl, d->B * d->H * d->W, d->Cin, !pointwise);
+    pl.rns_ok = true;
     *out = pl;
     return CG_OK;
 }
@@ -1083,10 +1091,11 @@ cg_status run_planes(Plan& pl, void* workspace, size_t workspace_bytes, void* st
 // With scratch memory: the residue route where it pays and the memory holds it, else the digit planes, else the plain
 // kernel.
 cg_status run_with_workspace(Plan& pl, void* workspace, size_t workspace_bytes, void* stream) {
-    if (pl.rns_pays && workspace && aligned(workspace, 16)) {
-        const u64 need = cg::rns_workspace_bytes(pl.rns);
+    const Residues res = plan_residues(pl);
+    if (res.pay && workspace && aligned(workspace, 16)) {
+        const u64 need = cg::rns_workspace_bytes(res.p);
         if (workspace_bytes >= need && !workspace_overlaps(pl, workspace, need)) {
-            const hipError_t e = cg::launch_share_gemm_rns(pl.rns, workspace, static_cast<hipStream_t>(stream));
+            const hipError_t e = cg::launch_share_gemm_rns(res.p, workspace, static_cast<hipStream_t>(stream));
             return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
         }
     }
@@ -1146,7 +1155,7 @@ cg_status cg_share_matmul_t(const uint64_t* x_i, const uint64_t* x_ip1, const ui
 size_t cg_share_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     Plan pl;
     if (plan_matmul(nullptr, nullptr, nullptr, nullptr, nullptr, M, N, K, false, &pl) != CG_OK) return 0;
-    return (size_t)plan_workspace_bytes(pl);
+    return (size_t)plan_workspace_bytes(pl, plan_residues(pl));
 }
 
 cg_status cg_share_matmul_ws(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t* y_i,
@@ -1210,19 +1219,19 @@ cg_status cg_share_conv2d(const uint64_t* x_i, const uint64_t* x_ip1, const uint
 int cg_share_matmul_prefers_workspace(int64_t M, int64_t N, int64_t K) {
     Plan pl;
     if (plan_matmul(nullptr, nullptr, nullptr, nullptr, nullptr, M, N, K, false, &pl) != CG_OK) return 0;
-    return pl.rns_pays || planes_pay(pl) ? 1 : 0;
+    return planes_pay(pl) || plan_residues(pl).pay ? 1 : 0;
 }
 
 int cg_share_conv2d_prefers_workspace(const cg_conv2d_desc* d) {
     Plan pl;
     if (plan_conv2d(nullptr, nullptr, nullptr, nullptr, nullptr, d, false, &pl) != CG_OK) return 0;
-    return pl.rns_pays || planes_pay(pl) ? 1 : 0;
+    return planes_pay(pl) || plan_residues(pl).pay ? 1 : 0;
 }
 
 size_t cg_share_conv2d_workspace_bytes(const cg_conv2d_desc* d) {
     Plan pl;
     if (plan_conv2d(nullptr, nullptr, nullptr, nullptr, nullptr, d, false, &pl) != CG_OK) return 0;
-    return (size_t)plan_workspace_bytes(pl);
+    return (size_t)plan_workspace_bytes(pl, plan_residues(pl));
 }
 
 cg_status cg_share_conv2d_ws(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t* w_i,
