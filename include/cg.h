@@ -114,28 +114,34 @@ CG_API cg_status cg_share_matmul_t(const uint64_t *x_i, const uint64_t *x_ip1,
 
 /*
  * The same product with caller-supplied scratch memory (device memory, 16-byte
- * aligned, cg_share_matmul_workspace_bytes(M, N, K) bytes for the fastest route,
- * not overlapping any operand).  Large products go through residues: every word is
- * reduced once modulo 18 or 19 numbers of eight bits, one int8 product per modulus
- * follows, and a last pass puts the words together; this takes 18 or 19 bytes per
- * operand word and per output.  Other products, and a call whose scratch memory holds
- * the digits (8 bytes per operand word, rows padded to a multiple of 32 words) but
- * not the residues, take the digit route: each share tensor is split
- * into its eight signed-byte digits ONCE, by a streaming pass that writes the
- * digits there, instead of once per output tile that needs it inside the product
- * kernel; the product kernel then only moves bytes.  Result and argument rules
- * are those of cg_share_matmul, bit for bit.  The scratch contents are
- * undefined afterwards and carry no state between calls.  When the residues do
- * not pay or do not fit and the digit route does not apply (odd K, a pointer that is only 8-byte aligned, K above 2^20,
- * or a left operand of so few rows, at most 64, that the plain call's kernel for
- * such products is the faster one) the call
- * computes exactly as cg_share_matmul and does not touch the scratch memory;
- * cg_share_matmul_workspace_bytes returns 0 where no route uses scratch memory (and
- * for invalid sizes).
- * CG_ERR_WORKSPACE if workspace_bytes is too small for the digits, CG_ERR_NULL / CG_ERR_ALIGN /
- * CG_ERR_ALIAS for a missing, misaligned or overlapping workspace.
+ * aligned, not overlapping any operand).  Two routes use it, and
+ * cg_share_matmul_workspace_bytes(M, N, K) bytes are enough for the faster one:
+ *   residues : large products.  Every word is reduced once modulo 18 or 19 numbers of
+ *              eight bits, one int8 product per modulus follows, and a last pass puts
+ *              the words together; 18 or 19 bytes per operand word and per output.
+ *   digits   : each share tensor is split into its eight signed-byte digits ONCE, by a
+ *              streaming pass that writes the digits there, instead of once per output
+ *              tile that needs it inside the product kernel, which then only moves
+ *              bytes; cg_share_matmul_digit_workspace_bytes(M, N, K) bytes (8 per operand
+ *              word, rows padded to a multiple of 32 words), 0 where the route does not
+ *              apply: odd K, a pointer that is only 8-byte aligned, K above 2^20, or a
+ *              left operand of so few rows, at most 64, that the plain call's kernel for
+ *              such products is the faster one.
+ * A call takes the residues where they pay and the scratch memory is there (aligned,
+ * large enough, clear of the operands), else the digits where they apply, else it
+ * computes exactly as cg_share_matmul and does not touch the scratch memory.  Result and
+ * argument rules are those of cg_share_matmul, bit for bit, on every route.  The scratch
+ * contents are undefined afterwards and carry no state between calls.
+ * Where the digit route applies: CG_ERR_NULL / CG_ERR_ALIGN / CG_ERR_WORKSPACE / CG_ERR_ALIAS
+ * for a workspace that is missing, misaligned, smaller than the digits need or
+ * overlapping an operand within those bytes.  Everywhere else a workspace that cannot be
+ * used is no error, and one that is too small for the residues is none anywhere: the
+ * call takes the next route.  A caller that wants the residues brings the full size.
+ * cg_share_matmul_workspace_bytes returns 0 where no route uses scratch memory, and
+ * like cg_share_matmul_digit_workspace_bytes for invalid sizes.
  */
 CG_API size_t cg_share_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K);
+CG_API size_t cg_share_matmul_digit_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
 /*
  * 1 when, for these sizes (16-byte-aligned operands assumed), the route with scratch
@@ -143,9 +149,12 @@ CG_API size_t cg_share_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K);
  * when the plain call is, or when the sizes are invalid.  A measured rule of thumb
  * for callers that have scratch memory and want to pick per layer: large products
  * whose operands are small against M*N*K gain (4096^3 about a third), skinny
- * or short ones lose.  Same for cg_share_conv2d_prefers_workspace below.
+ * or short ones lose.  cg_share_matmul_prefers_digit_workspace answers the same for a
+ * caller that can bring the digits' bytes but not all of
+ * cg_share_matmul_workspace_bytes.  Same for the two cg_share_conv2d queries below.
  */
 CG_API int cg_share_matmul_prefers_workspace(int64_t M, int64_t N, int64_t K);
+CG_API int cg_share_matmul_prefers_digit_workspace(int64_t M, int64_t N, int64_t K);
 
 CG_API cg_status cg_share_matmul_ws(const uint64_t *x_i, const uint64_t *x_ip1,
                              const uint64_t *y_i, const uint64_t *y_ip1,
@@ -159,10 +168,10 @@ CG_API cg_status cg_share_matmul_ws(const uint64_t *x_i, const uint64_t *x_ip1,
  * array of CG_STATIC_SCRATCH_BYTES bytes inside the library's device image
  * (one copy per GPU, held until the process ends); the call itself allocates and
  * frees nothing.  Result and argument rules are those of cg_share_matmul, bit
- * for bit.  CG_ERR_WORKSPACE when cg_share_matmul_workspace_bytes(M, N, K)
+ * for bit.  CG_ERR_WORKSPACE when cg_share_matmul_digit_workspace_bytes(M, N, K)
  * exceeds CG_STATIC_SCRATCH_BYTES (nothing is launched then); products the digit
  * route does not apply to (odd K, 8-byte-aligned pointers) run as
- * cg_share_matmul, whatever their size.  The array's address is looked up on the
+ * cg_share_matmul, whatever their size; residues are not used.  The array's address is looked up on the
  * first call on each device, which must be the current device, as for every
  * call here.  All calls on one GPU share the array and every call overwrites the part
  * it uses: calls that overlap in time on one GPU (different streams, or
@@ -206,12 +215,16 @@ CG_API cg_status cg_share_conv2d(const uint64_t *x_i, const uint64_t *x_ip1,
                           uint64_t *z_i, const cg_conv2d_desc *desc, void *stream);
 
 /*
- * cg_share_conv2d with caller-supplied scratch memory; see cg_share_matmul_ws.
- * The digit route applies when Cin is a multiple of 32 (or the convolution is
- * 1x1, stride 1, unpadded with even Cin) and all pointers are 16-byte aligned.
+ * cg_share_conv2d with caller-supplied scratch memory: routes, errors and queries as
+ * for cg_share_matmul_ws.  The digit route applies when Cin is a multiple of 32 and the
+ * window has at most 32 taps (or the convolution is 1x1, stride 1, unpadded with even
+ * Cin) and all pointers are 16-byte aligned; the residues whatever Cin, window, stride and
+ * alignment are, as long as they pay (kh*kw*Cin at most 65000).
  */
 CG_API size_t cg_share_conv2d_workspace_bytes(const cg_conv2d_desc *desc);
+CG_API size_t cg_share_conv2d_digit_workspace_bytes(const cg_conv2d_desc *desc);
 CG_API int cg_share_conv2d_prefers_workspace(const cg_conv2d_desc *desc);
+CG_API int cg_share_conv2d_prefers_digit_workspace(const cg_conv2d_desc *desc);
 
 CG_API cg_status cg_share_conv2d_ws(const uint64_t *x_i, const uint64_t *x_ip1,
                              const uint64_t *w_i, const uint64_t *w_ip1,

@@ -28,8 +28,10 @@ EXPORTS = ("cg_status_string", "cg_version", "cg_share_matmul", "cg_share_conv2d
            "cg_bit_transpose64", "cg_bshare_carry_level", "cg_bits_unpack", "cg_bshare_csa", "cg_bshare_half_adder",
            "cg_share_matmul_acc", "cg_share_conv2d_acc", "cg_share_matmul_f64limb", "cg_share_matmul_static",
            "cg_share_matmul_prefers_workspace", "cg_share_conv2d_prefers_workspace",
-           "cg_share_matmul_workspace_bytes", "cg_share_conv2d_workspace_bytes")
-SIZE_EXPORTS = 2      # the last entries return size_t, the first two a string and an int, the rest cg_status
+           "cg_share_matmul_prefers_digit_workspace", "cg_share_conv2d_prefers_digit_workspace",
+           "cg_share_matmul_workspace_bytes", "cg_share_conv2d_workspace_bytes",
+           "cg_share_matmul_digit_workspace_bytes", "cg_share_conv2d_digit_workspace_bytes")
+SIZE_EXPORTS = 4      # the last entries return size_t, the first two a string and an int, the rest cg_status
 
 
 class ConvDesc(ctypes.Structure):
@@ -79,10 +81,9 @@ def lib() -> ctypes.CDLL:
         L.cg_reconstruct.argtypes = [vp] * 4 + [sz, vp]
         L.cg_share_matmul_ws.argtypes = [vp] * 5 + [i64] * 3 + [vp, sz, vp]
         L.cg_share_conv2d_ws.argtypes = [vp] * 5 + [ctypes.POINTER(ConvDesc), vp, sz, vp]
-        L.cg_share_matmul_workspace_bytes.argtypes = [i64] * 3
-        L.cg_share_conv2d_workspace_bytes.argtypes = [ctypes.POINTER(ConvDesc)]
-        L.cg_share_matmul_prefers_workspace.argtypes = [i64] * 3
-        L.cg_share_conv2d_prefers_workspace.argtypes = [ctypes.POINTER(ConvDesc)]
+        for name in ("workspace_bytes", "digit_workspace_bytes", "prefers_workspace", "prefers_digit_workspace"):
+            getattr(L, "cg_share_matmul_" + name).argtypes = [i64] * 3
+            getattr(L, "cg_share_conv2d_" + name).argtypes = [ctypes.POINTER(ConvDesc)]
         key = ctypes.c_char_p
         L.cg_zero_share.argtypes = [key, key, u64, u64, vp, sz, vp]
         L.cg_reshare.argtypes = [vp, key, key, u64, u64, vp, sz, vp]
@@ -230,6 +231,10 @@ def cg_share_matmul_workspace_bytes(M: int, N: int, K: int) -> int:
     return int(lib().cg_share_matmul_workspace_bytes(M, N, K))
 
 
+def cg_share_matmul_digit_workspace_bytes(M: int, N: int, K: int) -> int:
+    return int(lib().cg_share_matmul_digit_workspace_bytes(M, N, K))
+
+
 def _ws(workspace) -> Tuple[int, int]:
     if workspace is None:
         return 0, 0
@@ -302,18 +307,30 @@ def cg_share_matmul_prefers_workspace(M: int, N: int, K: int) -> bool:
     return bool(lib().cg_share_matmul_prefers_workspace(M, N, K))
 
 
-def cg_share_conv2d_prefers_workspace(x_shape, w_shape, stride=(1, 1), pad=(0, 0)) -> bool:
+def cg_share_matmul_prefers_digit_workspace(M: int, N: int, K: int) -> bool:
+    return bool(lib().cg_share_matmul_prefers_digit_workspace(M, N, K))
+
+
+def _conv_desc(x_shape, w_shape, stride, pad):
     B, H, W, Cin = x_shape
     Cout, kh, kw, _ = w_shape
-    d = ConvDesc(B, H, W, Cin, Cout, kh, kw, stride[0], stride[1], pad[0], pad[1])
-    return bool(lib().cg_share_conv2d_prefers_workspace(ctypes.byref(d)))
+    return ctypes.byref(ConvDesc(B, H, W, Cin, Cout, kh, kw, stride[0], stride[1], pad[0], pad[1]))
+
+
+def cg_share_conv2d_prefers_workspace(x_shape, w_shape, stride=(1, 1), pad=(0, 0)) -> bool:
+    return bool(lib().cg_share_conv2d_prefers_workspace(_conv_desc(x_shape, w_shape, stride, pad)))
+
+
+def cg_share_conv2d_prefers_digit_workspace(x_shape, w_shape, stride=(1, 1), pad=(0, 0)) -> bool:
+    return bool(lib().cg_share_conv2d_prefers_digit_workspace(_conv_desc(x_shape, w_shape, stride, pad)))
 
 
 def cg_share_conv2d_workspace_bytes(x_shape, w_shape, stride=(1, 1), pad=(0, 0)) -> int:
-    B, H, W, Cin = x_shape
-    Cout, kh, kw, _ = w_shape
-    d = ConvDesc(B, H, W, Cin, Cout, kh, kw, stride[0], stride[1], pad[0], pad[1])
-    return int(lib().cg_share_conv2d_workspace_bytes(ctypes.byref(d)))
+    return int(lib().cg_share_conv2d_workspace_bytes(_conv_desc(x_shape, w_shape, stride, pad)))
+
+
+def cg_share_conv2d_digit_workspace_bytes(x_shape, w_shape, stride=(1, 1), pad=(0, 0)) -> int:
+    return int(lib().cg_share_conv2d_digit_workspace_bytes(_conv_desc(x_shape, w_shape, stride, pad)))
 
 
 def cg_share_conv2d_ws(x_i, x_ip1, w_i, w_ip1, workspace, stride=(1, 1), pad=(0, 0), z_i=None,

@@ -617,7 +617,7 @@ const char* cg_status_string(cg_status s) {
         case CG_ERR_ALIAS: return "CG_ERR_ALIAS: output overlaps an input";
         case CG_ERR_UNSUPPORTED: return "CG_ERR_UNSUPPORTED: shape outside the kernels' addressing range";
         case CG_ERR_DEVICE: return "CG_ERR_DEVICE: HIP launch error";
-        case CG_ERR_WORKSPACE: return "CG_ERR_WORKSPACE: scratch memory smaller than the product needs (cg_*_workspace_bytes())";
+        case CG_ERR_WORKSPACE: return "CG_ERR_WORKSPACE: scratch memory smaller than the digit route needs (cg_*_digit_workspace_bytes())";
     }
     return "unknown cg_status";
 }
@@ -1158,6 +1158,12 @@ size_t cg_share_matmul_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     return (size_t)plan_workspace_bytes(pl, plan_residues(pl));
 }
 
+size_t cg_share_matmul_digit_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    Plan pl;
+    if (plan_matmul(nullptr, nullptr, nullptr, nullptr, nullptr, M, N, K, false, &pl) != CG_OK) return 0;
+    return (size_t)planes_workspace_bytes(pl);
+}
+
 cg_status cg_share_matmul_ws(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t* y_i,
                              const uint64_t* y_ip1, uint64_t* z_i, int64_t M, int64_t N, int64_t K,
                              void* workspace, size_t workspace_bytes, void* stream) {
@@ -1222,16 +1228,34 @@ int cg_share_matmul_prefers_workspace(int64_t M, int64_t N, int64_t K) {
     return planes_pay(pl) || plan_residues(pl).pay ? 1 : 0;
 }
 
+int cg_share_matmul_prefers_digit_workspace(int64_t M, int64_t N, int64_t K) {
+    Plan pl;
+    if (plan_matmul(nullptr, nullptr, nullptr, nullptr, nullptr, M, N, K, false, &pl) != CG_OK) return 0;
+    return planes_pay(pl) ? 1 : 0;
+}
+
 int cg_share_conv2d_prefers_workspace(const cg_conv2d_desc* d) {
     Plan pl;
     if (plan_conv2d(nullptr, nullptr, nullptr, nullptr, nullptr, d, false, &pl) != CG_OK) return 0;
     return planes_pay(pl) || plan_residues(pl).pay ? 1 : 0;
 }
 
+int cg_share_conv2d_prefers_digit_workspace(const cg_conv2d_desc* d) {
+    Plan pl;
+    if (plan_conv2d(nullptr, nullptr, nullptr, nullptr, nullptr, d, false, &pl) != CG_OK) return 0;
+    return planes_pay(pl) ? 1 : 0;
+}
+
 size_t cg_share_conv2d_workspace_bytes(const cg_conv2d_desc* d) {
     Plan pl;
     if (plan_conv2d(nullptr, nullptr, nullptr, nullptr, nullptr, d, false, &pl) != CG_OK) return 0;
     return (size_t)plan_workspace_bytes(pl, plan_residues(pl));
+}
+
+size_t cg_share_conv2d_digit_workspace_bytes(const cg_conv2d_desc* d) {
+    Plan pl;
+    if (plan_conv2d(nullptr, nullptr, nullptr, nullptr, nullptr, d, false, &pl) != CG_OK) return 0;
+    return (size_t)planes_workspace_bytes(pl);
 }
 
 cg_status cg_share_conv2d_ws(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t* w_i,

@@ -231,10 +231,40 @@ def test_static_scratch_entry_point_validates_and_bounds_its_size(L):
     assert f(*far, 4, 0, 4, None) == b.CG_ERR_SHAPE
     assert f(*far[:4], far[0] + 8, 4, 4, 4, None) == b.CG_ERR_ALIAS
     # 2 * (4096 + 4096) rows of 4096 words as digit planes are 512 MiB: beyond the fixed array, refused on the host
-    assert L.cg_share_matmul_workspace_bytes(4096, 4096, 4096) > b.STATIC_SCRATCH_BYTES
+    assert L.cg_share_matmul_digit_workspace_bytes(4096, 4096, 4096) == 512 << 20 > b.STATIC_SCRATCH_BYTES
     assert f(*far, 4096, 4096, 4096, None) == b.CG_ERR_WORKSPACE
+    # the digits decide and not what the faster route with scratch memory takes: 1024 x 1792 x 1472 needs 63 MiB of them
+    # and is not refused (the launch fails where there is no GPU, the argument checks do not)
+    assert L.cg_share_matmul_digit_workspace_bytes(1024, 1792, 1472) <= b.STATIC_SCRATCH_BYTES
+    assert L.cg_share_matmul_workspace_bytes(1024, 1792, 1472) > b.STATIC_SCRATCH_BYTES
+    assert f(*far, 1024, 1793, 1490, None) == b.CG_ERR_WORKSPACE
+    text = " ".join(open(os.path.join(ROOT, "include", "cg.h")).read().replace(" * ", " ").split())
+    assert "CG_ERR_WORKSPACE when cg_share_matmul_digit_workspace_bytes(M, N, K) exceeds CG_STATIC_SCRATCH_BYTES" in text
     text = open(os.path.join(ROOT, "include", "cg.h")).read()
     assert re.search(r"#define\s+CG_STATIC_SCRATCH_BYTES\s+\(64u << 20\)", text) and b.STATIC_SCRATCH_BYTES == 64 << 20
+
+
+def test_digit_scratch_can_be_asked_for(L):
+    """A caller that cannot bring the residues' bytes asks for the digits' and whether they are worth it."""
+    from paper_2104_10949_amd import binding as b
+    rows16 = lambda R, k: (R + 15) // 16 * 16 * ((k + 31) // 32) * 256
+    for M, N, K in [(4096, 4096, 4096), (8192, 8192, 2048), (128, 64, 64), (1024, 1792, 1472), (3000, 2001, 1000)]:
+        assert b.cg_share_matmul_digit_workspace_bytes(M, N, K) == 2 * rows16(M, K) + 2 * rows16(N, K)
+        assert b.cg_share_matmul_workspace_bytes(M, N, K) >= b.cg_share_matmul_digit_workspace_bytes(M, N, K)
+    for M, N, K in [(4096, 4096, 4095), (64, 64, 64), (0, 64, 64), (128, 64, (1 << 20) + 2)]:
+        assert b.cg_share_matmul_digit_workspace_bytes(M, N, K) == 0
+        assert not b.cg_share_matmul_prefers_digit_workspace(M, N, K)
+    assert b.cg_share_matmul_workspace_bytes(4096, 4096, 4095) > 0 and b.cg_share_matmul_prefers_workspace(4096, 4096, 4095)
+    assert b.cg_share_matmul_prefers_digit_workspace(4096, 4096, 4096)
+    # residues pay here and the digits do not: with less than the full scratch memory the plain call is the one to make
+    assert b.cg_share_matmul_prefers_workspace(675, 2557, 4582) and not b.cg_share_matmul_prefers_digit_workspace(675, 2557, 4582)
+    layer = (32, 16, 16, 256), (256, 3, 3, 256), (1, 1), (1, 1)
+    assert b.cg_share_conv2d_digit_workspace_bytes(*layer) == 2 * rows16(32 * 256, 256) + 2 * rows16(256, 2304)
+    assert b.cg_share_conv2d_workspace_bytes(*layer) > b.cg_share_conv2d_digit_workspace_bytes(*layer)
+    assert b.cg_share_conv2d_prefers_digit_workspace(*layer)
+    odd = (32, 16, 16, 250), (256, 3, 3, 250), (1, 1), (1, 1)
+    assert b.cg_share_conv2d_digit_workspace_bytes(*odd) == 0 < b.cg_share_conv2d_workspace_bytes(*odd)
+    assert L.cg_share_conv2d_digit_workspace_bytes(None) == 0 and L.cg_share_conv2d_prefers_digit_workspace(None) == 0
 
 
 def test_truncation_and_binary_gate_validation(L):

@@ -34,11 +34,6 @@ def wl():
     return workloads
 
 
-def digit_plane_bytes(x_rows, x_k, N, K):
-    rows16 = lambda R, k: (R + 15) // 16 * 16 * ((k + 31) // 32) * 256
-    return 2 * rows16(x_rows, x_k) + 2 * rows16(N, K)
-
-
 def poisoned(nbytes):
     return torch.full((nbytes // 8 + 2,), 0x5A5A5A5A5A5A5A5A, dtype=torch.int64, device="cuda")
 
@@ -57,7 +52,7 @@ SHAPES = [(1150, 1145, 3001), (1023, 2047, 3001), (2048, 2048, 2048), (3001, 204
 def test_matmul(cg, ro, wl, M, N, K):
     say(f"residue route matmul M={M} N={N} K={K}")
     need = cg.cg_share_matmul_workspace_bytes(M, N, K)
-    assert cg.cg_share_matmul_prefers_workspace(M, N, K) and need > digit_plane_bytes(M, K, N, K)
+    assert cg.cg_share_matmul_prefers_workspace(M, N, K) and need > cg.cg_share_matmul_digit_workspace_bytes(M, N, K)
     ops = [wl.draw_ring((r, K), 9100 + i) for i, r in enumerate((M, M, N, N))]
     dev = [cg.to_device(a) for a in ops]
     plain = cg.cg_share_matmul(*dev)
@@ -81,7 +76,7 @@ def test_largest_integers(cg, x_word, w_word, K):
     x = torch.full((M, K), signed(x_word), dtype=torch.int64, device="cuda")
     w = torch.full((N, K), signed(w_word), dtype=torch.int64, device="cuda")
     need = cg.cg_share_matmul_workspace_bytes(M, N, K)
-    assert need > digit_plane_bytes(M, K, N, K)
+    assert need > cg.cg_share_matmul_digit_workspace_bytes(M, N, K)
     got = cg.cg_share_matmul_ws(x, x, w, torch.zeros_like(w), poisoned(need))
     want = signed(2 * K * x_word * w_word % (1 << 64))
     assert bool((got == want).all())
@@ -96,9 +91,8 @@ def test_conv(cg, ro, wl, xs, ws, stride, pad):
     say(f"residue route conv x={xs} w={ws} stride={stride} pad={pad}")
     st, pd = (stride, stride), (pad, pad)
     need = cg.cg_share_conv2d_workspace_bytes(xs, ws, st, pd)
-    K = ws[1] * ws[2] * ws[3]
     assert cg.cg_share_conv2d_prefers_workspace(xs, ws, st, pd)
-    assert need > digit_plane_bytes(xs[0] * xs[1] * xs[2], xs[3], ws[0], K)
+    assert need > cg.cg_share_conv2d_digit_workspace_bytes(xs, ws, st, pd)
     ops = [wl.draw_ring(s, 9200 + i) for i, s in enumerate((xs, xs, ws, ws))]
     dev = [cg.to_device(a) for a in ops]
     plain = cg.cg_share_conv2d(*dev, stride=st, pad=pd)
@@ -139,7 +133,7 @@ def test_scratch_of_the_digit_planes_is_still_enough(cg, wl):
     """A caller that brings no more than the digit planes take, or memory the route cannot use, gets the same words."""
     M, N, K = 2000, 2040, 2044
     say("residue route with the digit planes' scratch memory")
-    planes, need = digit_plane_bytes(M, K, N, K), cg.cg_share_matmul_workspace_bytes(M, N, K)
+    planes, need = cg.cg_share_matmul_digit_workspace_bytes(M, N, K), cg.cg_share_matmul_workspace_bytes(M, N, K)
     assert need > planes
     dev = [cg.to_device(wl.draw_ring((r, K), 9300 + i)) for i, r in enumerate((M, M, N, N))]
     want = cg.cg_share_matmul(*dev)
@@ -148,6 +142,30 @@ def test_scratch_of_the_digit_planes_is_still_enough(cg, wl):
         got = cg.cg_share_matmul_ws(*dev, buf[:nbytes // 8])
         assert torch.equal(got, want)
         assert bool((buf[nbytes // 8:] == 7).all())
+
+
+@pytest.mark.parametrize("K", [3001, 3008])
+def test_workspace_that_the_residues_cannot_use(cg, wl, K):
+    """Missing, misaligned or overlapping scratch memory: the next route where there is one without it (odd K), the
+    documented error where the digit route applies and the fault lies within its bytes."""
+    M, N = 2048, 2040
+    say(f"residue route, unusable workspace K={K}")
+    need, digits = cg.cg_share_matmul_workspace_bytes(M, N, K), cg.cg_share_matmul_digit_workspace_bytes(M, N, K)
+    assert need > digits and (digits == 0) == bool(K % 2)
+    dev = [cg.to_device(wl.draw_ring((r, K), 9700 + i)) for i, r in enumerate((M, M, N, N))]
+    want = cg.cg_share_matmul(*dev)
+    whole = torch.empty(need // 8 + M * N + 8, dtype=torch.int64, device="cuda")
+    z_at = lambda byte: whole[byte // 8:byte // 8 + M * N].view(M, N)
+    beyond = (digits + 255) // 256 * 256 + 256   # inside the residues' bytes, behind the digits'
+    cases = [(whole[1:], None, cg.CG_ERR_ALIGN), (None, None, cg.CG_ERR_NULL), (whole, z_at(64), cg.CG_ERR_ALIAS),
+             (whole, z_at(beyond), cg.CG_OK), (whole[:digits // 8], None, cg.CG_OK)]
+    for ws, z, status in cases:
+        if K % 2 or status == cg.CG_OK:
+            assert torch.equal(cg.cg_share_matmul_ws(*dev, ws, z_i=z), want)
+        else:
+            with pytest.raises(cg.CgError) as e:
+                cg.cg_share_matmul_ws(*dev, ws, z_i=z)
+            assert e.value.status == status
 
 
 def test_operands_at_odd_words(cg, wl):

@@ -19,11 +19,12 @@ def test_static_scratch_matches_workspace_entry_point_twice():
         pytest.skip("needs a GPU")
     cg.lib()
     # the second product is smaller in every dimension: it reuses the front of the array the first one filled
-    for case, (M, N, K) in enumerate([(300, 200, 1000), (70, 130, 96)]):
+    # (the last one's digits fit the array while the residues that the workspace call would prefer do not)
+    for case, (M, N, K) in enumerate([(300, 200, 1000), (70, 130, 96), (1024, 1792, 1472)]):
         say(f"cg_share_matmul_static call {case}: M={M} N={N} K={K}")
         host = [wl.draw_ring(s, 9100 + 10 * case + j) for j, s in enumerate([(M, K), (M, K), (N, K), (N, K)])]
         dev = [cg.to_device(a) for a in host]
-        need = cg.cg_share_matmul_workspace_bytes(M, N, K)
+        need = cg.cg_share_matmul_digit_workspace_bytes(M, N, K)
         assert 0 < need <= cg.STATIC_SCRATCH_BYTES
         ws = torch.empty(need, dtype=torch.uint8, device="cuda")
         want_ws = cg.cg_share_matmul_ws(*dev, ws)
@@ -42,7 +43,7 @@ def test_static_scratch_rejects_products_beyond_its_size():
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
     M = N = K = 2048
-    assert cg.cg_share_matmul_workspace_bytes(M, N, K) > cg.STATIC_SCRATCH_BYTES
+    assert cg.cg_share_matmul_digit_workspace_bytes(M, N, K) > cg.STATIC_SCRATCH_BYTES
     x = torch.zeros((M, K), dtype=torch.int64, device="cuda")
     y = torch.zeros((N, K), dtype=torch.int64, device="cuda")
     z = torch.full((M, N), 7, dtype=torch.int64, device="cuda")
