@@ -132,12 +132,17 @@ def _ptr(t: torch.Tensor) -> int:
     return t.data_ptr()
 
 
+# not part of torch's public interface: a torch without them goes the public way
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
         # the raw handle of torch.cuda.current_stream(), without the object around it (it costs more than the launch
         # of a short call takes the GPU)
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 

@@ -332,3 +332,21 @@ def test_binding_refuses_cpu_tensors():
         b._ptr(x)
     with pytest.raises(TypeError):
         b._ptr(torch.zeros((2, 2), dtype=torch.float32))
+
+
+@pytest.mark.parametrize("missing", [None, "_raw_stream", "_device"])
+def test_current_stream_with_and_without_the_short_way(monkeypatch, missing):
+    import torch
+    from paper_2104_10949_amd import binding as b
+
+    class Stream:
+        cuda_stream = 4321
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    monkeypatch.setattr(b, "_raw_stream", {2: 1234}.__getitem__)
+    monkeypatch.setattr(b, "_device", lambda: 2)
+    if missing:
+        monkeypatch.setattr(b, missing, None)
+    assert b._stream(None) == (4321 if missing else 1234)
+    assert b._stream(Stream()) == 4321 and b._stream(7) == 7
