@@ -63,13 +63,15 @@ def test_matmul(cg, ro, wl, M, N, K):
     assert np.array_equal(cg.to_host(got[rows]), want)
 
 
-@pytest.mark.parametrize("x_word,w_word", [(0x8080808080808080, 0x8080808080808080), (0x7F7F7F7F7F7F7F7F, 0x8080808080808080),
+@pytest.mark.parametrize("x_word,w_word", [(0x7F7F7F7F7F7F7F80, 0x7F7F7F7F7F7F7F80), (0x7F7F7F7F7F7F7F80, 0x7F7F7F7F7F7F7F7F),
+                                           (0x8080808080808080, 0x8080808080808080), (0x7F7F7F7F7F7F7F7F, 0x8080808080808080),
                                            (0x7F7F7F7F7F7F7F7F, 0x7F7F7F7F7F7F7F7F), (0x8000000000000000, 0x8000000000000000),
                                            (0, 0), (1, 0xFFFFFFFFFFFFFFFF)])
 @pytest.mark.parametrize("K", [5500, 9000])
 def test_largest_integers(cg, x_word, w_word, K):
-    """w_b = 0, so both terms of every product are x_word * w_word: with the words of the largest signed-digit value and
-    the longest K of 18 moduli the integer is as near to half the moduli's product as it gets."""
+    """w_b = 0, so both terms of every product are x_word * w_word: with the word of the largest signed-digit value
+    (0x7F..7F80, eight digits of -128) and the longest K of 18 moduli the integer is as near to half the moduli's product as
+    it gets, 0.4943 of it."""
     M, N = 2048, 2048
     say(f"residue route constant words {x_word:016x} {w_word:016x} K={K}")
     signed = lambda w: w - (1 << 64) if w >> 63 else w
@@ -101,6 +103,61 @@ def test_conv(cg, ro, wl, xs, ws, stride, pad):
     last = ops[0][-1:], ops[1][-1:]
     want = ro.party_conv2d(*last, ops[2][:40], ops[3][:40], st, pd)
     assert np.array_equal(cg.to_host(got[-1:, :, :, :40].contiguous()), want)
+
+
+def test_longest_contraction(cg):
+    """K at the end of the route, words whose residues modulo 256 are -128 on both sides (the inverse multiplied into the
+    right one is odd): 2 * 65000 products of 2^14 and the 2^15 that the accumulators start from."""
+    M, N, K, word = 2048, 2048, 65000, 0x7F7F7F7F7F7F7F80
+    say(f"residue route K={K}, largest accumulators")
+    need = cg.cg_share_matmul_workspace_bytes(M, N, K)
+    assert need > cg.cg_share_matmul_digit_workspace_bytes(M, N, K)
+    assert cg.cg_share_matmul_workspace_bytes(M, N, K + 2) == cg.cg_share_matmul_digit_workspace_bytes(M, N, K + 2)
+    x = torch.full((M, K), word, dtype=torch.int64, device="cuda")
+    w = torch.full((N, K), word, dtype=torch.int64, device="cuda")
+    got = cg.cg_share_matmul_ws(x, x, w, torch.zeros_like(w), poisoned(need))
+    want = 2 * K * word * word % (1 << 64)
+    assert bool((got == (want - (1 << 64) if want >> 63 else want)).all())
+
+
+def device_ring(shape, seed):   # drawn on the GPU: gigabytes of words
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return torch.randint(-2 ** 63, 2 ** 63 - 1, shape, dtype=torch.int64, device="cuda", generator=gen)
+
+
+# residues of one modulus just below 2^31 bytes, on the left, on the right, and gathered
+@pytest.mark.parametrize("M,N", [(262142, 512), (512, 262143)])
+def test_largest_planes(cg, ro, M, N):
+    K = 4096
+    say(f"residue route near the limit of a plane M={M} N={N} K={K}")
+    more = (M + (M > N), N + (N > M), K)
+    assert cg.cg_share_matmul_workspace_bytes(*more) == cg.cg_share_matmul_digit_workspace_bytes(*more)
+    need = cg.cg_share_matmul_workspace_bytes(M, N, K)
+    assert need > cg.cg_share_matmul_digit_workspace_bytes(M, N, K)
+    dev = [device_ring((r, K), 9800 + i) for i, r in enumerate((M, M, N, N))]
+    got = cg.cg_share_matmul_ws(*dev, poisoned(need))
+    assert torch.equal(got, cg.cg_share_matmul(*dev))
+    host = [cg.to_host(t[-40:].contiguous()) for t in dev]
+    assert np.array_equal(cg.to_host(got[-40:, -40:].contiguous()), ro.party_matmul(*host))
+    del dev, got
+    torch.cuda.empty_cache()
+
+
+def test_largest_gathered_plane(cg, ro):
+    xs, ws = (8, 362, 362, 1024), (256, 3, 3, 1024)
+    say(f"residue route near the limit of a plane, conv x={xs} w={ws}")
+    need = cg.cg_share_conv2d_workspace_bytes(xs, ws, (1, 1), (1, 1))
+    assert need > cg.cg_share_conv2d_digit_workspace_bytes(xs, ws, (1, 1), (1, 1))
+    dev = [device_ring(s, 9850 + i) for i, s in enumerate((xs, xs, ws, ws))]
+    got = cg.cg_share_conv2d_ws(*dev, poisoned(need), stride=(1, 1), pad=(1, 1))
+    assert torch.equal(got, cg.cg_share_conv2d(*dev, stride=(1, 1), pad=(1, 1)))
+    # the last image's last corner
+    host = [cg.to_host(t[-1:, -4:, -4:].contiguous()) for t in dev[:2]] + [cg.to_host(t[-8:].contiguous()) for t in dev[2:]]
+    want = ro.party_conv2d(*host, (1, 1), (1, 1))[:, 1:, 1:]
+    assert np.array_equal(cg.to_host(got[-1:, -3:, -3:, -8:].contiguous()), want)
+    del dev, got
+    torch.cuda.empty_cache()
 
 
 # both tiles with 18 and with 19 moduli on gathered patches: even and odd channel counts, windows, strides and paddings

@@ -4,11 +4,32 @@ import numpy as np
 import pytest
 
 from tests.gpu_util import say
-from tests.test_gpu_residue import cg, ro, wl  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def cg():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2104_10949_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.fixture(scope="module")
+def ro():
+    from oracle import ring_oracle
+    return ring_oracle
+
+
+@pytest.fixture(scope="module")
+def wl():
+    from paper_2104_10949_amd import workloads
+    return workloads
+
 
 SHAPES = [(65, 1, 2), (66, 17, 34), (128, 128, 784), (127, 129, 62), (1000, 10, 130), (300, 33, 1026), (128, 10, 2048),
           (80, 16, 9000),                        # K split over blocks
@@ -19,7 +40,7 @@ SHAPES = [(65, 1, 2), (66, 17, 34), (128, 128, 784), (127, 129, 62), (1000, 10, 
 
 
 @pytest.mark.parametrize("M,N,K", SHAPES)
-def test_small_products(cg, ro, wl, M, N, K):  # noqa: F811
+def test_small_products(cg, ro, wl, M, N, K):
     say(f"small product M={M} N={N} K={K}")
     ops = [wl.draw_ring((r, K), 9600 + i) for i, r in enumerate((M, M, N, N))]
     dev = [cg.to_device(a) for a in ops]
