@@ -37,22 +37,24 @@ LAST_LEVEL_CACHE_BYTES = 256 << 20
 DIGIT_MACS_PER_RING_MAC_TRIPLE = 72  # 2 ring products x 36 signed-byte digit pairs per (m, n, k)
 
 
-def ws_macs_per_triple(ws_bytes, x_rows, x_k, N, K):
+RESIDUE_K_18 = 5500   # RNS_K_18 of share_gemm_rns.h: the longest contraction of 18 moduli, beyond it there are 19
+
+
+def ws_macs_per_triple(ws_bytes, digit_bytes, K):
     """int8 products per (m, n, k) of the route an *_ws call with the full scratch memory takes: the digit planes (or no
-    scratch memory) 72; the residues, which ask for more than the planes' bytes, 2 per modulus, 18 of them up to K = 5500."""
-    rows16 = lambda R, k: (R + 15) // 16 * 16 * ((k + 31) // 32) * 256
-    if ws_bytes <= 2 * rows16(x_rows, x_k) + 2 * rows16(N, K):
+    scratch memory) 72; the residues, which ask for more than the planes' bytes, 2 per modulus."""
+    if ws_bytes <= digit_bytes:
         return DIGIT_MACS_PER_RING_MAC_TRIPLE
-    return 36 if K <= 5500 else 38
+    return 2 * (18 if K <= RESIDUE_K_18 else 19)
 
 
 WORKLOAD_CONFIG = 4
-# HBM bytes per share_gemm_kernel launch on the config-4 step, from the two rocprofv3 --pmc runs summarised in
-# profiles/share_gemm_config4_hbm_traffic.txt, taken with the digit planes on every layer that uses scratch memory
-# (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000 by the 1 GiB copy calibration).
-PROFILED_TRAFFIC_CONFIG4 = {"read_bytes_per_launch": 65.8e6, "write_bytes_per_launch": 22.6e6,
+# HBM bytes on the config-4 step as it is timed by default, from the two rocprofv3 --pmc runs summarised in
+# profiles/share_gemm_config4_hbm_traffic.txt (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000 by the 1 GiB copy calibration): per
+# product kernel, and all conversions, combinations and clearings of a step together.
+PROFILED_TRAFFIC_CONFIG4 = {"read_bytes_per_launch": 89.1e6, "write_bytes_per_launch": 29.5e6,
                             "algorithmic_bytes_per_launch": 61.0e6,
-                            "conversion_pass_per_scratch_route_layer": {"read_bytes": 47.8e6, "write_bytes": 43.5e6},
+                            "other_kernels_per_step": {"read_bytes": 634.5e6, "write_bytes": 856.0e6},
                             "source": "profiles/share_gemm_config4_hbm_traffic.txt"}
 
 
@@ -123,7 +125,8 @@ def measure_rows(torch, cg, wl, headline_config):
         z = torch.empty((M, N), dtype=torch.int64, device="cuda")
         ws = torch.empty(cg.cg_share_matmul_workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda")
         ops_per = 2.0 * DIGIT_MACS_PER_RING_MAC_TRIPLE * M * N * K
-        ws_ops_per = 2.0 * ws_macs_per_triple(ws.numel(), M, K, N, K) * M * N * K
+        ws_macs = ws_macs_per_triple(ws.numel(), cg.cg_share_matmul_digit_workspace_bytes(M, N, K), K)
+        ws_ops_per = 2.0 * ws_macs * M * N * K
         ms = _timed(torch, lambda: cg.cg_share_matmul(*ops, z_i=z), warm=2, iters=8)
         ms_ws = _timed(torch, lambda: cg.cg_share_matmul_ws(*ops, ws, z_i=z), warm=2, iters=8)
         rows.append({"gemm": [M, N, K], "cg_share_matmul_ms": round(ms, 4),
@@ -438,7 +441,7 @@ def main() -> int:
     torch.cuda.synchronize()
 
     # Route per layer.  The library offers every product with and without caller-supplied scratch memory (the
-    # *_ws entry points: operands split into digit planes once, then a product kernel without split work); its
+    # *_ws entry points: operands turned into residues or digit planes once, then a product kernel that moves bytes); its
     # own rule of thumb (cg_share_*_prefers_workspace) says which one to call for a shape.  The scratch buffer
     # is allocated here, once, outside the timed region, like the operands; --plain times the plain calls only.
     def prefers_ws(L) -> bool:
@@ -452,6 +455,11 @@ def main() -> int:
         if L.kind == "conv":
             return cg.cg_share_conv2d_workspace_bytes(L.x_shape, L.w_shape, (L.stride, L.stride), (L.pad, L.pad))
         return cg.cg_share_matmul_workspace_bytes(*L.gemm)
+
+    def digit_bytes(L) -> int:
+        if L.kind == "conv":
+            return cg.cg_share_conv2d_digit_workspace_bytes(L.x_shape, L.w_shape, (L.stride, L.stride), (L.pad, L.pad))
+        return cg.cg_share_matmul_digit_workspace_bytes(*L.gemm)
     use_ws = [prefers_ws(L) for L in layers]
     scratch = torch.empty(max([ws_bytes(L) for L, u in zip(layers, use_ws) if u] + [16]), dtype=torch.uint8,
                           device="cuda")
@@ -594,8 +602,7 @@ def main() -> int:
     def ops_of(L) -> float:   # int8 operations that the timed route of one launch executes
         macs = DIGIT_MACS_PER_RING_MAC_TRIPLE
         if prefers_ws(L):
-            x_rows, x_k = (L.B * L.H * L.W, L.Cin) if L.kind == "conv" else (L.M, L.K)
-            macs = ws_macs_per_triple(ws_bytes(L), x_rows, x_k, L.gemm[1], L.gemm[2])
+            macs = ws_macs_per_triple(ws_bytes(L), digit_bytes(L), L.gemm[2])
         return 2.0 * macs * L.mnk
     int8_ops_per_step = sum(ops_of(L) * L.repeat for L in layers)
     achieved_tops = int8_ops_per_step / (kernel_ms_sum * 1e-3) / 1e12
@@ -630,7 +637,9 @@ def main() -> int:
     for L, ms in zip(layers, per_layer_ms):
         t_mfma = ops_of(L) / (INT8_PEAK_TOPS * 1e12)
         t_hbm = L.algorithmic_bytes / 8e12
+        macs = int(round(ops_of(L) / (2.0 * L.mnk)))
         per_layer.append({"name": L.name, "gemm": list(L.gemm), "repeat": L.repeat, "us": round(ms * 1e3, 2),
+                          "int8_products": "digits" if macs == DIGIT_MACS_PER_RING_MAC_TRIPLE else f"{macs // 2} residues",
                           "t_roof_us": round(max(t_mfma, t_hbm) * 1e6, 2), "bound": "mfma" if t_mfma >= t_hbm else "hbm",
                           "frac_of_roof": round(max(t_mfma, t_hbm) / (ms * 1e-3), 4)})
     roofline["layers"] = per_layer
@@ -706,7 +715,8 @@ def main() -> int:
         "metric": METRIC, "value": value, "unit": "ring MAC/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step, "step_spread": step_spread,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "int8", "dtype_note": "u64 ring elements as 8 signed-byte digits on int8 MFMA, i32 accumulate, exact",
+        "dtype": "int8", "dtype_note": "u64 ring elements as 8 signed-byte digits, or as 18 to 19 residues of 8 bits where "
+                                       "roofline.layers says so, on int8 MFMA, i32 accumulate, exact",
         "data": "synthetic",
         "config": {"workload": {1: "config 1: share matmul 256^3",
                                 2: "config 2: FC stack 784-128-128-10, batch 128",

@@ -12,10 +12,14 @@
 // and k = round(sum_m r_m / p_m): the integer lies within 0.499 P of zero (that is what RNS_K_18 says), the rounded
 // sum is exact to 3e-4, so k is the right one.
 //
-// Measured on MI355X, whole calls against the digit-plane route: 4096^3 3400 -> 2300 us, 3072 x 3072 x 1024 517 -> 415,
-// 2048^3 445 -> 371; 3x3 layers at batch 32: 16 x 16 x 256 -> 256 242 -> 208, 8 x 8 x 512 -> 512 248 -> 201.  At 4096^3:
-// conversion 330 us (52 bytes per word pair at 5.3 TB/s: memory), product 1850-2000 us (62 % of the cycles issue matrix
-// instructions; 1410 us on all-zero words, so the rest is the clock that random operands leave), combination 85 us.
+// Exact matrix products through int8 products modulo such numbers and the Chinese remainder theorem are a published
+// method (Ozaki, Uchino and Imamura, "Ozaki Scheme II", 2025, there for floating-point products).
+//
+// Measured on MI355X, whole calls, the better of the plain kernel and the digit planes against residues: 4096^3 3450 -> 2190 us,
+// 2048^3 456 -> 372, 3072 x 3072 x 1024 517 -> 415; 3x3 layers at batch 32: 16 x 16 x 256 -> 256 254 -> 204, 8 x 8 x 512 -> 512
+// 262 -> 209, the 5x5 one 628 -> 468.  At 4096^3: conversion 330 us (52 bytes per word pair at 5.2 TB/s: memory), product
+// 1840-1980 us (the matrix pipes are busy 75 % of the cycles, at 1.6 GHz; 1410 us on all-zero words: the clock that random operands
+// leave), combination 90 us.
 // Where operands or outputs are large against M*N*K, or the grid leaves most of a round empty, the three passes cost
 // more than they save; the caller's rule compares both.
 #include "share_gemm_rns.h"

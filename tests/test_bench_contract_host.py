@@ -56,8 +56,18 @@ def test_traffic_constants_are_the_ones_the_committed_counter_summary_holds():
     assert abs(float(m.group(2)) * 1e6 - t["write_bytes_per_launch"]) < 0.05e6
     m = re.search(r"([\d.]+) MB per dispatch", text)
     assert m and abs(float(m.group(1)) * 1e6 - t["algorithmic_bytes_per_launch"]) < 0.05e6
-    # the conversion pass: the to_planes_kernel line holds FETCH_SIZE and WRITE_SIZE in KiB per dispatch (x 2.000, x 1.000)
-    m = re.search(r"to_planes_kernel\S*\s+\d+\s+([\d.]+)\s+([\d.]+)", text)
-    conv = t["conversion_pass_per_scratch_route_layer"]
-    assert m and abs(float(m.group(1)) * 1024 * 2.0 - conv["read_bytes"]) < 0.05e6
-    assert abs(float(m.group(2)) * 1024 * 1.0 - conv["write_bytes"]) < 0.05e6
+    m = re.search(r"([\d.]+) MB read, ([\d.]+) MB written per step", text)
+    other = t["other_kernels_per_step"]
+    assert m and abs(float(m.group(1)) * 1e6 - other["read_bytes"]) < 0.05e6
+    assert abs(float(m.group(2)) * 1e6 - other["write_bytes"]) < 0.05e6
+
+
+def test_operations_are_counted_for_the_route_taken():
+    import re
+    sys.path.insert(0, ROOT)
+    import bench
+    text = open(os.path.join(ROOT, "paper_2104_10949_amd", "csrc", "share_gemm_rns.h")).read()
+    assert int(re.search(r"RNS_K_18 = (\d+);", text).group(1)) == bench.RESIDUE_K_18
+    assert bench.ws_macs_per_triple(100, 100, 64) == bench.ws_macs_per_triple(0, 0, 64) == 72
+    assert bench.ws_macs_per_triple(101, 100, 5500) == bench.ws_macs_per_triple(101, 0, 5499) == 36
+    assert bench.ws_macs_per_triple(101, 100, 5501) == 38
