@@ -688,14 +688,16 @@ Residues plan_residues(const Plan& pl) {
     if (!cg::rns_plan(&r)) return res;
     // Both routes in seconds, from measurements on MI355X.  Plain kernel: 144 operations per (m, n, k) of its 128 x 64
     // tiles at 2.6e15 a second, 1.2 times that with 8-byte loads, 1.3 times with 8-byte gathers (1.2 to 1.8 over 650 layers,
-    // median 1.55), 8 microseconds, and up to 8 more where the tiles are so few that K is split; 0.93 of it where the digit planes
+    // median 1.55; less where the window is larger than the image, 1.04, 1.12 and 1.22 at 4, 5 and 6 pixels under 7 taps), 8 microseconds, and up to 8 more where the tiles are so few that K is split; 0.93 of it where the digit planes
     // pay.  Residues: 16 + 2 * nmod bytes per word pair converted at 4.9 TB/s (4.0 with 8-byte loads), 2 * nmod + 8 per output
     // combined at 8.5 TB/s (measured up to 16384 x 16384 outputs), the product as rns_plan models it, and 12
     // microseconds for three launches that do not fill the chip at both ends.  They must win by a margin to be preferred,
-    // a little more on strided layers, where the model scatters most: of 3400 random layers and 1300 products, none
-    // that is taken was more than 2 % slower than without residues.
+    // a little more on strided layers, where the model scatters most: of 1900 random layers and 1300 products other than
+    // those of the fit, none that is taken is more than 2 % slower than without residues.
     const double up_m = (double)((p.M + (int64_t)127) / 128 * 128), up_n = (double)((p.N + (int64_t)63) / 64 * 64);
-    const double work = 144.0 * up_m * up_n * (double)p.K / 2.6e15 * (pl.planes_ok ? 1.0 : conv ? 1.3 : 1.2);
+    const double inside = conv ? (p.H < p.kh ? (double)p.H / p.kh : 1.0) * (p.W < p.kw ? (double)p.W / p.kw : 1.0) : 1.0;
+    const double loads = pl.planes_ok ? 1.0 : !conv ? 1.2 : inside < 0.9 ? 0.85 + 0.5 * inside : 1.3;
+    const double work = 144.0 * up_m * up_n * (double)p.K / 2.6e15 * loads;
     double best = work + 8.0e-6;
     if (up_m * up_n < 256.0 * 128.0 * 64.0) best += work < 8.0e-6 ? work : 8.0e-6;
     if (planes_pay(pl)) best *= 0.93;

@@ -120,6 +120,7 @@ LAYERS = [(((15, 69, 69, 896), (144, 5, 5, 896), (2, 2), (2, 2)), 0, 4096, 3653,
           (((4, 101, 101, 1024), (352, 3, 3, 1024), (1, 2), (1, 1)), 1, 3833, 3221, 3344),
           (((13, 5, 5, 1136), (1008, 7, 7, 1136), (1, 1), (3, 3)), 0, 1309, 1846, 1638),
           (((20, 13, 13, 1296), (224, 5, 5, 1296), (2, 2), (2, 2)), 0, 608, 776, 689),
+          (((35, 4, 4, 1104), (496, 7, 7, 1104), (1, 1), (3, 3)), 0, 1032, 1119, 1119),
           (((32, 16, 16, 256), (256, 3, 3, 256), (1, 1), (1, 1)), 1, 254, 211, 204),
           (((32, 8, 8, 512), (512, 3, 3, 512), (1, 1), (1, 1)), 1, 262, 246, 209),
           (((32, 32, 32, 128), (128, 3, 3, 128), (1, 1), (1, 1)), 1, 266, 356, 237),
