@@ -28,9 +28,9 @@
 //
 // Bound: the vector ALU (about 290 instructions per AES block, 128 of them lookup addresses), with the LDS close
 // behind (133 lookups of two cycles each, one LDS for four SIMDs).  Measured: the truncation step with both streams on
-// 2^23 words 167 -> 129 us (of that 30 us by the shared rounds and short-call launch shape, 8 us by keys in
-// registers and three-input xors); a call of 2^15 words 10.2 -> 6.8 us (all compute units instead of 17, tables read
-// from device memory and filled 16 bytes at a time).
+// 2^23 words 167 -> 126 us (of that 30 us by the shared rounds and short-call launch shape, 8 us by keys in
+// registers and three-input xors); a zero share of 2^15 words 8.7 -> 5.9 us (all compute units instead of 17, tables read
+// from device memory and filled 16 bytes at a time, keys requested ahead of them).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
