@@ -56,6 +56,11 @@ def test_traffic_constants_are_the_ones_the_committed_counter_summary_holds():
     assert abs(float(m.group(2)) * 1e6 - t["write_bytes_per_launch"]) < 0.05e6
     m = re.search(r"([\d.]+) MB per dispatch", text)
     assert m and abs(float(m.group(1)) * 1e6 - t["algorithmic_bytes_per_launch"]) < 0.05e6
+    # the conversion pass: the to_planes_kernel line holds FETCH_SIZE and WRITE_SIZE in KiB per dispatch (x 2.000, x 1.000)
+    m = re.search(r"to_planes_kernel\S*\s+\d+\s+([\d.]+)\s+([\d.]+)", text)
+    conv = t["conversion_pass_per_scratch_route_layer"]
+    assert m and abs(float(m.group(1)) * 1024 * 2.0 - conv["read_bytes"]) < 0.05e6
+    assert abs(float(m.group(2)) * 1024 * 1.0 - conv["write_bytes"]) < 0.05e6
     m = re.search(r"([\d.]+) MB read, ([\d.]+) MB written per step", text)
     other = t["other_kernels_per_step"]
     assert m and abs(float(m.group(1)) * 1e6 - other["read_bytes"]) < 0.05e6
