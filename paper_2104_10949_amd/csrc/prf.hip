@@ -10,13 +10,13 @@
 //
 // AES rounds use the classic 32-bit table formulation of FIPS-197: the table
 // T0[x] = (2 S[x], S[x], S[x], 3 S[x]); the other three columns of the MixColumns
-// matrix are its byte rotations T1 = rotl8(T0), T2 = rotl16(T0), T3 = rotl8(T2).
-// Rotation distributes over XOR, so with T0 and T2 both in memory a column costs one
-// rotation: (T0[a] ^ T2[c]) ^ rotl8(T0[b] ^ T2[d]).  The last round uses the S-box
-// byte of T0.  Each table sits in LDS once per bank (64 copies, 64 KiB each, 128 KiB
-// per block of up to 16 waves): lane i reads entry x of table t at byte 65536 t + 256 x + 4 i,
-// always from bank i, so the data-dependent lookups of a wave never collide, and the
-// whole address is ONE byte permute of (state word, lane constant).  Round keys are
+// matrix are its byte rotations T1 = rotl8(T0), T2 = rotl16(T0), T3 = rotl24(T0).
+// With all four in memory a column is four lookups and two three-input xors; the last round takes S-box bytes
+// from the table that has them in the right place.  The LDS serves a wave's lookup in two halves of 32 lanes
+// (the counters show two cycles each and no conflict), so 32 copies of an entry are enough: a row of 256 bytes
+// holds entry x of T0 and of T1, 32 copies each, 64 KiB further on lie T2 and T3 (128 KiB per block of up to 16
+// waves).  Lane i reads byte 65536 p + 256 x + 128 t + 4 (i % 32), always from its own bank, and the
+// address is ONE byte permute of (state word, lane constant) with 128 t as the instruction's offset.  Round keys are
 // expanded on the host and passed by value.
 //
 // Two rounds shared by 256 counters.  In counter mode 256 consecutive block indices differ
@@ -26,11 +26,12 @@
 // caching, Bernstein and Schwabe, "New AES software speed records", 2008).  A block is
 // 5 + 7*16 + 16 = 133 lookups instead of 160.
 //
-// Bound: the vector ALU (about 290 instructions per AES block, 128 of them lookup addresses), with the LDS close
-// behind (133 lookups of two cycles each, one LDS for four SIMDs).  Measured: the truncation step with both streams on
+// Bound: the LDS (133 lookups of two cycles per wave, stream and block of AES, 87 of the 119 us of the measured call),
+// with the vector ALU behind it (about 215 instructions per AES block, 128 of them lookup addresses; 290 with two tables,
+// whose columns needed a rotation, 64 copies each).  Measured: the truncation step with both streams on
 // 2^23 words 167 -> 126 us (of that 30 us by the shared rounds and short-call launch shape, 8 us by keys in
-// registers and three-input xors); a zero share of 2^15 words 8.7 -> 5.9 us (all compute units instead of 17, tables read
-// from device memory and filled 16 bytes at a time, keys requested ahead of them).
+// registers and three-input xors), 128.5 -> 119.6 by four tables; a zero share of 2^15 words 8.7 -> 5.9 us (all compute units
+// instead of 17, tables read from device memory and filled 16 bytes at a time, keys requested ahead of them).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -105,13 +106,14 @@ constexpr int PRF_MAX_WAVES = 16;      // waves of a block; its tables leave roo
 constexpr int PRF_MAX_GROUPS = 512;    // groups of 256 counters whose constants a block can hold
 constexpr int PRF_MAX_CHUNKS = 4 * (PRF_MAX_GROUPS - 1);   // chunks of 64 counters, the first anywhere in its group
 
-// LDS byte address of a table entry: byte 0 = 4 * (lane % 64) and byte 2 = table number
-// come from the lane constant `lc` = 4 * lane | 0x0100, byte 1 = byte `B` of the state word.
+// Entry of table T<TABLE> for byte B of a state word.  Byte 0 of the LDS address = 4 * (lane % 32) and byte 2 = which pair
+// of tables come from the lane constant `lc` = 4 * (lane % 32) | 0x0100, byte 1 = the state byte; the second table of a
+// pair lies 128 bytes on, which is the instruction's own offset.
 // v_perm_b32(S0, S1, sel): selector values 0-3 pick bytes of S1, 4-7 bytes of S0, 0x0c gives 0.
 template <int B, int TABLE>
 __device__ __forceinline__ u32 lut(const char* __restrict__ tbl, u32 state, u32 lc) {
-    constexpr u32 sel = 0x0C000000u | (TABLE ? 0x00010000u : 0x000C0000u) | ((u32)(4 + B) << 8);
-    return *reinterpret_cast<const u32*>(tbl + __builtin_amdgcn_perm(state, lc, sel));
+    constexpr u32 sel = 0x0C000000u | (TABLE >= 2 ? 0x00010000u : 0x000C0000u) | ((u32)(4 + B) << 8);
+    return *reinterpret_cast<const u32*>(tbl + __builtin_amdgcn_perm(state, lc, sel) + (TABLE & 1) * 128);
 }
 
 __device__ __forceinline__ u32 rotl8(u32 v) { return __builtin_amdgcn_alignbit(v, v, 24); }
@@ -121,16 +123,15 @@ __device__ __forceinline__ u32 xor3(u32 a, u32 b, u32 c) { return __builtin_amdg
 
 // one output column of a full round: bytes 0..3 taken from state words a, b, c, d
 __device__ __forceinline__ u32 column(const char* tbl, u32 lc, u32 a, u32 b, u32 c, u32 d, u32 rk) {
-    return xor3(lut<0, 0>(tbl, a, lc), lut<2, 1>(tbl, c, lc), rk) ^ rotl8(lut<1, 0>(tbl, b, lc) ^ lut<3, 1>(tbl, d, lc));
+    return xor3(xor3(lut<0, 0>(tbl, a, lc), lut<1, 1>(tbl, b, lc), rk), lut<2, 2>(tbl, c, lc), lut<3, 3>(tbl, d, lc));
 }
 
-// one output word of the last round: S-box bytes (byte 1 of T0) of byte 0 of a, 1 of b, 2 of c, 3 of d
+// one output word of the last round: S-box bytes of byte 0 of a, 1 of b, 2 of c, 3 of d, each from a table that has it in
+// that place (T3 in bytes 0 and 1, T1 in bytes 2 and 3)
 __device__ __forceinline__ u32 last_column(const char* tbl, u32 lc, u32 a, u32 b, u32 c, u32 d, u32 rk) {
-    const u32 ta = lut<0, 0>(tbl, a, lc), tb = lut<1, 0>(tbl, b, lc), tc = lut<2, 0>(tbl, c, lc),
-              td = lut<3, 0>(tbl, d, lc);
-    const u32 lo = __builtin_amdgcn_perm(tb, ta, 0x0C0C0501u);  // (ta.b1, tb.b1, 0, 0)
-    const u32 hi = __builtin_amdgcn_perm(td, tc, 0x0C0C0501u);
-    return __builtin_amdgcn_perm(hi, lo, 0x05040100u) ^ rk;
+    const u32 lo = __builtin_amdgcn_perm(lut<1, 3>(tbl, b, lc), lut<0, 3>(tbl, a, lc), 0x0C0C0500u);
+    const u32 hi = __builtin_amdgcn_perm(lut<3, 1>(tbl, d, lc), lut<2, 1>(tbl, c, lc), 0x07020C0Cu);
+    return xor3(lo, hi, rk);
 }
 
 // What a group of 256 counters shares of rounds 1 and 2: column 0 after round 1 without the lookup of the counter's
@@ -139,14 +140,14 @@ __device__ __forceinline__ void group_constants(const char* __restrict__ tbl, u3
                                                 u64 first_block, u64 nonce, u32& c1, uint4& c2) {
     const u32 s0 = (u32)first_block ^ rk[0], s1 = (u32)(first_block >> 32) ^ rk[1], s2 = (u32)nonce ^ rk[2],
               s3 = (u32)(nonce >> 32) ^ rk[3];
-    c1 = lut<2, 1>(tbl, s2, lc) ^ rotl8(lut<1, 0>(tbl, s1, lc) ^ lut<3, 1>(tbl, s3, lc)) ^ rk[4];
+    c1 = xor3(lut<1, 1>(tbl, s1, lc), lut<2, 2>(tbl, s2, lc), lut<3, 3>(tbl, s3, lc)) ^ rk[4];
     const u32 n1 = column(tbl, lc, s1, s2, s3, s0, rk[5]);
     const u32 n2 = column(tbl, lc, s2, s3, s0, s1, rk[6]);
     const u32 n3 = column(tbl, lc, s3, s0, s1, s2, rk[7]);
-    c2.x = lut<2, 1>(tbl, n2, lc) ^ rotl8(lut<1, 0>(tbl, n1, lc) ^ lut<3, 1>(tbl, n3, lc)) ^ rk[8];
-    c2.y = lut<0, 0>(tbl, n1, lc) ^ lut<2, 1>(tbl, n3, lc) ^ rotl8(lut<1, 0>(tbl, n2, lc)) ^ rk[9];
-    c2.z = lut<0, 0>(tbl, n2, lc) ^ rotl8(lut<1, 0>(tbl, n3, lc) ^ lut<3, 1>(tbl, n1, lc)) ^ rk[10];
-    c2.w = lut<0, 0>(tbl, n3, lc) ^ lut<2, 1>(tbl, n1, lc) ^ rotl8(lut<3, 1>(tbl, n2, lc)) ^ rk[11];
+    c2.x = xor3(lut<1, 1>(tbl, n1, lc), lut<2, 2>(tbl, n2, lc), lut<3, 3>(tbl, n3, lc)) ^ rk[8];
+    c2.y = xor3(lut<0, 0>(tbl, n1, lc), lut<1, 1>(tbl, n2, lc), lut<2, 2>(tbl, n3, lc)) ^ rk[9];
+    c2.z = xor3(lut<0, 0>(tbl, n2, lc), lut<1, 1>(tbl, n3, lc), lut<3, 3>(tbl, n1, lc)) ^ rk[10];
+    c2.w = xor3(lut<0, 0>(tbl, n3, lc), lut<2, 2>(tbl, n1, lc), lut<3, 3>(tbl, n2, lc)) ^ rk[11];
 }
 
 // Round keys 3..10 of the streams of a launch and the byte that meets the counter's byte 0, fetched once per wave and
@@ -181,9 +182,9 @@ __device__ __forceinline__ void aes_blocks(const char* __restrict__ tbl, u32 lc,
     for (int e = 0; e < NS; ++e) {
         const u32 t = c1[e] ^ lut<0, 0>(tbl, byte0 ^ key.k0[e], lc);
         s[e][0] = c2[e].x ^ lut<0, 0>(tbl, t, lc);
-        s[e][1] = c2[e].y ^ rotl8(lut<3, 1>(tbl, t, lc));
-        s[e][2] = c2[e].z ^ lut<2, 1>(tbl, t, lc);
-        s[e][3] = c2[e].w ^ rotl8(lut<1, 0>(tbl, t, lc));
+        s[e][1] = c2[e].y ^ lut<3, 3>(tbl, t, lc);
+        s[e][2] = c2[e].z ^ lut<2, 2>(tbl, t, lc);
+        s[e][3] = c2[e].w ^ lut<1, 1>(tbl, t, lc);
     }
 #pragma unroll
     for (int r = 0; r < 7; ++r) {
@@ -221,23 +222,23 @@ __global__ __launch_bounds__(64 * PRF_MAX_WAVES) void prf_combine_kernel(const u
                                                           u64 mask_nonce, int d, bool add_mask, bool xor_mode,
                                                           bool pairs, u32 per_wg, const PrfKeys keys) {
     constexpr int NS = (ALPHA ? 2 : 0) + (MASK ? 1 : 0);
-    __shared__ __attribute__((aligned(16))) u32 tables[2 * 256 * 64];  // T0 then T2, one copy per bank
+    __shared__ __attribute__((aligned(16))) u32 tables[2 * 256 * 64];  // (T0, T1) then (T2, T3), 32 copies of an entry
     __shared__ uint4 group_c2[NS][PRF_MAX_GROUPS];
     __shared__ u32 group_c1[NS][PRF_MAX_GROUPS];
     // The keys first: their way from the argument buffer passes while the tables are filled.
     RoundKeys<NS> key;
     key.load(keys);
-    // 16 bytes, i.e. four of the 64 copies, of an entry of both tables per thread and trip
+    // 16 bytes, i.e. four of the 32 copies, of an entry of one table of either pair per thread and trip
 #pragma unroll 4
     for (u32 i = threadIdx.x; i < 256 * 16; i += blockDim.x) {
-        const u32 v0 = device_tables.t0[i >> 4], v2 = (v0 << 16) | (v0 >> 16);
+        const u32 t = device_tables.t0[i >> 4], v0 = i & 8u ? rotl8(t) : t, v2 = (v0 << 16) | (v0 >> 16);
         reinterpret_cast<uint4*>(tables)[i] = uint4{v0, v0, v0, v0};
         reinterpret_cast<uint4*>(tables)[256 * 16 + i] = uint4{v2, v2, v2, v2};
     }
     __syncthreads();
     const char* tbl = reinterpret_cast<const char*>(tables);
     const u32 lane = threadIdx.x & 63;
-    const u32 lc = (lane << 2) | 0x0100u;
+    const u32 lc = ((lane & 31u) << 2) | 0x0100u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = blockDim.x >> 6;
     const u64 b_first = first >> 1, b_last = (first + n - 1) >> 1;  // n >= 1
     const u64 ch_last = b_last >> 6;
