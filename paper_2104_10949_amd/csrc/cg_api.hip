@@ -702,8 +702,9 @@ Residues plan_residues(const Plan& pl) {
     if (up_m * up_n < 256.0 * 128.0 * 64.0) best += work < 8.0e-6 ? work : 8.0e-6;
     if (planes_pay(pl)) best *= 0.93;
     const double pairs = ((double)r.x_rows + (double)p.N * r.kh * r.kw) * r.slices * 64.0;
+    const double outputs = (double)round_up((u64)r.M, (u64)r.tile) * (double)round_up((u64)r.N, (u64)r.tile);
     const double rns = pairs * (16.0 + 2.0 * r.nmod) / (words % 2 == 0 ? 4.9e12 : 4.0e12) +
-                       (double)r.r_plane * (2.0 * r.nmod + 8.0) / 8.5e12 + 1.0e-6 * r.product_us + 12.0e-6;
+                       outputs * (2.0 * r.nmod + 8.0) / 8.5e12 + 1.0e-6 * r.product_us + 12.0e-6;
     res.pay = rns < (conv && (p.sh > 1 || p.sw > 1) ? 0.90 : 0.92) * best;
     return res;
 }

@@ -15,6 +15,13 @@ namespace cg {
 constexpr int64_t RNS_K_18 = 5500;
 constexpr int64_t RNS_K_MAX = 65000;
 
+// The product of some of the moduli on square tiles of one size.
+struct RnsPart {
+    int tiles_m, tiles_n;
+    int first, count;                        // moduli first .. first + count - 1
+    FastDiv div_tiles, div_group;
+};
+
 struct RnsParams {
     const uint64_t *x_a, *x_b, *w_a, *w_b;   // shares: left rows of `words` words, right rows of taps * words words
     uint64_t* z;                             // [M, N] row-major
@@ -26,9 +33,12 @@ struct RnsParams {
     int conv;                                // the left operand's rows are gathered tap by tap
     int H, W, Ho, Wo, kh, kw, sh, sw, ph, pw;
     int nmod;
-    int tile, tiles_m, tiles_n;              // square tiles of 256 or 128
-    double product_us;                       // modelled time of the product
-    FastDiv div_slices, div_taps, div_howo, div_wo, div_tiles, div_group, div_blocks_n;
+    RnsPart large, small;                    // which moduli run on tiles of 256 and which on tiles of 128
+    int tile;                                // the size that would be taken for all moduli, were it one (256 or 128)
+    int by_rounds;                           // the XCDs work on one modulus at a time
+    int blocks_n;                            // 16 x 16 blocks of the result's planes along N
+    double product_us;                       // modelled time of the product with that size for all moduli
+    FastDiv div_slices, div_taps, div_howo, div_wo, div_blocks_n;
 };
 
 // Fills every size of p that follows from M, N, words, x_rows and the window; false where the route does not apply
