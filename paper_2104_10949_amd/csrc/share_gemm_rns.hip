@@ -16,8 +16,8 @@
 // method (Ozaki, Uchino and Imamura, "Ozaki Scheme II", 2025, there for floating-point products).
 //
 // Measured on MI355X, whole calls, the better of the plain kernel and the digit planes against residues: 4096^3 3450 -> 2140 us,
-// 2048^3 456 -> 366, 3072 x 3072 x 1024 517 -> 415; 3x3 layers at batch 32: 16 x 16 x 256 -> 256 254 -> 190, 8 x 8 x 512 -> 512
-// 262 -> 193, the 5x5 one 628 -> 439.  At 4096^3: conversion 330 us (52 bytes per word pair at 5.2 TB/s: memory), product
+// 2048^3 456 -> 367, 3072 x 3072 x 1024 517 -> 418; 3x3 layers at batch 32: 16 x 16 x 256 -> 256 254 -> 179, 8 x 8 x 512 -> 512
+// 262 -> 181, the 5x5 one 628 -> 425.  At 4096^3: conversion 330 us (52 bytes per word pair at 5.2 TB/s: memory), product
 // 1670-1750 us (the matrix pipes are busy 78 % of the cycles, at 1.75 GHz: the clock that random operands leave), combination 90 us.
 // Where operands or outputs are large against M*N*K, or the grid leaves most of a round empty, the three passes cost
 // more than they save; the caller's rule compares both.
@@ -565,8 +565,8 @@ bool rns_plan(RnsParams* p) {
         return false;
     p->x_plane = x_plane;
     p->w_plane = w_plane;
-    // With one size of tile for all moduli: the less modelled time, in microseconds, by which the caller's rule decides too.
-    // A step is a tap of a slice.  The chip takes 256 of the large tile's
+    // With one size of tile for all moduli: the less modelled time, in microseconds, by which the caller's rule decides
+    // (measured before the shares below, which only shorten it).  A step is a tap of a slice.  The chip takes 256 of the large tile's
     // blocks at a time and 512 of the small one's; a part of the time goes with the rounds and a part with the blocks (a
     // compute unit with one small block runs it faster).  Strided layers leave half of every line they gather unused.
     // The residues that are read once (those of a matrix, of a filter) come on top.  Small against large tile, whole
@@ -592,12 +592,41 @@ bool rns_plan(RnsParams* p) {
         p->tile = t.edge;
     }
     p->product_us = best;
+    // Which moduli run on the large tile and which on the small one.  The large tile asks half as much of the L1 (half
+    // of its 64 bytes a clock, where the small tile takes all), but its rounds are the coarser ones, so whole rounds of it go first
+    // and the moduli that would leave its last round partly empty run on the small tile: the 3x3 layer 16 x 16 x 256 -> 256 at
+    // batch 32, 191 us with five rounds of the small tile alone (4.5 of work), 179 with two rounds of the large one (16
+    // moduli) and half a round of the other.  Modelled as above, and a last round of at most one small block per
+    // compute unit takes 0.6 of a full one.  Coefficients: least squares over 8000 whole calls, 2013 shapes (products of M, N 100 .. 8192,
+    // K 128 .. 8192; layers of 1 .. 64 images of 4 x 4 .. 112 x 112, 32 .. 1024 channels, windows of 1, 3, 5, strides of 1 and 2) with four
+    // shares of the moduli each: nine calls in ten within 14 %; the share chosen is within 2 % of the best one measured for
+    // nine shapes in ten, 13 % at worst.
+    struct Split { double round_step, block_step, fixed, per_mb; };
+    static const Split splits[3][2] = {{{0.714, 0.715, 8.2, 0.0}, {0.300, 0.637, 2.9, 0.033}},
+                                       {{0.932, 0.208, 8.2, 0.0}, {0.527, 0.204, 3.7, 0.0}},
+                                       {{0.872, 0.384, 8.1, 0.053}, {0.443, 0.465, 4.05, 0.020}}};
     auto set = [&](RnsPart& part, int edge, int first, int count) {
         part.tiles_m = (int)((p->M + (int64_t)edge - 1) / edge);
         part.tiles_n = (int)((p->N + (int64_t)edge - 1) / edge);
         part.first = first; part.count = count;
     };
-    const int best_large = p->tile == 256 ? p->nmod : 0;
+    auto cost = [&](const RnsPart& part, const Split& t, int slots) {
+        if (part.count == 0) return 0.0;
+        const int64_t blocks = (int64_t)part.tiles_m * part.tiles_n * part.count, rounds = (blocks + slots - 1) / slots;
+        const bool half = slots == 512 && blocks % 512 != 0 && blocks % 512 <= 256;
+        return steps * (((double)rounds - (half ? 0.4 : 0.0)) * t.round_step + (double)blocks / slots * t.block_step) +
+               (double)rounds * t.fixed + once_mb / p->nmod * part.count * t.per_mb;
+    };
+    int best_large = 0;
+    best = 0.0;
+    for (int large = 0; large <= p->nmod; ++large) {
+        set(p->large, 256, 0, large);
+        set(p->small, 128, large, p->nmod - large);
+        const double us = cost(p->large, splits[kind][0], 256) + cost(p->small, splits[kind][1], 512);
+        if (large > 0 && us >= best) continue;
+        best = us;
+        best_large = large;
+    }
     set(p->large, 256, 0, best_large);
     set(p->small, 128, best_large, p->nmod - best_large);
     for (RnsPart* part : {&p->large, &p->small}) {

@@ -21,13 +21,16 @@ int main(int argc, char** argv) {
         if (!strcmp(argv[1], "prf")) {
             const cg::PrfSplit s = cg::prf_split((uint64_t)a[0], (size_t)a[1]);
             printf("%llu %u %u\n", (unsigned long long)s.blocks, s.waves, s.per_wg);
-        } else if (!strcmp(argv[1], "residues")) {   // M N words x_rows gathered kh kw stride_h stride_w
+        } else if (!strncmp(argv[1], "residue", 7)) {   // M N words x_rows gathered kh kw stride_h stride_w
             cg::RnsParams p = {};
             p.M = (int)a[0]; p.N = (int)a[1]; p.words = (int)a[2]; p.x_rows = (int)a[3]; p.conv = (int)a[4];
             p.kh = (int)a[5]; p.kw = (int)a[6]; p.sh = (int)a[7]; p.sw = (int)a[8];
             p.Ho = p.Wo = 1;
             const bool fits = cg::rns_plan(&p);
-            printf("%d %d %llu\n", fits ? p.tile : 0, p.nmod, fits ? (unsigned long long)cg::rns_workspace_bytes(p) : 0ull);
+            if (!strcmp(argv[1], "residue_shares"))   // moduli on the large tile, on the small one, and the first of each
+                printf("%d %d %d %d %d\n", p.large.count, p.small.count, p.large.first, p.small.first, p.nmod);
+            else
+                printf("%d %d %llu\n", fits ? p.tile : 0, p.nmod, fits ? (unsigned long long)cg::rns_workspace_bytes(p) : 0ull);
         } else {   // small: M N K accumulate
             cg::GemmParams p = {};
             p.M = (int)a[0]; p.N = (int)a[1]; p.K = p.lda = (int)a[2]; p.z_add = (int)a[3];
@@ -113,6 +116,18 @@ def test_the_residue_tests_reach_every_instantiation(rules):
         assert need == nbytes, row   # the route is taken: its bytes are more than the digit planes'
         seen.add((tile, nmod, row[4]))
     assert seen == {(tile, nmod, gathered) for tile in (128, 256) for nmod in (18, 19) for gathered in (0, 1)}
+
+
+def test_every_modulus_runs_on_one_tile_and_the_residue_tests_reach_all_shares(rules):
+    """All moduli on the large tile, all on the small one, and both sizes in one call, of rows and of patches."""
+    from tests import test_gpu_residue as t
+    layers = [(xs, ws, (s, s), (p, p)) for xs, ws, s, p in t.CONVS] + t.GATHERS
+    rows = [(M, N, K, M, 0, 1, 1, 1, 1) for M, N, K in t.SHAPES + t.SMALL_TILE_SHAPES] + [_residue_row(*l) for l in layers]
+    seen = set()
+    for row, (large, small, first_large, first_small, nmod) in zip(rows, rules("residue_shares", rows)):
+        assert large >= 0 and small >= 0 and large + small == nmod and (first_large, first_small) == (0, large), row
+        seen.add((large > 0, small > 0, row[4]))
+    assert seen == {(large, small, gathered) for large, small in ((True, False), (False, True), (True, True)) for gathered in (0, 1)}
 
 
 # Taken or not, and whole calls in microseconds without residues and with them on either tile (256, 128).

@@ -63,6 +63,15 @@ def test_matmul(cg, ro, wl, M, N, K):
     assert np.array_equal(cg.to_host(got[rows]), want)
 
 
+# every modulus on the small tile (see test_every_modulus_runs_on_one_tile...)
+SMALL_TILE_SHAPES = [(1077, 1133, 1913)]
+
+
+@pytest.mark.parametrize("M,N,K", SMALL_TILE_SHAPES)
+def test_matmul_on_the_small_tile_alone(cg, ro, wl, M, N, K):
+    test_matmul(cg, ro, wl, M, N, K)
+
+
 @pytest.mark.parametrize("x_word,w_word", [(0x7F7F7F7F7F7F7F80, 0x7F7F7F7F7F7F7F80), (0x7F7F7F7F7F7F7F80, 0x7F7F7F7F7F7F7F7F),
                                            (0x8080808080808080, 0x8080808080808080), (0x7F7F7F7F7F7F7F7F, 0x8080808080808080),
                                            (0x7F7F7F7F7F7F7F7F, 0x7F7F7F7F7F7F7F7F), (0x8000000000000000, 0x8000000000000000),
