@@ -1623,9 +1623,25 @@ hipError_t launch_share_gemm_group1(const GemmParams& p, int amode, int bmode, h
 }
 #endif
 #if CG_G2
+// Few rows against a transposed right operand: both kernels' modelled times, this file's in the terms of its launcher (slices in
+// rounds, rounds, megabytes of right operand; over the same 692 shapes nine in ten within 13 %).  The calls together 17.6 ms -> 13.96,
+// 13.94 with the better kernel each time; one of the 411 taken is slower, by 10 %.
+static bool few_rows_pay(const GemmParams& p) {
+    const double few = share_gemm_rows_t_us(p);
+    if (few == 0.0) return false;
+    const int64_t rows = (p.M + (int64_t)127) / 128, tiles = rows * ((p.N + (int64_t)63) / 64);
+    const int nk = (p.K + 31) / 32, ks = choose_ksplit(tiles, nk);
+    const double tiled = 2.42 * classic_cost(tiles, nk, ks) + (ks > 1 ? 0.4 : 0.0) +
+                         1.92 * (double)((tiles * ks + ROUND_BLOCKS - 1) / ROUND_BLOCKS) +
+                         0.124 * 16.0e-6 * (double)rows * (double)p.N * (double)p.K;
+    return few < 0.95 * tiled;
+}
+
 hipError_t launch_share_gemm_group2(const GemmParams& p, int amode, int bmode, hipStream_t stream, bool* found) {
     typedef DefaultStepTile T;
     *found = true;
+    if (amode == A_TRANS && bmode == B_TRANS && share_gemm_outer_applies(p)) return launch_share_gemm_outer(p, stream);
+    if (amode == A_LINEAR_VEC && bmode == B_TRANS && few_rows_pay(p)) return launch_share_gemm_rows_t(p, stream);
     CG_CASE(A_LINEAR_VEC, B_TRANS);
     CG_CASE(A_LINEAR_SCALAR, B_TRANS);
     CG_CASE(A_TRANS, B_VEC);

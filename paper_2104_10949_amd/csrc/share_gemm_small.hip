@@ -194,6 +194,241 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void share_gemm_small_kernel(cons
     }
 }
 
+// ---- products whose right operand is stored transposed, [K, N] with N contiguous (gradients of a fully connected layer) --------
+// A lane of the matrix instruction wants sixteen consecutive k of one column.  In this storage sixteen lanes on
+// neighbouring pairs of columns read 256 contiguous bytes of every k, so the words go straight from memory to the lane that
+// splits them: no LDS, no exchange.  The three terms are taken as (x_a + x_b)*w_a + x_a*w_b here: a lane then loads one share of the right
+// operand, and the sum is formed on the left, which is split once per wave.
+
+// Sixteen words of a column (the first or the second of a lane's pairs) -> eight digit registers
+template <int SECOND>
+__device__ __forceinline__ void split_column(const u4 (&v)[16], v4i (&d)[8]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        u32 lo[4], hi[4], dl[4], dh[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            lo[t] = SECOND ? v[4 * j + t].z : v[4 * j + t].x;
+            hi[t] = SECOND ? v[4 * j + t].w : v[4 * j + t].y;
+            recode(lo[t], hi[t]);
+        }
+        transpose4(lo[0], lo[1], lo[2], lo[3], dl);
+        transpose4(hi[0], hi[1], hi[2], hi[3], dh);
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            d[l][j] = (int)dl[l];
+            d[4 + l][j] = (int)dh[l];
+        }
+    }
+}
+
+// The right operand of one lane: a pair of columns of the share that its half-wave takes, words k = 32 ks + 16 (g & 1) + j,
+// j = 0 .. 15.  Rows past K are replaced by the last one: the left operand's words there are zeros.
+struct PairColumn {
+    const u64* base;   // the pair in row 0
+    __device__ __forceinline__ void load(u4 (&v)[16], int ks, int g, u32 K, u32 N) const {
+        const u32 want = 32u * (u32)ks + 16u * (u32)(g & 1), row = want < K ? want : K - 1u;
+        u32 last = K - 1u - row;
+        asm volatile("" : "+v"(last));   // (the sixteen offsets are computed here and not kept in registers across a loop)
+        const char* const p = reinterpret_cast<const char*>(base + (u64)row * N);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const u32 r = (u32)j < last ? (u32)j : last;
+            v[j] = *reinterpret_cast<const u4*>(p + (u64)(u32)__umul24(r, N * 8u));
+        }
+    }
+};
+
+// element i of the four that a lane holds of a block
+__device__ __forceinline__ u64 fold_element(const v4i (&acc)[8], int i) {
+    u64 v = (u64)(int64_t)acc[0][i];
+    v += (u64)(int64_t)acc[1][i] << 8;
+    v += (u64)(int64_t)acc[2][i] << 16;
+    v += (u64)(int64_t)acc[3][i] << 24;
+    const u32 hi = (u32)acc[4][i] + ((u32)acc[5][i] << 8) + ((u32)acc[6][i] << 16) + ((u32)acc[7][i] << 24);
+    return v + ((u64)hi << 32);
+}
+
+__device__ __forceinline__ void multiply36(const v4i (&a)[8], const v4i (&b)[8], v4i (&acc)[8]) {
+#pragma unroll
+    for (int l = 0; l < 8; ++l)
+#pragma unroll
+        for (int m = 0; m + l < 8; ++m)
+            acc[l + m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[l], b[m], acc[l + m], 0, 0, 0);
+}
+
+// Both operands transposed and K <= 32, one slice: the weight gradient at batches of up to 32.  A wave splits 32 rows of the
+// left operand once and walks along `per` blocks of 32 columns; nothing is shared between waves, so a block is one wave and
+// short calls spread over all compute units (eight waves to a block: 7.9 us instead of 4.7 at 64 x 512 x 32, a compute unit's loads
+// one after the other).  Block q of 16 rows holds rows 2 r + q, block c of 16 columns columns 2 r + c: a lane's pairs in memory.
+// Bound: the vector ALU (split and fold, 690 instructions beside 144 matrix instructions) and, on long outputs, the loads' latency.
+__global__ __launch_bounds__(64, 2) void share_gemm_outer_kernel(const GemmParams p, u32 runs, u32 per) {
+    const int lane = threadIdx.x, r16 = lane & 15, g = lane >> 4;
+    const bool low = g < 2;
+    const u32 rows = blockIdx.x / runs, c0 = (blockIdx.x - rows * runs) * per * 32u;
+    const u32 K = (u32)p.K, N = (u32)p.N, M = (u32)p.M, m0 = rows * 32u;
+    if (m0 >= M || c0 >= N) return;
+    const u32 blocks = (N - c0 + 31u) / 32u < per ? (N - c0 + 31u) / 32u : per;
+    auto column = [&](u32 b) { const u32 n = c0 + 32u * b + 2u * (u32)r16; return n < N ? n : N - 2u; };   // (N is even)
+    PairColumn right;
+    v4i ad[2][8];
+    u4 w[16];
+    {
+        const __amdgpu_buffer_rsrc_t rxa = make_rsrc(p.x_a, K * M * 8u), rxb = make_rsrc(p.x_b, K * M * 8u);
+        const u32 m = m0 + 2u * (u32)r16 < M ? m0 + 2u * (u32)r16 : M - 2u, off = ((u32)(16 * (g & 1)) * M + m) * 8u;
+        u4 x[16], y[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            x[j] = __builtin_amdgcn_raw_buffer_load_b128(rxa, off + (u32)j * M * 8u, 0, 0);
+            y[j] = __builtin_amdgcn_raw_buffer_load_b128(rxb, low ? off + (u32)j * M * 8u : OOB, 0, 0);   // else zero
+        }
+        right.base = (low ? p.w_a : p.w_b) + column(0);
+        right.load(w, 0, g, K, N);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = add64x2(x[j], y[j]);
+        split_column<0>(x, ad[0]);
+        split_column<1>(x, ad[1]);
+    }
+    const u64 z_left = (u64)(M - m0) * N * 8u;
+    const __amdgpu_buffer_rsrc_t rz = make_rsrc(p.z + (u64)m0 * N, z_left > 0x7FFFFFFFull ? 0x7FFFFFFFu : (u32)z_left);
+    for (u32 b = 0; b < blocks; ++b) {
+        v4i bd[2][8];
+        split_column<0>(w, bd[0]);
+        split_column<1>(w, bd[1]);
+        const u32 n = c0 + 32u * b + 2u * (u32)r16;
+        if (b + 1 < blocks) {
+            right.base = (low ? p.w_a : p.w_b) + column(b + 1);
+            right.load(w, 0, g, K, N);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            u64 v[2][4];   // (one block's accumulators at a time: two do not fit beside the digits and the words on their way)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                v4i acc[8];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) acc[s] = v4i{0, 0, 0, 0};
+                multiply36(ad[q], bd[c], acc);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[c][i] = fold_element(acc, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {   // rows past M lie outside the view, columns past N are sent there
+                const u4 out = {(u32)v[0][i], (u32)(v[0][i] >> 32), (u32)v[1][i], (u32)(v[1][i] >> 32)};
+                const u32 off = ((u32)(2 * (4 * g + i) + q) * N + n) * 8u;
+                __builtin_amdgcn_raw_buffer_store_b128(out, rz, n < N ? off : OOB, 0, 0);
+            }
+        }
+    }
+}
+
+// Few rows on the left, row-major: the input gradient at small batch.  A block owns 16 RB rows x 32 columns of z, its four waves
+// (one per SIMD, 512 registers: the next slice's words arrive while this one is split and multiplied) share out the slices of K.
+// The left operand crosses a wave-private LDS buffer as in share_gemm_small_kernel.  Bound: memory (the right operand, read once
+// per 16 RB rows).  32 x 8192 x 512: 32.2 -> 22.3 us (67 MB of right operand, 13 us at 5 TB/s); with 16-column loads of 8 bytes
+// and w_a read for both terms 24.5.
+template <int RB>
+__global__ __launch_bounds__(256, 1) void share_gemm_rows_t_kernel(const GemmParams p) {
+    __shared__ __attribute__((aligned(16))) char stage[4][RB * 2][16 * 256];
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+    const bool low = g < 2;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = blockIdx.x * 32, m0 = blockIdx.y * 16 * RB;
+    const u32 K = (u32)p.K, N = (u32)p.N;
+    const int nk = (int)((K + 31) >> 5);
+    const int lp = lane & 15, lr = lane >> 4;
+    auto swizzle = [](int r) { return r ^ (((r >> 2) ^ (r >> 3)) & 1) << 3; };
+    const __amdgpu_buffer_rsrc_t rs_xa = make_rsrc(p.x_a, (u32)((u64)p.M * K * 8u)), rs_xb = make_rsrc(p.x_b, (u32)((u64)p.M * K * 8u));
+    u32 a_off[RB][4];
+    int st_off[4], rd_off[8];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = 4 * j + lr;
+#pragma unroll
+        for (int q = 0; q < RB; ++q) a_off[q][j] = (u32)(m0 + 16 * q + r < p.M ? m0 + 16 * q + r : p.M - 1) * K * 8u + 16u * lp;
+        st_off[j] = r * 256 + ((lp ^ swizzle(r)) << 4);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) rd_off[i] = (g >> 1) * 4096 + r16 * 256 + (((8 * (g & 1) + i) ^ swizzle(r16)) << 4);
+    char* const my_stage = &stage[wave][0][0];
+
+    u4 rx[RB][2][4];
+    auto load_x = [&](int ks) {
+        const u32 at = (32u * (u32)ks + 2u * (u32)lp < K ? 0u : OOB) + 256u * (u32)ks;
+#pragma unroll
+        for (int q = 0; q < RB; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                rx[q][0][j] = __builtin_amdgcn_raw_buffer_load_b128(rs_xa, a_off[q][j] + at, 0, 0);
+                rx[q][1][j] = __builtin_amdgcn_raw_buffer_load_b128(rs_xb, a_off[q][j] + at, 0, 0);
+            }
+    };
+    u4 w[16];
+    const u32 pair = (u32)(n0 + 2 * r16 < p.N ? n0 + 2 * r16 : p.N - 2);   // (N is even)
+    const PairColumn right = {(low ? p.w_a : p.w_b) + pair};
+    v4i acc[RB][2][8];
+#pragma unroll
+    for (int q = 0; q < RB; ++q)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) acc[q][c][s] = v4i{0, 0, 0, 0};
+    int ks = wave;
+    if (ks < nk) {
+        right.load(w, ks, g, K, N);
+        load_x(ks);
+    }
+    while (ks < nk) {   // uniform over the wave
+        const int next = ks + 4;   // past the end: nothing is read
+        v4i ad[RB][8], bd[2][8];
+        split_column<0>(w, bd[0]);
+        split_column<1>(w, bd[1]);
+        if (next < nk) right.load(w, next, g, K, N);
+#pragma unroll
+        for (int q = 0; q < RB; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                *reinterpret_cast<u4*>(my_stage + 8192 * q + st_off[j]) = add64x2(rx[q][0][j], rx[q][1][j]);
+                *reinterpret_cast<u4*>(my_stage + 8192 * q + 4096 + st_off[j]) = rx[q][0][j];
+            }
+        if (next < nk) load_x(next);
+        __builtin_amdgcn_wave_barrier();   // (compiler only) the reads below follow the writes above
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            u4 raw[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) raw[i] = *reinterpret_cast<const u4*>(my_stage + 8192 * q + rd_off[i]);
+            split16(raw, ad[q]);
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int q = 0; q < RB; ++q) multiply36(ad[q], bd[c], acc[q][c]);
+        ks = next;
+    }
+    // the waves' partial sums meet in LDS, [wave][row][32 columns]
+    __syncthreads();
+    u64* const part = reinterpret_cast<u64*>(&stage[0][0][0]);
+#pragma unroll
+    for (int q = 0; q < RB; ++q)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[(wave * 16 * RB + 16 * q + 4 * g + i) * 32 + 2 * r16 + c] = fold_element(acc[q][c], i);
+    __syncthreads();
+    for (int e = tid; e < 16 * RB * 32; e += 256) {
+        const int row = m0 + e / 32, col = n0 + e % 32;
+        if (row < p.M && col < p.N) {
+            u64 v = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v += part[k * 16 * RB * 32 + e];
+            p.z[(u64)row * N + (u64)col] = v;
+        }
+    }
+}
+
 }  // namespace
 
 // Row-major operands with 16-byte loads (K even, 16-byte aligned bases), few blocks of z, and a K whose
@@ -228,6 +463,47 @@ hipError_t launch_share_gemm_small(const GemmParams& p, hipStream_t stream) {
         if (hipError_t e = launch_zero_words(p.z, (size_t)p.M * (size_t)p.N, stream)) return e;
     hipLaunchKernelGGL(share_gemm_small_kernel, dim3((unsigned)tiles_n, (unsigned)tiles_m, (unsigned)ksplit),
                        dim3(SMALL_WAVES * 64), 0, stream, p);
+    return hipGetLastError();
+}
+
+namespace {
+bool pairs_aligned(const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; }
+}  // namespace
+
+// 697 shapes of M 10 .. 4096, N 32 .. 16384, K 1 .. 32 against share_gemm_kernel, whole calls: 0.61 - 0.83 of its time with at most
+// one wave per SIMD (7.3 -> 4.6 us), 0.64 - 1.04 where the tiled kernel needs more than one round of its 128 x 64 tiles (512 x 8192 x 32 17.3 ->
+// 14.1 us, 4096 x 4096 x 32 57 -> 49); in between the waves share a SIMD while the tiles still run in one round (1.02, 1.07 at worst).
+bool share_gemm_outer_applies(const GemmParams& p) {
+    if (p.K > 32 || p.z_add || p.N % 2 != 0 || p.M % 2 != 0 || p.N >= (1 << 21) || p.M >= (1 << 21)) return false;
+    if (!pairs_aligned(p.w_a, p.w_b) || !pairs_aligned(p.x_a, p.x_b) || ((uintptr_t)p.z & 15) != 0) return false;
+    const int64_t units = ((int64_t)p.M + 31) / 32 * (((int64_t)p.N + 31) / 32), tiles = ((int64_t)p.M + 127) / 128 * (((int64_t)p.N + 63) / 64);
+    return units <= 1024 || tiles > 256;
+}
+
+hipError_t launch_share_gemm_outer(const GemmParams& p, hipStream_t stream) {
+    const int64_t row_tiles = (p.M + (int64_t)31) / 32, cols = (p.N + (int64_t)31) / 32;
+    int64_t per = (row_tiles * cols + 2047) / 2048;
+    if (per > cols) per = cols;
+    const int64_t runs = (cols + per - 1) / per, waves = row_tiles * runs;
+    hipLaunchKernelGGL(share_gemm_outer_kernel, dim3((unsigned)waves), dim3(64), 0, stream, p, (u32)runs, (u32)per);
+    return hipGetLastError();
+}
+
+// Modelled time in microseconds, or 0 where the kernel does not apply: turns of a wave times rounds of the chip, and the right
+// operand once per group of rows (fitted over 692 shapes of M 2 .. 300, N 10 .. 16384, K 8 .. 8192, nine in ten within 8 %).
+double share_gemm_rows_t_us(const GemmParams& p) {
+    const int64_t nk = (p.K + (int64_t)31) / 32;
+    if (p.lda != p.K || p.z_add || p.M > 512 || nk > 511 * 4 || p.N % 2 != 0 || p.N >= (1 << 21) || !pairs_aligned(p.w_a, p.w_b)) return 0.0;
+    const int64_t groups = p.M <= 16 ? 1 : (p.M + 31) / 32, blocks = (p.N + (int64_t)31) / 32 * groups;
+    const double turns = (double)((nk + 3) / 4), rounds = (double)((blocks + 255) / 256);
+    const double mb = 16.0e-6 * (double)groups * (double)p.N * (double)p.K;
+    return p.M <= 16 ? 1.1 + rounds * (1.87 * turns + 1.28) + 0.080 * mb : 1.2 + rounds * (2.69 * turns + 2.27) + 0.083 * mb;
+}
+
+hipError_t launch_share_gemm_rows_t(const GemmParams& p, hipStream_t stream) {
+    const dim3 grid((unsigned)((p.N + (int64_t)31) / 32), (unsigned)(p.M <= 16 ? 1 : (p.M + 31) / 32));
+    if (p.M <= 16) hipLaunchKernelGGL((share_gemm_rows_t_kernel<1>), grid, dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL((share_gemm_rows_t_kernel<2>), grid, dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
