@@ -306,6 +306,19 @@ CG_API cg_status cg_share_conv2d_dgrad(const uint64_t *g_i, const uint64_t *g_ip
                                 const uint64_t *w_i, const uint64_t *w_ip1,
                                 uint64_t *dx_i, const cg_conv2d_desc *desc, void *stream);
 
+/*
+ * The input gradient with scratch memory (256-byte aligned where it comes from an
+ * allocator; 16 bytes are enough): large unit-stride layers run through residues, as
+ * cg_share_conv2d_ws.  workspace_bytes says how much that takes, 0 where scratch
+ * memory is of no use.  With less, or none, the call is cg_share_conv2d_dgrad.
+ */
+CG_API size_t cg_share_conv2d_dgrad_workspace_bytes(const cg_conv2d_desc *desc);
+
+CG_API cg_status cg_share_conv2d_dgrad_ws(const uint64_t *g_i, const uint64_t *g_ip1,
+                                const uint64_t *w_i, const uint64_t *w_ip1,
+                                uint64_t *dx_i, const cg_conv2d_desc *desc,
+                                void *workspace, size_t workspace_bytes, void *stream);
+
 CG_API cg_status cg_share_conv2d_wgrad(const uint64_t *g_i, const uint64_t *g_ip1,
                                 const uint64_t *x_i, const uint64_t *x_ip1,
                                 uint64_t *dw_i, const cg_conv2d_desc *desc, void *stream);

@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libcg.so")
 EXPORTS = ("cg_status_string", "cg_version", "cg_share_matmul", "cg_share_conv2d", "cg_share_add",
            "cg_share_mul_public", "cg_share_add_public", "cg_reconstruct",
            "cg_share_matmul_ws", "cg_share_conv2d_ws", "cg_zero_share", "cg_reshare", "cg_share_matmul_t",
-           "cg_share_mul", "cg_share_sum_pool2d", "cg_share_conv2d_dgrad", "cg_share_conv2d_wgrad",
+           "cg_share_mul", "cg_share_sum_pool2d", "cg_share_conv2d_dgrad", "cg_share_conv2d_dgrad_ws", "cg_share_conv2d_wgrad",
            "cg_trunc1_local", "cg_prf_words", "cg_bshare_xor", "cg_bshare_and", "cg_bshare_prefix_stage",
            "cg_bzero_share", "cg_breshare", "cg_share_bias_add", "cg_share_col_sum",
            "cg_bit_transpose64", "cg_bshare_carry_level", "cg_bits_unpack", "cg_bshare_csa", "cg_bshare_half_adder",
@@ -30,8 +30,9 @@ EXPORTS = ("cg_status_string", "cg_version", "cg_share_matmul", "cg_share_conv2d
            "cg_share_matmul_prefers_workspace", "cg_share_conv2d_prefers_workspace",
            "cg_share_matmul_prefers_digit_workspace", "cg_share_conv2d_prefers_digit_workspace",
            "cg_share_matmul_workspace_bytes", "cg_share_conv2d_workspace_bytes",
-           "cg_share_matmul_digit_workspace_bytes", "cg_share_conv2d_digit_workspace_bytes")
-SIZE_EXPORTS = 4      # the last entries return size_t, the first two a string and an int, the rest cg_status
+           "cg_share_matmul_digit_workspace_bytes", "cg_share_conv2d_digit_workspace_bytes",
+           "cg_share_conv2d_dgrad_workspace_bytes")
+SIZE_EXPORTS = 5      # the last entries return size_t, the first two a string and an int, the rest cg_status
 
 
 class ConvDesc(ctypes.Structure):
@@ -105,6 +106,8 @@ def lib() -> ctypes.CDLL:
         L.cg_trunc1_local.argtypes = [vp, vp, key, key, u64, u64, ctypes.c_int, key, u64, vp, sz, vp]
         L.cg_prf_words.argtypes = [key, u64, u64, vp, sz, vp]
         L.cg_share_conv2d_dgrad.argtypes = [vp] * 5 + [ctypes.POINTER(ConvDesc), vp]
+        L.cg_share_conv2d_dgrad_ws.argtypes = [vp] * 5 + [ctypes.POINTER(ConvDesc), vp, sz, vp]
+        L.cg_share_conv2d_dgrad_workspace_bytes.argtypes = [ctypes.POINTER(ConvDesc)]
         L.cg_share_conv2d_wgrad.argtypes = [vp] * 5 + [ctypes.POINTER(ConvDesc), vp]
         for name in EXPORTS[2:-SIZE_EXPORTS]:
             getattr(L, name).restype = ctypes.c_int
@@ -248,6 +251,23 @@ def _ws(workspace) -> Tuple[int, int]:
     return workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
+SCRATCH_LIMIT = 4 << 30   # bytes: a call that would take more runs without
+
+
+def _scratch(nbytes: int, device, stream) -> Optional[torch.Tensor]:
+    """Scratch memory of one call, from torch's caching allocator: it belongs to the current stream and goes back to the
+    allocator when the call returns, for later work of the same stream.  None, and the route without scratch memory, where the
+    call asks for none, runs on a stream that it names (whose order the allocator would not know), is being captured (the
+    graph would keep the memory), or where the memory is not to be had."""
+    if nbytes == 0 or nbytes > SCRATCH_LIMIT or stream is not None or device.index != torch.cuda.current_device() or \
+            torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def cg_share_matmul_ws(x_i, x_ip1, y_i, y_ip1, workspace, z_i=None, stream=None) -> torch.Tensor:
     """cg_share_matmul with caller-supplied scratch memory (any contiguous GPU tensor)."""
     M, K = x_i.shape
@@ -362,7 +382,8 @@ def cg_share_conv2d_ws(x_i, x_ip1, w_i, w_ip1, workspace, stride=(1, 1), pad=(0,
 def cg_share_conv2d_dgrad(g_i, g_ip1, w_i, w_ip1, x_shape, stride=(1, 1), pad=(0, 0), dx_i=None,
                           stream=None) -> torch.Tensor:
     """Party-local input gradient of a convolution layer; g NHWC [B,Ho,Wo,Cout], w [Cout,kh,kw,Cin],
-    x_shape = (B,H,W,Cin) of the layer input, result NHWC of that shape."""
+    x_shape = (B,H,W,Cin) of the layer input, result NHWC of that shape.  Large layers take scratch memory from torch's
+    allocator for the time of the call (see _scratch)."""
     B, H, W, Cin = (int(v) for v in x_shape)
     Cout, kh, kw, Cin2 = w_i.shape
     if g_ip1.shape != g_i.shape or w_ip1.shape != w_i.shape or Cin2 != Cin:
@@ -374,8 +395,37 @@ def cg_share_conv2d_dgrad(g_i, g_ip1, w_i, w_ip1, x_shape, stride=(1, 1), pad=(0
         dx_i = torch.empty((B, H, W, Cin), dtype=torch.int64, device=g_i.device)
     elif tuple(dx_i.shape) != (B, H, W, Cin):
         raise ValueError("output shape does not match")
-    _check(lib().cg_share_conv2d_dgrad(_ptr(g_i), _ptr(g_ip1), _ptr(w_i), _ptr(w_ip1), _ptr(dx_i),
-                                       ctypes.byref(d), _stream(stream)), "cg_share_conv2d_dgrad")
+    ptrs = _ptr(g_i), _ptr(g_ip1), _ptr(w_i), _ptr(w_ip1), _ptr(dx_i)
+    ws = _scratch(lib().cg_share_conv2d_dgrad_workspace_bytes(ctypes.byref(d)), g_i.device, stream)
+    if ws is None:
+        _check(lib().cg_share_conv2d_dgrad(*ptrs, ctypes.byref(d), _stream(stream)), "cg_share_conv2d_dgrad")
+    else:
+        _check(lib().cg_share_conv2d_dgrad_ws(*ptrs, ctypes.byref(d), ws.data_ptr(), ws.numel(), _stream(stream)),
+               "cg_share_conv2d_dgrad")
+    return dx_i
+
+
+def cg_share_conv2d_dgrad_workspace_bytes(x_shape, w_shape, stride=(1, 1), pad=(0, 0)) -> int:
+    return int(lib().cg_share_conv2d_dgrad_workspace_bytes(_conv_desc(x_shape, w_shape, stride, pad)))
+
+
+def cg_share_conv2d_dgrad_ws(g_i, g_ip1, w_i, w_ip1, x_shape, workspace, stride=(1, 1), pad=(0, 0), dx_i=None,
+                             stream=None) -> torch.Tensor:
+    """cg_share_conv2d_dgrad with the caller's scratch memory (or none: the route without it)."""
+    B, H, W, Cin = (int(v) for v in x_shape)
+    Cout, kh, kw, Cin2 = w_i.shape
+    if g_ip1.shape != g_i.shape or w_ip1.shape != w_i.shape or Cin2 != Cin:
+        raise ValueError("operand shapes do not match")
+    if tuple(g_i.shape) != conv_out_shape((B, H, W, Cin), w_i.shape, stride, pad):
+        raise ValueError("gradient shape does not match the layer")
+    d = ConvDesc(B, H, W, Cin, Cout, kh, kw, stride[0], stride[1], pad[0], pad[1])
+    if dx_i is None:
+        dx_i = torch.empty((B, H, W, Cin), dtype=torch.int64, device=g_i.device)
+    elif tuple(dx_i.shape) != (B, H, W, Cin):
+        raise ValueError("output shape does not match")
+    wp, wb = _ws(workspace)
+    _check(lib().cg_share_conv2d_dgrad_ws(_ptr(g_i), _ptr(g_ip1), _ptr(w_i), _ptr(w_ip1), _ptr(dx_i), ctypes.byref(d), wp, wb,
+                                          _stream(stream)), "cg_share_conv2d_dgrad_ws")
     return dx_i
 
 

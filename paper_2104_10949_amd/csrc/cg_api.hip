@@ -639,6 +639,7 @@ struct Plan {
     u64 xp_bytes, wp_bytes;  // bytes of one left / right plane tensor
     u64 x_bytes, w_bytes, z_bytes;
     bool rns_ok;      // the residue route applies as far as the operands' form goes
+    bool rns_flip;    // ... with a filter as the right operand of its input gradient
 };
 
 // Residue route of a plan.
@@ -685,6 +686,7 @@ Residues plan_residues(const Plan& pl) {
     r.words = (int)words; r.x_rows = (int)x_rows; r.conv = conv;
     r.H = p.H; r.W = p.W; r.Ho = p.Ho; r.Wo = p.Wo; r.sh = p.sh; r.sw = p.sw; r.ph = p.ph; r.pw = p.pw;
     r.kh = conv ? p.kh : 1; r.kw = conv ? p.kw : 1;
+    r.flip = pl.rns_flip;
     if (!cg::rns_plan(&r)) return res;
     // Both routes in seconds, from measurements on MI355X.  Plain kernel: 144 operations per (m, n, k) of its 128 x 64
     // tiles at 2.6e15 a second, 1.2 times that with 8-byte loads, 1.3 times with 8-byte gathers (1.2 to 1.8 over 650 layers,
@@ -696,14 +698,19 @@ Residues plan_residues(const Plan& pl) {
     // those of the fit, none that is taken is more than 2 % slower than without residues.
     const double up_m = (double)((p.M + (int64_t)127) / 128 * 128), up_n = (double)((p.N + (int64_t)63) / 64 * 64);
     const double inside = conv ? (p.H < p.kh ? (double)p.H / p.kh : 1.0) * (p.W < p.kw ? (double)p.W / p.kw : 1.0) : 1.0;
-    const double loads = pl.planes_ok ? 1.0 : !conv ? 1.2 : inside < 0.9 ? 0.85 + 0.5 * inside : 1.3;
+    // (an input gradient reads its filter across the rows: 1.1 of the forward layer's time with the gather of 32 channels)
+    const bool wide_loads = pl.amode == cg::A_CONV_C32 || pl.amode == cg::A_LINEAR_VEC;
+    const double loads = pl.rns_flip && wide_loads ? 1.1 : pl.planes_ok ? 1.0 : !conv ? 1.2 : inside < 0.9 ? 0.85 + 0.5 * inside : 1.3;
     const double work = 144.0 * up_m * up_n * (double)p.K / 2.6e15 * loads;
     double best = work + 8.0e-6;
     if (up_m * up_n < 256.0 * 128.0 * 64.0) best += work < 8.0e-6 ? work : 8.0e-6;
     if (planes_pay(pl)) best *= 0.93;
     const double pairs = ((double)r.x_rows + (double)p.N * r.kh * r.kw) * r.slices * 64.0;
     const double outputs = (double)round_up((u64)r.M, (u64)r.tile) * (double)round_up((u64)r.N, (u64)r.tile);
-    const double rns = pairs * (16.0 + 2.0 * r.nmod) / (words % 2 == 0 ? 4.9e12 : 4.0e12) +
+    // an input gradient's filter is converted across its rows, at 0.6 of the rate, and short calls need more of a margin (1954
+    // random unit-stride layers that are taken: 1621 -> 916 ms, one of them slower, by 7 %; without these terms 69 of 3043)
+    const double flip = pl.rns_flip ? 0.6 * (double)p.N * r.kh * r.kw * r.slices * 64.0 * (16.0 + 2.0 * r.nmod) / 4.9e12 + 6.0e-6 : 0.0;
+    const double rns = flip + pairs * (16.0 + 2.0 * r.nmod) / (words % 2 == 0 ? 4.9e12 : 4.0e12) +
                        outputs * (2.0 * r.nmod + 8.0) / 8.5e12 + 1.0e-6 * r.product_us + 12.0e-6;
     res.pay = rns < (conv && (p.sh > 1 || p.sw > 1) ? 0.90 : 0.92) * best;
     return res;
@@ -860,13 +867,14 @@ cg_status plan_conv2d(const uint64_t* x_i, const uint64_t* x_ip1, const uint64_t
 // strided) with padding k - 1 - pad, and the right operand is the filter with its taps
 // reversed and its channel roles exchanged, addressed in place.
 cg_status plan_conv2d_dgrad(const uint64_t* g_i, const uint64_t* g_ip1, const uint64_t* w_i, const uint64_t* w_ip1,
-                            uint64_t* dx_i, const cg_conv2d_desc* d, Plan* out) {
-    if (!d || !g_i || !g_ip1 || !w_i || !w_ip1 || !dx_i) return CG_ERR_NULL;
+                            uint64_t* dx_i, const cg_conv2d_desc* d, bool check_ptrs_too, Plan* out) {
+    if (!d || (check_ptrs_too && (!g_i || !g_ip1 || !w_i || !w_ip1 || !dx_i))) return CG_ERR_NULL;
     ConvDims cd;
     if (cg_status st = conv_dims(d, &cd)) return st;
-    if (cg_status st = check_product_ptrs(g_i, g_ip1, w_i, w_ip1, dx_i, (u64)cd.z_el * 8, (u64)cd.w_el * 8,
-                                          (u64)cd.x_el * 8))
-        return st;
+    if (check_ptrs_too)
+        if (cg_status st = check_product_ptrs(g_i, g_ip1, w_i, w_ip1, dx_i, (u64)cd.z_el * 8, (u64)cd.w_el * 8,
+                                              (u64)cd.x_el * 8))
+            return st;
     const int64_t taps = d->kh * d->kw;
     const int64_t Kg = taps * d->Cout;                 // contraction length
     const int64_t Mg = d->B * d->H * d->W;             // one row per input pixel
@@ -877,8 +885,11 @@ cg_status plan_conv2d_dgrad(const uint64_t* g_i, const uint64_t* g_ip1, const ui
         return CG_ERR_UNSUPPORTED;
 
     const bool pointwise = taps == 1 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 0 && d->pad_w == 0;
-    if (pointwise)  // dX [B*H*W, Cin] = G [B*H*W, Cout] x W, the filter [Cout, Cin] being the right operand stored transposed
-        return plan_matmul(g_i, g_ip1, w_i, w_ip1, dx_i, Mg, d->Cin, d->Cout, true, out, false, true);
+    if (pointwise) {  // dX [B*H*W, Cin] = G [B*H*W, Cout] x W, the filter [Cout, Cin] being the right operand stored transposed
+        if (cg_status st = plan_matmul(g_i, g_ip1, w_i, w_ip1, dx_i, Mg, d->Cin, d->Cout, check_ptrs_too, out, false, true)) return st;
+        out->rns_ok = out->rns_flip = Kg <= MAX_ROW_WORDS;
+        return CG_OK;
+    }
 
     Plan pl = {};
     cg::GemmParams& p = pl.p;
@@ -904,7 +915,7 @@ cg_status plan_conv2d_dgrad(const uint64_t* g_i, const uint64_t* g_ip1, const ui
 
     const void* in[4] = {g_i, g_ip1, w_i, w_ip1};
     const bool strided = d->stride_h != 1 || d->stride_w != 1;
-    const bool c32 = !strided && all_aligned16(in, 4) && d->Cout % 32 == 0 && taps * d->Cin <= ((int64_t)1 << 22) &&
+    const bool c32 = !strided && (!check_ptrs_too || all_aligned16(in, 4)) && d->Cout % 32 == 0 && taps * d->Cin <= ((int64_t)1 << 22) &&
                      taps <= cg::MAX_MASK_TAPS;
     if (c32) {
         pl.amode = cg::A_CONV_C32; pl.bmode = cg::B_FLIP_C32;
@@ -920,6 +931,10 @@ cg_status plan_conv2d_dgrad(const uint64_t* g_i, const uint64_t* g_ip1, const ui
         pl.bmode = cg::B_FLIP_GEN;
     }
     pl.x_bytes = (u64)cd.z_el * 8; pl.w_bytes = (u64)cd.w_el * 8; pl.z_bytes = (u64)cd.x_el * 8;
+    // unit stride: the same gather as a forward layer, of the gradient, and the filter converted as it is read here
+    pl.x_rows = d->B * cd.howo; pl.x_k = d->Cout;
+    pl.planes_conv = true;
+    pl.rns_ok = pl.rns_flip = !strided;
     *out = pl;
     return CG_OK;
 }
@@ -1091,17 +1106,24 @@ cg_status run_planes(Plan& pl, void* workspace, size_t workspace_bytes, void* st
     return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
 }
 
+// The residue route where it pays and the scratch memory holds it; *taken says whether it was.
+cg_status run_residues(const Plan& pl, void* workspace, size_t workspace_bytes, void* stream, bool* taken) {
+    *taken = false;
+    const Residues res = plan_residues(pl);
+    if (!res.pay || !workspace || !aligned(workspace, 16)) return CG_OK;
+    const u64 need = cg::rns_workspace_bytes(res.p);
+    if (workspace_bytes < need || workspace_overlaps(pl, workspace, need)) return CG_OK;
+    *taken = true;
+    const hipError_t e = cg::launch_share_gemm_rns(res.p, workspace, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
+}
+
 // With scratch memory: the residue route where it pays and the memory holds it, else the digit planes, else the plain
 // kernel.
 cg_status run_with_workspace(Plan& pl, void* workspace, size_t workspace_bytes, void* stream) {
-    const Residues res = plan_residues(pl);
-    if (res.pay && workspace && aligned(workspace, 16)) {
-        const u64 need = cg::rns_workspace_bytes(res.p);
-        if (workspace_bytes >= need && !workspace_overlaps(pl, workspace, need)) {
-            const hipError_t e = cg::launch_share_gemm_rns(res.p, workspace, static_cast<hipStream_t>(stream));
-            return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;
-        }
-    }
+    bool taken;
+    const cg_status st = run_residues(pl, workspace, workspace_bytes, stream, &taken);
+    if (taken) return st;
     if (!pl.planes_ok) return run_direct(pl, stream);
     return run_planes(pl, workspace, workspace_bytes, stream);
 }
@@ -1272,7 +1294,7 @@ cg_status cg_share_conv2d_ws(const uint64_t* x_i, const uint64_t* x_ip1, const u
 cg_status cg_share_conv2d_dgrad(const uint64_t* g_i, const uint64_t* g_ip1, const uint64_t* w_i,
                                 const uint64_t* w_ip1, uint64_t* dx_i, const cg_conv2d_desc* d, void* stream) {
     Plan pl;
-    const cg_status generic = plan_conv2d_dgrad(g_i, g_ip1, w_i, w_ip1, dx_i, d, &pl);
+    const cg_status generic = plan_conv2d_dgrad(g_i, g_ip1, w_i, w_ip1, dx_i, d, true, &pl);
     if (generic != CG_OK && generic != CG_ERR_UNSUPPORTED) return generic;  // arguments are wrong either way
     auto fallback = [&]() { return generic == CG_OK ? run_direct(pl, stream) : generic; };
     const void* in[4] = {g_i, g_ip1, w_i, w_ip1};
@@ -1296,6 +1318,25 @@ cg_status cg_share_conv2d_dgrad(const uint64_t* g_i, const uint64_t* g_ip1, cons
         if (!empty[i])
             if (cg_status st = run_direct(phase[i], stream)) return st;
     return CG_OK;
+}
+
+size_t cg_share_conv2d_dgrad_workspace_bytes(const cg_conv2d_desc* d) {
+    Plan pl;
+    if (plan_conv2d_dgrad(nullptr, nullptr, nullptr, nullptr, nullptr, d, false, &pl) != CG_OK) return 0;
+    const Residues res = plan_residues(pl);
+    return res.pay ? (size_t)cg::rns_workspace_bytes(res.p) : 0;
+}
+
+cg_status cg_share_conv2d_dgrad_ws(const uint64_t* g_i, const uint64_t* g_ip1, const uint64_t* w_i, const uint64_t* w_ip1,
+                                   uint64_t* dx_i, const cg_conv2d_desc* d, void* workspace, size_t workspace_bytes,
+                                   void* stream) {
+    Plan pl;
+    if (plan_conv2d_dgrad(g_i, g_ip1, w_i, w_ip1, dx_i, d, true, &pl) == CG_OK) {
+        bool taken;
+        const cg_status st = run_residues(pl, workspace, workspace_bytes, stream, &taken);
+        if (taken) return st;
+    }
+    return cg_share_conv2d_dgrad(g_i, g_ip1, w_i, w_ip1, dx_i, d, stream);
 }
 
 cg_status cg_share_conv2d_wgrad(const uint64_t* g_i, const uint64_t* g_ip1, const uint64_t* x_i,

@@ -31,6 +31,7 @@ struct RnsParams {
     int words, slices;                       // words of a row per tap, and the 64-word slices they take
     int x_rows;                              // rows of the left operand (pixels); row x_rows of a plane is zero
     int conv;                                // the left operand's rows are gathered tap by tap
+    int flip;                                // the right operand is stored [words, taps in reverse, N] (a filter, for its input gradient)
     int H, W, Ho, Wo, kh, kw, sh, sw, ph, pw;
     int nmod;
     RnsPart large, small;                    // which moduli run on tiles of 256 and which on tiles of 128
@@ -38,7 +39,7 @@ struct RnsParams {
     int by_rounds;                           // the XCDs work on one modulus at a time
     int blocks_n;                            // 16 x 16 blocks of the result's planes along N
     double product_us;                       // modelled time of the product with that size for all moduli
-    FastDiv div_slices, div_taps, div_howo, div_wo, div_blocks_n;
+    FastDiv div_slices, div_taps, div_n, div_howo, div_wo, div_blocks_n;
 };
 
 // Fills every size of p that follows from M, N, words, x_rows and the window; false where the route does not apply

@@ -127,8 +127,9 @@ __device__ __forceinline__ u32 fast_div(u32 n, FastDiv d) { return (__umulhi(n, 
 // Plane layout: [modulus][slice of 64 words][tap][term][row][64 bytes]; the terms are x_a, x_b on the left and
 // w_a + w_b, w_a on the right.  The rows a tile of the product reads in a step (one term of one slice) follow each
 // other: 16 KB in one run for 256 rows of a matrix.
-// A thread takes 8 words of both shares; 8 lanes write one row, a wave 8 rows of one slice.
-template <int NM, bool RIGHT>
+// A thread takes 8 words of both shares; 8 lanes write one row, a wave 8 rows of one slice.  FLIP: row (tap, n) of the right operand
+// has its words at [word][taps - 1 - tap][n] of a filter; the 8 rows of a wave are neighbours in n.
+template <int NM, bool RIGHT, bool FLIP = false>
 __device__ __forceinline__ void planes_part(const u64* __restrict__ a, const u64* __restrict__ b, char* __restrict__ out,
                                             u64 plane, u32 unit, int words, int slices, u32 rows, u32 out_rows, u32 taps,
                                             FastDiv div_slices, FastDiv div_taps, bool vec) {
@@ -140,8 +141,12 @@ __device__ __forceinline__ void planes_part(const u64* __restrict__ a, const u64
     // long as both operands have it)
     const int k = (int)(slice * 64u + (unit & 7u) * 2u);
     u64 va[8], vb[8];
-    const size_t at = (size_t)row * (size_t)words + (size_t)k;
-    if (vec) {   // an even number of words: both of a pair are there or none
+    // (row of the plane and tap: a filter's own order is [row][tap])
+    const u32 major = fast_div(row, div_taps);
+    const u32 out_row = FLIP ? row - major * out_rows : major, tap = FLIP ? major : row - major * taps;
+    const size_t at = FLIP ? ((size_t)k * taps + (taps - 1u - tap)) * out_rows + out_row : (size_t)row * (size_t)words + (size_t)k;
+    const size_t pitch = FLIP ? (size_t)taps * out_rows : 1;
+    if (!FLIP && vec) {   // an even number of words: both of a pair are there or none
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool in = row < rows && k + 16 * j < words;
@@ -156,8 +161,8 @@ __device__ __forceinline__ void planes_part(const u64* __restrict__ a, const u64
         for (int j = 0; j < 8; ++j) {
             const int w = 16 * (j >> 1) + (j & 1);
             const bool in = row < rows && k + w < words;
-            va[j] = in ? a[at + w] : 0;
-            vb[j] = in ? b[at + w] : 0;
+            va[j] = in ? a[at + w * pitch] : 0;
+            vb[j] = in ? b[at + w * pitch] : 0;
         }
     }
     u32 d[2][8][2];
@@ -169,7 +174,6 @@ __device__ __forceinline__ void planes_part(const u64* __restrict__ a, const u64
         d[0][j][0] = (u32)t0; d[0][j][1] = (u32)(t0 >> 32);
         d[1][j][0] = (u32)t1; d[1][j][1] = (u32)(t1 >> 32);
     }
-    const u32 out_row = fast_div(row, div_taps), tap = row - out_row * taps;
     char* dst = out + ((size_t)(slice * taps + tap) * 2u * out_rows + out_row) * 64u + (unit & 7u) * 8u;
     const size_t term_bytes = (size_t)out_rows * 64u;
     for_each_index([&](auto mi) {
@@ -193,7 +197,7 @@ __device__ __forceinline__ void planes_part(const u64* __restrict__ a, const u64
     }, std::make_integer_sequence<int, NM>{});
 }
 
-template <int NM>
+template <int NM, bool FLIP>
 __global__ __launch_bounds__(256) void rns_planes_kernel(RnsParams p, u32 x_blocks, u32 x_units, u32 w_units, int vec) {
     if (blockIdx.x < x_blocks) {
         const u32 unit = blockIdx.x * 256u + threadIdx.x;
@@ -203,8 +207,8 @@ __global__ __launch_bounds__(256) void rns_planes_kernel(RnsParams p, u32 x_bloc
     } else {
         const u32 unit = (blockIdx.x - x_blocks) * 256u + threadIdx.x;
         if (unit < w_units)
-            planes_part<NM, true>(p.w_a, p.w_b, p.wp, p.w_plane, unit, p.words, p.slices, (u32)(p.N * p.kh * p.kw),
-                                  (u32)p.N, (u32)(p.kh * p.kw), p.div_slices, p.div_taps, vec);
+            planes_part<NM, true, FLIP>(p.w_a, p.w_b, p.wp, p.w_plane, unit, p.words, p.slices, (u32)(p.N * p.kh * p.kw),
+                                        (u32)p.N, (u32)(p.kh * p.kw), p.div_slices, FLIP ? p.div_n : p.div_taps, vec);
     }
 }
 
@@ -540,7 +544,8 @@ hipError_t run(const RnsParams& p, hipStream_t stream) {
     const u32 w_units = ((u32)(p.N * p.kh * p.kw) + 7u) / 8u * (u32)p.slices * 64u;
     const u32 x_blocks = (x_units + 255u) / 256u, w_blocks = (w_units + 255u) / 256u;
     const int vec = p.words % 2 == 0 && (((uintptr_t)p.x_a | (uintptr_t)p.x_b | (uintptr_t)p.w_a | (uintptr_t)p.w_b) & 15) == 0;
-    hipLaunchKernelGGL((rns_planes_kernel<NM>), dim3(x_blocks + w_blocks), dim3(256), 0, stream, p, x_blocks, x_units, w_units, vec);
+    auto planes = p.flip ? rns_planes_kernel<NM, true> : rns_planes_kernel<NM, false>;
+    hipLaunchKernelGGL(planes, dim3(x_blocks + w_blocks), dim3(256), 0, stream, p, x_blocks, x_units, w_units, vec);
     if (hipError_t e = hipGetLastError()) return e;
     if (hipError_t e = launch_gemm<256, 256, 2, 4>(p, p.large, stream)) return e;
     if (hipError_t e = launch_gemm<128, 128, 2, 2>(p, p.small, stream)) return e;
@@ -644,6 +649,7 @@ bool rns_plan(RnsParams* p) {
     p->r_plane = (uint64_t)pitch.tiles_m * pitch.tiles_n * edge * edge;
     p->div_slices = make_fast_div((uint32_t)p->slices);
     p->div_taps = make_fast_div((uint32_t)taps);
+    p->div_n = make_fast_div((uint32_t)p->N);
     p->div_howo = make_fast_div((uint32_t)(p->conv ? p->Ho * p->Wo : 1));
     p->div_wo = make_fast_div((uint32_t)(p->conv ? p->Wo : 1));
     p->div_blocks_n = make_fast_div((uint32_t)p->blocks_n);

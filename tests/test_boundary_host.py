@@ -222,6 +222,29 @@ def test_conv_backward_validation(L):
     assert L.cg_share_conv2d_wgrad(*ok, desc(Cout=(1 << 22) + 1), None) == b.CG_ERR_UNSUPPORTED
 
 
+def test_input_gradient_with_scratch_validates_as_without(L):
+    from paper_2104_10949_amd import binding as b
+    ok = [1 << 40, 2 << 40, 3 << 40, 4 << 40, 5 << 40]
+
+    def desc(**kw):
+        base = dict(B=32, H=16, W=16, Cin=256, Cout=256, kh=3, kw=3, stride_h=1, stride_w=1, pad_h=1, pad_w=1)
+        base.update(kw)
+        return ctypes.byref(b.ConvDesc(**base))
+
+    need = L.cg_share_conv2d_dgrad_workspace_bytes
+    assert need(desc()) > 0
+    for none in (desc(stride_h=2), desc(Cout=0), desc(Cout=8), desc(Cout=1 << 18), None):   # strided, wrong, small, too long
+        assert need(none) == 0
+    f = L.cg_share_conv2d_dgrad_ws
+    ws = (6 << 40, 1 << 40)
+    assert f(*ok, None, *ws, None) == b.CG_ERR_NULL
+    assert f(*ok[:4], 0, desc(), *ws, None) == b.CG_ERR_NULL
+    assert f(*ok, desc(Cout=0), *ws, None) == b.CG_ERR_SHAPE
+    assert f(ok[0] + 4, *ok[1:], desc(), *ws, None) == b.CG_ERR_ALIGN
+    assert f(*ok[:4], ok[0] + 8, desc(), *ws, None) == b.CG_ERR_ALIAS
+    assert f(*ok, desc(Cout=1 << 18), *ws, None) == b.CG_ERR_UNSUPPORTED
+
+
 def test_static_scratch_entry_point_validates_and_bounds_its_size(L):
     from paper_2104_10949_amd import binding as b
     f = L.cg_share_matmul_static

@@ -195,6 +195,60 @@ def test_gathers(cg, ro, wl, xs, ws, st, pd):
         assert np.array_equal(cg.to_host(got[image:image + 1, :, :, lo:lo + 40].contiguous()), want)
 
 
+# the input gradient of unit-stride layers: 18 and 19 moduli, channel counts of any kind, padding beyond the window, windows that
+# differ along the axes, and the 1 x 1 layer, which is a product of rows
+DGRADS = [((32, 16, 16, 256), (256, 3, 3, 256), (1, 1)), ((5, 33, 21, 130), (200, 3, 5, 130), (0, 2)),
+          ((4, 25, 25, 257), (300, 3, 3, 257), (4, 1)), ((6, 21, 20, 333), (321, 5, 5, 333), (2, 2)),
+          ((8, 16, 16, 1025), (2049, 1, 1, 1025), (0, 0))]
+
+
+@pytest.mark.parametrize("xs,ws,pd", DGRADS)
+def test_input_gradient(cg, ro, wl, xs, ws, pd):
+    say(f"residue route input gradient x={xs} w={ws} pad={pd}")
+    need = cg.cg_share_conv2d_dgrad_workspace_bytes(xs, ws, (1, 1), pd)
+    assert need > 0
+    gs = (xs[0], xs[1] + 2 * pd[0] - ws[1] + 1, xs[2] + 2 * pd[1] - ws[2] + 1, ws[0])
+    ops = [wl.draw_ring(s, 9260 + i) for i, s in enumerate((gs, gs, ws, ws))]
+    dev = [cg.to_device(a) for a in ops]
+    buf = poisoned(need + 512)
+    got = cg.cg_share_conv2d_dgrad_ws(*dev, xs, buf[:need // 8], pad=pd)
+    assert bool((buf[need // 8:] == 0x5A5A5A5A5A5A5A5A).all())
+    plain = cg.cg_share_conv2d_dgrad_ws(*dev, xs, None, pad=pd)
+    assert torch.equal(got, plain)
+    for unusable in (buf[:need // 8 - 2], buf[1:need // 8 + 1]):   # too small, 8-byte aligned: the route without
+        assert torch.equal(cg.cg_share_conv2d_dgrad_ws(*dev, xs, unusable, pad=pd), plain)
+    assert torch.equal(cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd), plain)   # scratch memory of its own
+    last = [a[-1:] for a in ops[:2]]
+    want = ro.party_conv2d_dgrad(*last, *ops[2:], (1,) + xs[1:], (1, 1), pd)
+    assert np.array_equal(cg.to_host(got[-1:].contiguous()), want)
+
+
+def test_input_gradient_without_scratch_of_its_own(cg, wl):
+    """Captured, on a named stream or beyond the limit the call takes no memory; a graph's replays follow the operands."""
+    xs, ws, pd = (32, 16, 16, 256), (256, 3, 3, 256), (1, 1)
+    say("input gradient captured and on a named stream")
+    dev = [cg.to_device(wl.draw_ring(s, 9270 + i)) for i, s in enumerate((xs, xs, ws, ws))]
+    want = cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd)
+    dx = torch.empty_like(want)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    before = torch.cuda.memory_allocated()
+    torch.cuda.reset_peak_memory_stats()
+    cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd, dx_i=dx, stream=side)
+    side.synchronize()
+    assert torch.equal(dx, want) and torch.cuda.max_memory_allocated() < before + (64 << 20)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd, dx_i=dx)
+    for i in range(3):
+        for t in dev:
+            t.add_(i + 1)
+        want = cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dx, want)
+
+
 def test_scratch_of_the_digit_planes_is_still_enough(cg, wl):
     """A caller that brings no more than the digit planes take, or memory the route cannot use, gets the same words."""
     M, N, K = 2000, 2040, 2044
