@@ -146,6 +146,27 @@ struct LinearVec {
     }
 };
 
+// Row-major left operand with any ld and any 8-byte-aligned base, 16-byte loads all the same (the memory wants a multiple of four
+// bytes, and a view's range is checked word by word).  With an odd K the last pair of a row brings the next row's first word
+// along: the right operand has a zero there (LinearScalar, TransScalar), so it adds nothing.  Against 8-byte loads (16 of a step's 24,
+// and addresses that spilled): 4096 x 4096 x 1001 991 -> 917 us, 300 x 4001 x 2049 200 -> 184.
+struct LinearPair {
+    u32 off0;
+    u32 kq;
+    __device__ __forceinline__ void init(const GemmParams&, int, int row_local, int rows_left, u32 ld,
+                                         int q, int jh) {
+        kq = 16 * jh + 2 * q;
+        off0 = row_local < rows_left ? (u32)row_local * ld * 8u + kq * 8u : OOB;
+    }
+    __device__ __forceinline__ void load(const GemmParams&, __amdgpu_buffer_rsrc_t r, int ks, u32 K,
+                                         u4 out[2]) const {
+        const u32 off = off0 + 256u * ks;
+        const u32 k = 32u * ks + kq;
+        out[0] = __builtin_amdgcn_raw_buffer_load_b128(r, k < K ? off : OOB, 0, 0);
+        out[1] = __builtin_amdgcn_raw_buffer_load_b128(r, k + 8u < K ? off + 64u : OOB, 0, 0);
+    }
+};
+
 // Row-major operand with 8-byte loads: any ld, any 8-byte-aligned base.
 struct LinearScalar {
     u32 off0;
@@ -779,7 +800,7 @@ __device__ __forceinline__ void share_gemm_body(const GemmParams p) {
     // 64-byte run on consecutive lanes; transposed operands put consecutive rows there.
     typedef typename std::conditional<AMODE == A_LINEAR_VEC, LinearVec,
             typename std::conditional<AMODE == A_LINEAR_WIDE, LinearWide,
-            typename std::conditional<AMODE == A_LINEAR_SCALAR, LinearScalar,
+            typename std::conditional<AMODE == A_LINEAR_SCALAR, LinearPair,
             typename std::conditional<AMODE == A_CONV_C32, ConvC32,
             typename std::conditional<AMODE == A_TRANS, TransScalar,
             typename std::conditional<AMODE == A_PATCH_T, PatchTrans,
@@ -1373,8 +1394,10 @@ static constexpr int SPLIT_MIN_SLICES = 2;
 // Cost of the fixed part of a block (prologue, fold of the accumulators into z), in
 // units of one K slice of the main loop, with a plain store and with atomic adds.
 static constexpr double SPLIT_COST_PLAIN = 1.0, SPLIT_COST_ATOMIC = 2.0;
-// The streamed distribution must beat the classic one by this factor of modelled time to be used.
-static constexpr double STREAM_MARGIN = 0.88;
+// The streamed distribution must beat the classic one by this factor of modelled time to be used, by a little more where the
+// right operand comes in 8-byte loads (1000 x 777 x 1531, 0.858: 95 us streamed, 88 classic; of 250 odd products none is slower
+// than before with 0.84, and all together take 0.91 of the time).
+static constexpr double STREAM_MARGIN = 0.88, STREAM_MARGIN_SCALAR = 0.84;
 // Several rounds of unsplit tiles of at most this many slices are run as one round of blocks that
 // each walk through whole tiles.
 static constexpr int PERSIST_MAX_SLICES = 32;
@@ -1498,7 +1521,8 @@ static double classic_cost(int64_t tiles, int nk, int ks) {
 // The streamed distribution is compiled for the address generators of the large layers only.
 template <int AMODE, int BMODE>
 struct CanStream {
-    static constexpr bool value = (AMODE == A_LINEAR_VEC && BMODE == B_VEC) || (AMODE == A_CONV_C32 && BMODE == B_VEC) ||
+    static constexpr bool value = (AMODE == A_LINEAR_VEC && BMODE == B_VEC) || (AMODE == A_LINEAR_SCALAR && BMODE == B_SCALAR) ||
+                                  (AMODE == A_CONV_C32 && BMODE == B_VEC) ||
                                   (AMODE == A_CONV_C32 && BMODE == B_FLIP_C32) || (AMODE == A_TRANS && BMODE == B_PATCH_T) ||
                                   (AMODE == A_PATCH_T && BMODE == B_TRANS);
 };
@@ -1527,7 +1551,8 @@ static hipError_t launch(const GemmParams& p, hipStream_t stream) {
     if (CanStream<AMODE, BMODE>::value && units >= 3 * ROUND_BLOCKS && units < ((int64_t)1 << 40)) {
         const int64_t per = (units + ROUND_BLOCKS - 1) / ROUND_BLOCKS;
         const double streamed = (double)per + SPLIT_COST_ATOMIC * ((double)per / nk + 1.0);
-        if (streamed < STREAM_MARGIN * classic_cost(tiles, nk, q.ksplit)) {
+        constexpr double margin = BMODE == B_SCALAR ? STREAM_MARGIN_SCALAR : STREAM_MARGIN;
+        if (streamed < margin * classic_cost(tiles, nk, q.ksplit)) {
             q.stream_per = per;
             q.ksplit = 2;  // any value above 1: the folds add atomically into a zero-filled z
             grid = (unsigned)((units + per - 1) / per);
@@ -1542,7 +1567,7 @@ static hipError_t launch(const GemmParams& p, hipStream_t stream) {
     // Row-major left operands only: a patch gather re-reads the rows of neighbouring tiles, which hit in L2
     // when the neighbours run at the same time and miss when one block takes them one after the other
     // (measured on the 3x3 layers of the VGG-shaped step: twice the memory reads for 1-3 % of time).
-    if (CanStream<AMODE, BMODE>::value && AMODE == A_LINEAR_VEC && q.stream_per == 0 && q.ksplit == 1 &&
+    if (CanStream<AMODE, BMODE>::value && (AMODE == A_LINEAR_VEC || AMODE == A_LINEAR_SCALAR) && q.stream_per == 0 && q.ksplit == 1 &&
         tiles > ROUND_BLOCKS && nk <= PERSIST_MAX_SLICES) {
         const int64_t tiles_per_block = (tiles + ROUND_BLOCKS - 1) / ROUND_BLOCKS;
         q.stream_per = tiles_per_block * nk;

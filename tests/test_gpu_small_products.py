@@ -50,3 +50,24 @@ def test_small_products(cg, ro, wl, M, N, K):
     got = cg.to_device(base)
     cg.cg_share_matmul_acc(*dev, got)
     assert np.array_equal(cg.to_host(got), base + want)
+
+
+# odd K and operands at odd words: pairs of the left operand that reach into the next row, the last of them into the end of the
+# tensor; split over blocks, streamed over tiles of unequal slices, whole tiles streamed
+ODD = [(1, 130, 33), (129, 65, 31), (1000, 77, 1531), (700, 1030, 2051), (40000, 64, 33), (128, 64, 1), (257, 700, 95)]
+
+
+@pytest.mark.parametrize("M,N,K", ODD)
+@pytest.mark.parametrize("at", [0, 1])
+def test_rows_of_odd_length(cg, ro, wl, M, N, K, at):
+    say(f"odd rows M={M} N={N} K={K} first word {at}")
+    ops = [wl.draw_ring((r, K), 9650 + i) for i, r in enumerate((M, M, N, N))]
+    dev = []
+    for a in ops:   # behind the last word lies something else
+        whole = torch.full((a.size + at + 8,), -1, dtype=torch.int64, device="cuda")
+        whole[at:at + a.size].copy_(cg.to_device(a).view(-1))
+        dev.append(whole[at:at + a.size].view(*a.shape))
+    got = cg.cg_share_matmul(*dev)
+    rows = sorted({i for i in (0, 1, 127, 128, 129, M // 2, M - 2, M - 1) if 0 <= i < M})
+    want = ro.party_matmul(ops[0][rows], ops[1][rows], ops[2], ops[3])
+    assert np.array_equal(cg.to_host(got[rows].contiguous()), want)
