@@ -3,12 +3,13 @@
 //
 // Such a product is a few microseconds of matrix work, so what counts is the length of the chain
 // launch -> load -> split -> multiply -> store and how many compute units share it, not the rate of any
-// unit.  A block owns one 16 x 16 block of z; its waves share out the 32-word slices of K and never wait for
+// unit.  A block owns one 16 x 16 block of z (or 8 rows or columns of one, where that still fits one round of the chip); its waves
+// share out the 32-word slices of K and never wait for
 // each other until the end.  For v_mfma_i32_16x16x64_i8 a lane supplies 16 contraction bytes of one row, so
 // lane (r, g) ends up with the sixteen words of row r that make up k-group g (g = 2 * share + half of the
 // slice), splits them into eight signed digits in its own registers (which is the operand layout of the
 // instruction), and the wave issues the 36 digit-pair products of the slice.  The waves' partial results
-// meet in a 2 KB LDS tile through 64-bit LDS adds; one plain store per element, or an atomic add when K is
+// meet in LDS; one plain store per element, or an atomic add when K is
 // also split over blocks.
 // Same arithmetic as share_gemm_kernel: digits, accumulators P_0..P_7, one fold at the end (the launcher takes
 // products of at most 511 slices per wave).
@@ -69,7 +70,7 @@ __device__ __forceinline__ u4 add64x2(u4 a, u4 b) {
     return r;
 }
 
-// grid: x = 16-column block of z, y = 16-row block, z = range of K slices (gridDim.z > 1: z is cleared or
+// grid: x = block of COLS columns of z, y = block of ROWS rows, z = range of K slices (gridDim.z > 1: z is cleared or
 // holds the value to add to, and every block adds atomically).  Rows of the operands past M or N are
 // replaced by the last row: their products land in elements that are never stored.
 //
@@ -83,15 +84,13 @@ __device__ __forceinline__ u4 add64x2(u4 a, u4 b) {
 // eight rows' piece of the other, and these are sixteen different groups of four banks.  With plain p ^ r every turn met
 // a conflict: 32 x 512 x 512 7.38 -> 7.23 us, 128 x 128 x 784 10.29 -> 10.21.  No barrier is involved: a wave reads what it wrote
 // itself.
+template <int ROWS, int COLS>
 __global__ __launch_bounds__(SMALL_WAVES * 64) void share_gemm_small_kernel(const GemmParams p) {
     __shared__ __attribute__((aligned(16))) char stage[SMALL_WAVES][4][16 * 256];
-    __shared__ unsigned long long red[256];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // said to be uniform: the slice loop runs on the scalar unit
-    if (tid < 256) red[tid] = 0;
-    __syncthreads();
 
-    const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+    const int n0 = blockIdx.x * COLS, m0 = blockIdx.y * ROWS;
     const u32 K = (u32)p.K;
     const int nk = (int)((K + 31) >> 5);
     const int per = (nk + (int)gridDim.z - 1) / (int)gridDim.z;
@@ -124,16 +123,17 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void share_gemm_small_kernel(cons
 #pragma unroll
     for (int i = 0; i < 8; ++i) rd_off[i] = ((8 * (kg & 1) + i) ^ swizzle(r16)) << 4;
 
-    u4 rxa[4], rxb[4], rwa[4], rwb[4];
+    constexpr int AJ = ROWS / 4, BJ = COLS / 4;   // loads of four rows each
+    u4 rxa[AJ], rxb[AJ], rwa[BJ], rwb[BJ];
     // words 2 lp, 2 lp + 1 of slice ks of the four rows (K is even: the pair is inside or outside K as a whole)
     auto load = [&](int ks) {
         const u32 at = (32u * (u32)ks + 2u * (u32)lp < K ? 0u : OOB) + 256u * (u32)ks;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            rxa[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_xa, a_off[j] + at, 0, 0);
-            rxb[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_xb, a_off[j] + at, 0, 0);
-            rwa[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_wa, b_off[j] + at, 0, 0);
-            rwb[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_wb, b_off[j] + at, 0, 0);
+            if (j < AJ) rxa[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_xa, a_off[j] + at, 0, 0);
+            if (j < AJ) rxb[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_xb, a_off[j] + at, 0, 0);
+            if (j < BJ) rwa[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_wa, b_off[j] + at, 0, 0);
+            if (j < BJ) rwb[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_wb, b_off[j] + at, 0, 0);
         }
     };
 
@@ -145,10 +145,10 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void share_gemm_small_kernel(cons
     while (ks < ks_end) {   // uniform over the wave
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            *reinterpret_cast<u4*>(my_stage + st_off[j]) = rxa[j];
-            *reinterpret_cast<u4*>(my_stage + 4096 + st_off[j]) = rxb[j];
-            *reinterpret_cast<u4*>(my_stage + 8192 + st_off[j]) = add64x2(rwa[j], rwb[j]);
-            *reinterpret_cast<u4*>(my_stage + 12288 + st_off[j]) = rwa[j];
+            if (j < AJ) *reinterpret_cast<u4*>(my_stage + st_off[j]) = rxa[j];
+            if (j < AJ) *reinterpret_cast<u4*>(my_stage + 4096 + st_off[j]) = rxb[j];
+            if (j < BJ) *reinterpret_cast<u4*>(my_stage + 8192 + st_off[j]) = add64x2(rwa[j], rwb[j]);
+            if (j < BJ) *reinterpret_cast<u4*>(my_stage + 12288 + st_off[j]) = rwa[j];
         }
         const int next = ks + SMALL_WAVES;
         if (next < ks_end) load(next);
@@ -171,7 +171,8 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void share_gemm_small_kernel(cons
         ks = next;
     }
     // fold: sum_s sext(P_s) << 8s, P_4..P_7 only reach bits 32..63; lane (c, g) holds rows 4g .. 4g+3 of
-    // column c of the block
+    // column c of the block.  A wave leaves its sums where its words were staged.
+    u64* const part = reinterpret_cast<u64*>(my_stage);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         u64 v = (u64)(int64_t)acc[0][i];
@@ -180,14 +181,16 @@ __global__ __launch_bounds__(SMALL_WAVES * 64) void share_gemm_small_kernel(cons
         v += (u64)(int64_t)acc[3][i] << 24;
         const u32 hi = (u32)acc[4][i] + ((u32)acc[5][i] << 8) + ((u32)acc[6][i] << 16) + ((u32)acc[7][i] << 24);
         v += (u64)hi << 32;
-        atomicAdd(&red[(4 * kg + i) * 16 + r16], (unsigned long long)v);
+        part[(4 * kg + i) * 16 + r16] = v;
     }
     __syncthreads();
     if (tid < 256) {
         const int row = m0 + (tid >> 4), col = n0 + (tid & 15);
-        if (row < p.M && col < p.N) {
+        if ((tid >> 4) < ROWS && (tid & 15) < COLS && row < p.M && col < p.N) {
             u64* dst = p.z + (u64)row * (u64)p.N + (u64)col;
-            const u64 v = red[tid];
+            u64 v = 0;
+#pragma unroll
+            for (int k = 0; k < SMALL_WAVES; ++k) v += reinterpret_cast<const u64*>(&stage[k][0][0])[tid];
             if (gridDim.z > 1) atomicAdd(reinterpret_cast<unsigned long long*>(dst), (unsigned long long)v);
             else *dst = p.z_add ? *dst + v : v;
         }
@@ -461,8 +464,18 @@ hipError_t launch_share_gemm_small(const GemmParams& p, hipStream_t stream) {
     }
     if (ksplit > 1 && !p.z_prezeroed && !p.z_add)
         if (hipError_t e = launch_zero_words(p.z, (size_t)p.M * (size_t)p.N, stream)) return e;
-    hipLaunchKernelGGL(share_gemm_small_kernel, dim3((unsigned)tiles_n, (unsigned)tiles_m, (unsigned)ksplit),
-                       dim3(SMALL_WAVES * 64), 0, stream, p);
+    auto launch = [&](auto kernel, int rows, int cols) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((p.N + cols - 1) / cols), (unsigned)((p.M + rows - 1) / rows), (unsigned)ksplit),
+                           dim3(SMALL_WAVES * 64), 0, stream, p);
+    };
+    // Blocks of 8 rows and columns leave half of the matrix instruction's rows and columns to words that nobody stores, but a
+    // compute unit's loads, which are what such a call waits for, are those of half as many rows: 32 x 512 x 512 7.23 -> 6.58 us,
+    // 128 x 128 x 784 9.5 -> 8.5, 8 x 1000 x 512 7.3 -> 5.9 (of it 0.2 us by sums that meet without LDS atomics).
+    const int64_t m8 = ((int64_t)p.M + 7) / 8, n8 = ((int64_t)p.N + 7) / 8;
+    if (ksplit == 1 && m8 * n8 <= SMALL_ROUND_BLOCKS) launch(share_gemm_small_kernel<8, 8>, 8, 8);
+    else if (ksplit == 1 && m8 * tiles_n <= SMALL_ROUND_BLOCKS) launch(share_gemm_small_kernel<8, 16>, 8, 16);
+    else if (ksplit == 1 && tiles_m * n8 <= SMALL_ROUND_BLOCKS) launch(share_gemm_small_kernel<16, 8>, 16, 8);
+    else launch(share_gemm_small_kernel<16, 16>, 16, 16);
     return hipGetLastError();
 }
 

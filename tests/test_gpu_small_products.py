@@ -52,6 +52,16 @@ def test_small_products(cg, ro, wl, M, N, K):
     assert np.array_equal(cg.to_host(got), base + want)
 
 
+# blocks of 8 x 8, 8 x 16 and 16 x 8 up to a full round, and one block more
+BLOCKS = [(8, 8, 2), (9, 7, 34), (7, 9, 600), (128, 128, 32), (128, 136, 62), (1032, 24, 70), (2048, 8, 34), (2056, 8, 34), (8, 4096, 66),
+          (24, 1368, 34)]
+
+
+@pytest.mark.parametrize("M,N,K", BLOCKS)
+def test_blocks_of_eight(cg, ro, wl, M, N, K):
+    test_small_products(cg, ro, wl, M, N, K)
+
+
 # odd K and operands at odd words: pairs of the left operand that reach into the next row, the last of them into the end of the
 # tensor; split over blocks, streamed over tiles of unequal slices, whole tiles streamed
 ODD = [(1, 130, 33), (129, 65, 31), (1000, 77, 1531), (700, 1030, 2051), (40000, 64, 33), (128, 64, 1), (257, 700, 95)]
