@@ -604,7 +604,7 @@ __device__ __forceinline__ void logical_to_tile(const GemmParams& p, int tiles_m
 // GemmParams::out_*).  ZT: z is stored transposed, [N, M].
 template <bool REMAP, bool ZT>
 __device__ __forceinline__ void fold_blocks(const GemmParams& p, v4i (&acc)[2][2][8], int row0, int col0, int lane,
-                                            bool accumulate) {
+                                            bool accumulate, bool atomic) {
     int lane_f = lane;
     asm volatile("" : "+v"(lane_f));
     const int c16 = lane_f & 15, g4 = lane_f >> 4;
@@ -651,7 +651,7 @@ __device__ __forceinline__ void fold_blocks(const GemmParams& p, v4i (&acc)[2][2
                 }
             }
     };
-    if (p.ksplit > 1) all_elements(std::integral_constant<int, 2>{});
+    if (atomic) all_elements(std::integral_constant<int, 2>{});
     else if (accumulate) all_elements(std::integral_constant<int, 1>{});
     else all_elements(std::integral_constant<int, 0>{});
 }
@@ -725,13 +725,17 @@ struct Walker {
     int ks, nk;         // current slice; end of the current tile's slices
 };
 
-// STREAM selects the streamed work distribution (see run_index); the classic instantiation has exactly
+// DIST: the classic work distribution, the streamed one (see run_index) or the classic one with a split tail (see
+// GemmParams::tail_first); the classic instantiations have exactly
 // one tile per block and compiles to straight-line set-up code.
 // The kernel's body takes its parameters as a copy of the kernel argument: the compiler then reads every field once,
 // ahead of the loop, instead of fetching fields from the argument buffer inside it (measured on the general patch
 // gathers: 20-44 spilled registers become 0-4 and the first layers run 14-20 % faster).
-template <class T, int AMODE, int BMODE, bool STREAM>
+enum Distribution { CLASSIC = 0, STREAMED = 1, CLASSIC_TAIL = 2 };
+
+template <class T, int AMODE, int BMODE, int DIST>
 __device__ __forceinline__ void share_gemm_body(const GemmParams p) {
+    constexpr bool STREAM = DIST == STREAMED;
     constexpr int AU = T::A_UNITS, BU = T::B_UNITS;
     __shared__ __attribute__((aligned(16))) char lds[T::LDS_BYTES];
 
@@ -752,15 +756,25 @@ __device__ __forceinline__ void share_gemm_body(const GemmParams p) {
     const int nb = tiles_m * tiles_n;
     const int nk_all = (int)((p.K + 31) / 32);
     int64_t u0, u_end;
+    bool in_tail = false;   // uniform over the block
     int logical0 = 0, ks0 = 0;   // classic distribution: the block's tile and first slice, known without a division
     if constexpr (STREAM) {
         const int64_t units = (int64_t)nb * nk_all;
         u0 = (int64_t)run_index((int)gridDim.x) * p.stream_per;
         u_end = u0 + p.stream_per < units ? u0 + p.stream_per : units;
     } else {
-        const int run = run_index(nb * p.ksplit);
-        const int split = (int)fast_div((u32)run, p.div_tiles), logical = run - split * nb;
-        const int per_split = p.per_split;
+        int split, logical, per_split = p.per_split;
+        if constexpr (DIST == CLASSIC_TAIL) {   // (written as selects: a block's first load waits for all of this)
+            in_tail = (int)blockIdx.x >= p.tail_first;
+            const int at = in_tail ? (int)blockIdx.x - p.tail_first : run_index(p.tail_first);
+            split = in_tail ? (int)fast_div((u32)at, p.div_tail) : 0;
+            logical = at + (in_tail ? p.tail_first - split * p.tail_tiles : 0);
+            per_split = in_tail ? p.tail_per : per_split;
+        } else {
+            const int run = run_index(nb * p.ksplit);
+            split = (int)fast_div((u32)run, p.div_tiles);
+            logical = run - split * nb;
+        }
         const int kb = split * per_split;
         u0 = (int64_t)logical * nk_all + kb;
         u_end = (int64_t)logical * nk_all + (kb + per_split < nk_all ? kb + per_split : nk_all);
@@ -1285,15 +1299,16 @@ __device__ __forceinline__ void share_gemm_body(const GemmParams p) {
                 par ^= 1;
             }
             fold_blocks<BMODE == B_FLIP_C32, AMODE == A_PATCH_T>(p, acc, fm0, fn0, STREAM ? thread_id_again() & 63 : lane,
-                                                                 ks0 > wc.ks || p.z_add != 0);
+                                                                 ks0 > wc.ks || p.z_add != 0,
+                                                                 DIST == CLASSIC_TAIL ? in_tail : p.ksplit > 1);
         }
         if (!STREAM || wc.u >= u_end) break;
     }
 }
 
-template <class T, int AMODE, int BMODE, bool STREAM>
+template <class T, int AMODE, int BMODE, int DIST>
 __global__ __launch_bounds__(T::NT, 1) void share_gemm_kernel(const GemmParams p) {
-    share_gemm_body<T, AMODE, BMODE, STREAM>(p);
+    share_gemm_body<T, AMODE, BMODE, DIST>(p);
 }
 
 // ===========================================================================
@@ -1384,6 +1399,17 @@ __global__ __launch_bounds__(256) void zero_fill_kernel(u64* z, size_t n) {
 
 #endif  // CG_G0
 
+// z = 0 in the tiles of a split tail
+template <class T>
+static __global__ __launch_bounds__(256) void zero_tiles_kernel(const GemmParams p) {
+    int tm, tn;
+    logical_to_tile(p, (p.M + T::BM - 1) / T::BM, (p.N + T::BN - 1) / T::BN, p.tail_first + (int)blockIdx.x, tm, tn);
+    for (int e = threadIdx.x; e < T::BM * T::BN; e += 256) {
+        const int row = tm * T::BM + e / T::BN, col = tn * T::BN + e % T::BN;
+        if (row < p.M && col < p.N) p.z[(u64)row * (u64)p.N + (u64)col] = 0;
+    }
+}
+
 template <class T, int AMODE, int BMODE>
 static hipError_t launch(const GemmParams& p, hipStream_t stream);
 
@@ -1398,6 +1424,9 @@ static constexpr double SPLIT_COST_PLAIN = 1.0, SPLIT_COST_ATOMIC = 2.0;
 // right operand comes in 8-byte loads (1000 x 777 x 1531, 0.858: 95 us streamed, 88 classic; of 250 odd products none is slower
 // than before with 0.84, and all together take 0.91 of the time).
 static constexpr double STREAM_MARGIN = 0.88, STREAM_MARGIN_SCALAR = 0.84;
+// A last round that is at most half full shares its tiles out over all compute units where that shortens it by this many slices
+// (a launch that clears the tiles and the atomic adds cost about two).
+static constexpr int TAIL_MIN_SAVING = 3;
 // Several rounds of unsplit tiles of at most this many slices are run as one round of blocks that
 // each walk through whole tiles.
 static constexpr int PERSIST_MAX_SLICES = 32;
@@ -1535,6 +1564,20 @@ struct StreamOnly {
     static constexpr bool value = (AMODE == A_TRANS && BMODE == B_PATCH_T) || (AMODE == A_PATCH_T && BMODE == B_TRANS);
 };
 
+// The split tail is compiled where a product of a few slices per tile and no streamed instantiation is ordinary work: general gathers
+// (first layers) and the gradients of fully connected layers.  An instantiation of its own: the selects that find a block's part
+// cost the others 0.3 - 0.5 us a call.  7x7 stem on 224 x 224 x 3, batch 8, 784 tiles of five slices: 87.5 -> 80 us; weight gradient
+// 4200 x 512 x 256, 264 tiles of eight: 62 -> 44.
+template <int AMODE, int BMODE>
+struct CanTail {
+    static constexpr bool value = AMODE == A_CONV_GEN && BMODE != B_FLIP_GEN;
+    static_assert(!value || !CanStream<AMODE, BMODE>::value, "a streamed instantiation spreads the slices itself");
+};
+template <>
+struct CanTail<A_TRANS, B_TRANS> {
+    static constexpr bool value = true;
+};
+
 template <class T, int AMODE, int BMODE>
 static hipError_t launch(const GemmParams& p, hipStream_t stream) {
     const int64_t tiles_m = (p.M + T::BM - 1) / T::BM, tiles_n = (p.N + T::BN - 1) / T::BN;
@@ -1579,6 +1622,20 @@ static hipError_t launch(const GemmParams& p, hipStream_t stream) {
         q.stream_per = (nk + q.ksplit - 1) / q.ksplit;
         grid = (unsigned)((units + q.stream_per - 1) / q.stream_per);
     }
+    // Split tail: several rounds of unsplit tiles whose last one is at most half full
+    q.tail_tiles = 0;
+    const int64_t tail = tiles % ROUND_BLOCKS;
+    if (CanTail<AMODE, BMODE>::value && q.stream_per == 0 && q.ksplit == 1 && tiles > ROUND_BLOCKS && tail > 0 && tail <= ROUND_BLOCKS / 2) {
+        int64_t parts = ROUND_BLOCKS / tail < nk ? ROUND_BLOCKS / tail : nk;
+        const int64_t per = (nk + parts - 1) / parts;
+        parts = (nk + per - 1) / per;
+        if (nk - per >= TAIL_MIN_SAVING) {
+            q.tail_first = (int)(tiles - tail);
+            q.tail_tiles = (int)tail; q.tail_per = (int)per;
+            q.div_tail = make_fast_div((uint32_t)tail);
+            grid = (unsigned)(q.tail_first + tail * parts);
+        }
+    }
     constexpr bool MATRIX_PAIR =
         (AMODE == A_LINEAR_VEC || AMODE == A_LINEAR_SCALAR || AMODE == A_LINEAR_WIDE || AMODE == A_PLANES) &&
         (BMODE == B_VEC || BMODE == B_SCALAR || BMODE == B_WIDE || BMODE == B_PLANES);
@@ -1601,14 +1658,24 @@ static hipError_t launch(const GemmParams& p, hipStream_t stream) {
     }
     if (q.ksplit > 1)
         if (hipError_t e = launch_zero_fill(q, stream)) return e;
+    if constexpr (CanTail<AMODE, BMODE>::value) {
+        if (q.tail_tiles > 0) {
+            if (!q.z_add && !q.z_prezeroed) {
+                hipLaunchKernelGGL((zero_tiles_kernel<T>), dim3((unsigned)q.tail_tiles), dim3(256), 0, stream, q);
+                if (hipError_t e = hipGetLastError()) return e;
+            }
+            hipLaunchKernelGGL((share_gemm_kernel<T, AMODE, BMODE, CLASSIC_TAIL>), dim3(grid), dim3(T::NT), 0, stream, q);
+            return hipGetLastError();
+        }
+    }
     if constexpr (CanStream<AMODE, BMODE>::value) {
         if (q.stream_per > 0) {
-            hipLaunchKernelGGL((share_gemm_kernel<T, AMODE, BMODE, true>), dim3(grid), dim3(T::NT), 0, stream, q);
+            hipLaunchKernelGGL((share_gemm_kernel<T, AMODE, BMODE, STREAMED>), dim3(grid), dim3(T::NT), 0, stream, q);
             return hipGetLastError();
         }
     }
     if constexpr (!StreamOnly<AMODE, BMODE>::value)
-        hipLaunchKernelGGL((share_gemm_kernel<T, AMODE, BMODE, false>), dim3(grid), dim3(T::NT), 0, stream, q);
+        hipLaunchKernelGGL((share_gemm_kernel<T, AMODE, BMODE, CLASSIC>), dim3(grid), dim3(T::NT), 0, stream, q);
     return hipGetLastError();
 }
 

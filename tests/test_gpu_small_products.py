@@ -81,3 +81,36 @@ def test_rows_of_odd_length(cg, ro, wl, M, N, K, at):
     rows = sorted({i for i in (0, 1, 127, 128, 129, M // 2, M - 2, M - 1) if 0 <= i < M})
     want = ro.party_matmul(ops[0][rows], ops[1][rows], ops[2], ops[3])
     assert np.array_equal(cg.to_host(got[rows].contiguous()), want)
+
+
+# more than one round of unsplit tiles whose last one is shared out: first layers and a weight gradient, one tile and half a round
+# of them left over, plainly stored and added
+TAIL_LAYERS = [((3, 105, 105, 5), (64, 5, 5, 5), (1, 1), (2, 2)), ((1, 104, 106, 3), (130, 7, 7, 3), (1, 1), (3, 3)),
+               ((1, 182, 181, 7), (64, 5, 5, 7), (1, 1), (2, 2))]
+
+
+@pytest.mark.parametrize("xs,ws,st,pd", TAIL_LAYERS)
+def test_last_round_of_a_first_layer(cg, ro, wl, xs, ws, st, pd):
+    say(f"split tail conv x={xs} w={ws}")
+    ops = [wl.draw_ring(s, 9680 + i) for i, s in enumerate((xs, xs, ws, ws))]
+    dev = [cg.to_device(a) for a in ops]
+    z = torch.full(cg.conv_out_shape(xs, ws, st, pd), 77, dtype=torch.int64, device="cuda")
+    got = cg.cg_share_conv2d(*dev, stride=st, pad=pd, z_i=z)
+    want = ro.party_conv2d(*ops, st, pd)
+    assert np.array_equal(cg.to_host(got), want)
+    base = wl.draw_ring(tuple(got.shape), 9690)
+    acc = cg.to_device(base)
+    cg.cg_share_conv2d_acc(*dev, acc, stride=st, pad=pd)
+    assert np.array_equal(cg.to_host(acc), base + want)
+
+
+@pytest.mark.parametrize("M,N,K", [(4200, 512, 140), (257 * 128, 64, 129), (128 * 64 + 1, 256, 200)])
+def test_last_round_of_a_weight_gradient(cg, ro, wl, M, N, K):
+    say(f"split tail matmul_t M={M} N={N} K={K}")
+    ops = [wl.draw_ring((K, r), 9695 + i) for i, r in enumerate((M, M, N, N))]
+    z = torch.full((M, N), 77, dtype=torch.int64, device="cuda")
+    got = cg.cg_share_matmul_t(*[cg.to_device(a) for a in ops], True, True, z_i=z)
+    plain = cg.cg_share_matmul(*[cg.to_device(np.ascontiguousarray(a.T)) for a in ops])
+    assert torch.equal(got, plain)
+    want = ro.party_matmul(*[np.ascontiguousarray(a.T)[-130:] for a in ops[:2]], *[np.ascontiguousarray(a.T) for a in ops[2:]])
+    assert np.array_equal(cg.to_host(got[-130:].contiguous()), want)
