@@ -51,12 +51,12 @@ def ws_macs_per_triple(ws_bytes, digit_bytes, K):
 WORKLOAD_CONFIG = 4
 # HBM bytes on the config-4 step as it is timed by default, from the two rocprofv3 --pmc runs summarised in
 # profiles/share_gemm_config4_hbm_traffic.txt (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000 by the 1 GiB copy calibration): per
-# product kernel, the conversion to digit planes per layer that takes them, and all conversions, combinations and
+# layer call's product kernels, the conversion to digit planes per layer that takes them, and all conversions, combinations and
 # clearings of a step together.
-PROFILED_TRAFFIC_CONFIG4 = {"read_bytes_per_launch": 89.1e6, "write_bytes_per_launch": 29.5e6,
+PROFILED_TRAFFIC_CONFIG4 = {"read_bytes_per_launch": 76.5e6, "write_bytes_per_launch": 29.5e6,
                             "algorithmic_bytes_per_launch": 61.0e6,
                             "conversion_pass_per_scratch_route_layer": {"read_bytes": 34.8e6, "write_bytes": 34.7e6},
-                            "other_kernels_per_step": {"read_bytes": 634.5e6, "write_bytes": 856.0e6},
+                            "other_kernels_per_step": {"read_bytes": 598.3e6, "write_bytes": 855.7e6},
                             "source": "profiles/share_gemm_config4_hbm_traffic.txt"}
 
 
