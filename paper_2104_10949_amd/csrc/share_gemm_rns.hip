@@ -18,7 +18,7 @@
 // Measured on MI355X, whole calls, the better of the plain kernel and the digit planes against residues: 4096^3 3450 -> 2140 us,
 // 2048^3 456 -> 367, 3072 x 3072 x 1024 517 -> 418; 3x3 layers at batch 32: 16 x 16 x 256 -> 256 254 -> 179, 8 x 8 x 512 -> 512
 // 262 -> 181, the 5x5 one 628 -> 425.  At 4096^3: conversion 330 us (52 bytes per word pair at 5.2 TB/s: memory), product
-// 1670-1750 us (the matrix pipes are busy 78 % of the cycles, at 1.75 GHz: the clock that random operands leave), combination 90 us.
+// 1700-1780 us (the matrix pipes are busy 83 % of the cycles, at the clock that random operands leave), combination 90 us.
 // Where operands or outputs are large against M*N*K, or the grid leaves most of a round empty, the three passes cost
 // more than they save; the caller's rule compares both.
 #include "share_gemm_rns.h"
