@@ -252,19 +252,31 @@ def _ws(workspace) -> Tuple[int, int]:
 
 
 SCRATCH_LIMIT = 4 << 30   # bytes: a call that would take more runs without
+SCRATCH_SPARE = 8         # ... and so does one that would leave less than this part of the card's memory free
+
+
+def _scratch_fits(nbytes: int, device) -> bool:
+    """Whether the allocator can take nbytes without giving anything up for it.  Where memory is short it synchronises and
+    releases every cached block before it says so, on each call anew; a program near the card's capacity, or one that has limited
+    its own share, therefore is not asked for memory at all.  What is left free is for the blocks that the cache keeps per stream and
+    for the program's own next allocations, which must not meet the same release because of this one.  (6 us of host time.)"""
+    if torch.cuda.get_per_process_memory_fraction(device) < 1.0:
+        return False
+    free, total = torch.cuda.mem_get_info(device)
+    return nbytes <= free - total // SCRATCH_SPARE
 
 
 def _scratch(nbytes: int, device, stream) -> Optional[torch.Tensor]:
     """Scratch memory of one call, from torch's caching allocator: it belongs to the current stream and goes back to the
     allocator when the call returns, for later work of the same stream.  None, and the route without scratch memory, where the
-    call asks for none, runs on a stream that it names (whose order the allocator would not know), is being captured (the
-    graph would keep the memory), or where the memory is not to be had."""
+    call asks for none, names a stream, even the current one (the allocator would not know its order), is being captured (the
+    graph would keep the memory), or where memory is short."""
     if nbytes == 0 or nbytes > SCRATCH_LIMIT or stream is not None or device.index != torch.cuda.current_device() or \
-            torch.cuda.is_current_stream_capturing():
+            torch.cuda.is_current_stream_capturing() or not _scratch_fits(nbytes, device):
         return None
     try:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
-    except torch.OutOfMemoryError:
+    except torch.OutOfMemoryError:   # taken by someone else meanwhile
         return None
 
 

@@ -249,6 +249,38 @@ def test_input_gradient_without_scratch_of_its_own(cg, wl):
         assert torch.equal(dx, want)
 
 
+def test_input_gradient_where_memory_is_short(cg, wl, monkeypatch):
+    """A program that has no room for the scratch memory keeps its cached blocks: nothing is asked for, and nothing released."""
+    xs, ws, pd = (32, 16, 16, 256), (256, 3, 3, 256), (1, 1)
+    say("input gradient where memory is short")
+    dev = [cg.to_device(wl.draw_ring(s, 9280 + i)) for i, s in enumerate((xs, xs, ws, ws))]
+    want = cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd)
+    dx = torch.empty_like(want)
+    need, total = cg.cg_share_conv2d_dgrad_workspace_bytes(xs, ws, (1, 1), pd), torch.cuda.mem_get_info()[1]
+
+    def run():
+        dx.fill_(77)
+        torch.cuda.empty_cache()   # the block of a call before
+        del [torch.empty(64 << 20, dtype=torch.uint8, device="cuda")][0]   # a block of the program's own
+        before, stats = torch.cuda.memory_reserved(), torch.cuda.memory_stats()
+        cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd, dx_i=dx)
+        torch.cuda.synchronize()
+        after, taken = torch.cuda.memory_stats(), torch.cuda.memory_reserved() - before
+        assert all(after[k] == stats[k] for k in ("num_alloc_retries", "num_ooms"))
+        assert torch.equal(dx, want)
+        return taken
+
+    assert run() >= need   # there is room
+    torch.cuda.empty_cache()
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (96 << 20)) / total)
+        assert run() == 0
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda device=None: (total // 8 + need - 1, total))
+    assert run() == 0
+
+
 def test_scratch_of_the_digit_planes_is_still_enough(cg, wl):
     """A caller that brings no more than the digit planes take, or memory the route cannot use, gets the same words."""
     M, N, K = 2000, 2040, 2044
