@@ -266,6 +266,17 @@ def _scratch_fits(nbytes: int, device) -> bool:
     return nbytes <= free - total // SCRATCH_SPARE
 
 
+HIP_STREAM_CAPTURE_MODE_RELAXED = 2
+
+
+def _exchange_capture_mode(mode: int) -> Optional[int]:
+    """Sets the calling thread's stream capture mode and returns the one before, None if the runtime refuses.  While some thread
+    captures a graph in the default mode, an allocation by any thread that is not in the relaxed one fails and spoils that
+    capture.  (A call of the HIP runtime that the library is linked with; 0.2 us.)"""
+    value = ctypes.c_int(mode)
+    return value.value if lib().hipThreadExchangeStreamCaptureMode(ctypes.byref(value)) == 0 else None
+
+
 def _scratch(nbytes: int, device, stream) -> Optional[torch.Tensor]:
     """Scratch memory of one call, from torch's caching allocator: it belongs to the current stream and goes back to the
     allocator when the call returns, for later work of the same stream.  None, and the route without scratch memory, where the
@@ -274,10 +285,15 @@ def _scratch(nbytes: int, device, stream) -> Optional[torch.Tensor]:
     if nbytes == 0 or nbytes > SCRATCH_LIMIT or stream is not None or device.index != torch.cuda.current_device() or \
             torch.cuda.is_current_stream_capturing() or not _scratch_fits(nbytes, device):
         return None
+    mode = _exchange_capture_mode(HIP_STREAM_CAPTURE_MODE_RELAXED)
+    if mode is None:
+        return None
     try:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:   # taken by someone else meanwhile
         return None
+    finally:
+        _exchange_capture_mode(mode)
 
 
 def cg_share_matmul_ws(x_i, x_ip1, y_i, y_ip1, workspace, z_i=None, stream=None) -> torch.Tensor:

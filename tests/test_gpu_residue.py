@@ -3,6 +3,8 @@
 The route is taken where it is the faster one and the scratch memory holds it: cg_*_workspace_bytes then asks for more
 than the digit planes take.  Every output is compared with the plain kernel's, rows of it with the oracle's.
 """
+import threading
+
 import numpy as np
 import pytest
 
@@ -279,6 +281,46 @@ def test_input_gradient_where_memory_is_short(cg, wl, monkeypatch):
         torch.cuda.set_per_process_memory_fraction(1.0)
     monkeypatch.setattr(torch.cuda, "mem_get_info", lambda device=None: (total // 8 + need - 1, total))
     assert run() == 0
+
+
+def test_input_gradient_while_another_thread_captures(cg, wl):
+    """A capture in the default mode forbids allocations to every thread; the call is no part of it and leaves it valid."""
+    xs, ws, pd = (32, 16, 16, 256), (256, 3, 3, 256), (1, 1)
+    say("input gradient while another thread captures a graph")
+    dev = [cg.to_device(wl.draw_ring(s, 9290 + i)) for i, s in enumerate((xs, xs, ws, ws))]
+    want = cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd)
+    dx, counter = torch.empty_like(want), torch.zeros(64, dtype=torch.int64, device="cuda")
+    graph, side, errors = torch.cuda.CUDAGraph(), torch.cuda.Stream(), []
+    torch.cuda.synchronize()
+    capturing, called = threading.Event(), threading.Event()
+
+    def capture():
+        try:
+            with torch.cuda.graph(graph):   # (empties the allocator's cache: the call below has to allocate)
+                counter.add_(1)
+                capturing.set()
+                called.wait(30)
+                counter.add_(1)
+        except Exception as e:
+            errors.append(e)
+        finally:
+            capturing.set()
+    thread = threading.Thread(target=capture)
+    thread.start()
+    try:
+        assert capturing.wait(30)
+        with torch.cuda.stream(side):
+            cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd, dx_i=dx)
+    finally:
+        called.set()
+        thread.join()
+    assert not errors, errors
+    torch.cuda.synchronize()
+    assert torch.equal(dx, want)
+    for i in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bool((counter == 2 * (i + 1)).all())
 
 
 def test_scratch_of_the_digit_planes_is_still_enough(cg, wl):

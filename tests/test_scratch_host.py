@@ -10,7 +10,13 @@ NBYTES = 1 << 30
 @pytest.fixture
 def card(monkeypatch):
     """A card that is not there: what the decision asks about it, and the allocations that it makes."""
-    state = {"free": TOTAL, "fraction": 1.0, "capturing": False, "current": 0, "allocated": []}
+    from paper_2104_10949_amd import binding as b
+    state = {"free": TOTAL, "fraction": 1.0, "capturing": False, "current": 0, "allocated": [], "mode": 0}
+
+    def exchange(mode):
+        before, state["mode"] = state["mode"], mode
+        return before
+    monkeypatch.setattr(b, "_exchange_capture_mode", exchange)
     monkeypatch.setattr(torch.cuda, "mem_get_info", lambda device=None: (state["free"], TOTAL))
     monkeypatch.setattr(torch.cuda, "get_per_process_memory_fraction", lambda device=None: state["fraction"])
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["capturing"])
@@ -18,7 +24,7 @@ def card(monkeypatch):
     real_empty = torch.empty
 
     def empty(n, dtype=None, device=None):
-        state["allocated"].append(n)
+        state["allocated"].append((n, state["mode"]))
         return real_empty(8, dtype=dtype)
     monkeypatch.setattr(torch, "empty", empty)
     return state
@@ -28,7 +34,8 @@ def takes(state, nbytes=NBYTES, stream=None):
     from paper_2104_10949_amd import binding as b
     state["allocated"].clear()
     taken = b._scratch(nbytes, torch.device("cuda", 0), stream) is not None
-    assert state["allocated"] == ([nbytes] if taken else [])   # nothing is asked for where nothing is used
+    # nothing is asked for where nothing is used; what is asked for, in the relaxed capture mode, and the thread's own is back after it
+    assert state["allocated"] == ([(nbytes, b.HIP_STREAM_CAPTURE_MODE_RELAXED)] if taken else []) and state["mode"] == 0
     return taken
 
 
