@@ -1109,10 +1109,9 @@ cg_status run_planes(Plan& pl, void* workspace, size_t workspace_bytes, void* st
 // The residue route where it pays and the scratch memory holds it; *taken says whether it was.
 cg_status run_residues(const Plan& pl, void* workspace, size_t workspace_bytes, void* stream, bool* taken) {
     *taken = false;
-    const Residues res = plan_residues(pl);
+    Residues res = plan_residues(pl);
     if (!res.pay || !workspace || !aligned(workspace, 16)) return CG_OK;
-    const u64 need = cg::rns_workspace_bytes(res.p);
-    if (workspace_bytes < need || workspace_overlaps(pl, workspace, need)) return CG_OK;
+    if (!cg::rns_fit(&res.p, workspace_bytes) || workspace_overlaps(pl, workspace, cg::rns_workspace_bytes(res.p))) return CG_OK;
     *taken = true;
     const hipError_t e = cg::launch_share_gemm_rns(res.p, workspace, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? CG_OK : CG_ERR_DEVICE;

@@ -47,6 +47,9 @@ struct RnsParams {
 bool rns_plan(RnsParams* p);
 // Bytes of scratch memory: xp, wp and rp one after the other, each from a multiple of 256 on.
 uint64_t rns_workspace_bytes(const RnsParams& p);
+// Can a planned call run in this much memory?  Moduli on the large tile pad the result's planes to multiples of 256; a caller who
+// brings what the small tile alone takes, where that is the better one of both, gets all moduli on it.
+bool rns_fit(RnsParams* p, uint64_t bytes);
 hipError_t launch_share_gemm_rns(RnsParams p, void* workspace, hipStream_t stream);
 
 }  // namespace cg

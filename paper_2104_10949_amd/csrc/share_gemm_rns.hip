@@ -555,6 +555,31 @@ hipError_t run(const RnsParams& p, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// The first `large` moduli on the large tile and the others on the small one
+void set_parts(RnsParams* p, int large) {
+    auto set = [&](RnsPart& part, int edge, int first, int count) {
+        part.tiles_m = (int)((p->M + (int64_t)edge - 1) / edge);
+        part.tiles_n = (int)((p->N + (int64_t)edge - 1) / edge);
+        part.first = first; part.count = count;
+    };
+    set(p->large, 256, 0, large);
+    set(p->small, 128, large, p->nmod - large);
+}
+
+// ... and all that follows from it
+void share_moduli(RnsParams* p, int large) {
+    set_parts(p, large);
+    for (RnsPart* part : {&p->large, &p->small}) {
+        part->div_tiles = make_fast_div((uint32_t)(part->tiles_m * part->tiles_n));
+        part->div_group = make_fast_div((uint32_t)(GROUP_M * part->tiles_n));
+    }
+    const RnsPart& pitch = large > 0 ? p->large : p->small;   // the result's planes hold whole tiles of the larger size
+    const int edge = large > 0 ? 256 : 128;
+    p->blocks_n = pitch.tiles_n * (edge / 16);
+    p->div_blocks_n = make_fast_div((uint32_t)p->blocks_n);
+    p->r_plane = (uint64_t)pitch.tiles_m * pitch.tiles_n * edge * edge;
+}
+
 }  // namespace
 
 bool rns_plan(RnsParams* p) {
@@ -610,11 +635,6 @@ bool rns_plan(RnsParams* p) {
     static const Split splits[3][2] = {{{0.714, 0.715, 8.2, 0.0}, {0.300, 0.637, 2.9, 0.033}},
                                        {{0.932, 0.208, 8.2, 0.0}, {0.527, 0.204, 3.7, 0.0}},
                                        {{0.872, 0.384, 8.1, 0.053}, {0.443, 0.465, 4.05, 0.020}}};
-    auto set = [&](RnsPart& part, int edge, int first, int count) {
-        part.tiles_m = (int)((p->M + (int64_t)edge - 1) / edge);
-        part.tiles_n = (int)((p->N + (int64_t)edge - 1) / edge);
-        part.first = first; part.count = count;
-    };
     auto cost = [&](const RnsPart& part, const Split& t, int slots) {
         if (part.count == 0) return 0.0;
         const int64_t blocks = (int64_t)part.tiles_m * part.tiles_n * part.count, rounds = (blocks + slots - 1) / slots;
@@ -625,39 +645,33 @@ bool rns_plan(RnsParams* p) {
     int best_large = 0;
     best = 0.0;
     for (int large = 0; large <= p->nmod; ++large) {
-        set(p->large, 256, 0, large);
-        set(p->small, 128, large, p->nmod - large);
+        set_parts(p, large);
         const double us = cost(p->large, splits[kind][0], 256) + cost(p->small, splits[kind][1], 512);
         if (large > 0 && us >= best) continue;
         best = us;
         best_large = large;
     }
-    set(p->large, 256, 0, best_large);
-    set(p->small, 128, best_large, p->nmod - best_large);
-    for (RnsPart* part : {&p->large, &p->small}) {
-        part->div_tiles = make_fast_div((uint32_t)(part->tiles_m * part->tiles_n));
-        part->div_group = make_fast_div((uint32_t)(GROUP_M * part->tiles_n));
-    }
-    const RnsPart& pitch = best_large > 0 ? p->large : p->small;   // the result's planes hold whole tiles of the larger size
-    const int edge = best_large > 0 ? 256 : 128;
-    p->blocks_n = pitch.tiles_n * (edge / 16);
+    share_moduli(p, best_large);
     // An XCD reads the whole right operand once per GROUP_M tile rows, eight moduli's at a time where every XCD has a run of
     // its own.  The last-level cache of 256 MB holds eight of up to some 20 MB; beyond, the XCDs take one modulus
     // together: 34 MB (4096^3) 2154 -> 2097 us, 8192 x 8192 x 2048 4466 -> 4294, 22 MB (2048 x 2048 x 5400) 863 -> 856, 17 MB 1178 / 1178 at
     // 4096 x 4096 x 2048 and 2446 / 2557 at 8192 x 8192 x 1024, 6 MB (3072 x 3072 x 1024) 411 / 422.
     p->by_rounds = p->w_plane >= (20u << 20);
-    p->r_plane = (uint64_t)pitch.tiles_m * pitch.tiles_n * edge * edge;
     p->div_slices = make_fast_div((uint32_t)p->slices);
     p->div_taps = make_fast_div((uint32_t)taps);
     p->div_n = make_fast_div((uint32_t)p->N);
     p->div_howo = make_fast_div((uint32_t)(p->conv ? p->Ho * p->Wo : 1));
     p->div_wo = make_fast_div((uint32_t)(p->conv ? p->Wo : 1));
-    p->div_blocks_n = make_fast_div((uint32_t)p->blocks_n);
     return true;
 }
 
 uint64_t rns_workspace_bytes(const RnsParams& p) {
     return up256(p.x_plane * p.nmod) + up256(p.w_plane * p.nmod) + up256(p.r_plane * p.nmod);
+}
+
+bool rns_fit(RnsParams* p, uint64_t bytes) {
+    if (bytes < rns_workspace_bytes(*p) && p->tile == 128) share_moduli(p, 0);
+    return bytes >= rns_workspace_bytes(*p);
 }
 
 hipError_t launch_share_gemm_rns(RnsParams p, void* workspace, hipStream_t stream) {

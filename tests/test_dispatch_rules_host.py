@@ -24,12 +24,15 @@ int main(int argc, char** argv) {
         } else if (!strncmp(argv[1], "residue", 7)) {   // M N words x_rows gathered kh kw stride_h stride_w
             cg::RnsParams p = {};
             p.M = (int)a[0]; p.N = (int)a[1]; p.words = (int)a[2]; p.x_rows = (int)a[3]; p.conv = (int)a[4];
-            p.kh = (int)a[5]; p.kw = (int)a[6]; p.sh = (int)a[7]; p.sw = (int)a[8];
+            p.kh = (int)a[5]; p.kw = (int)a[6]; p.sh = (int)a[7]; p.sw = !strcmp(argv[1], "residue_fit") ? p.sh : (int)a[8];
             p.Ho = p.Wo = 1;
             const bool fits = cg::rns_plan(&p);
             if (!strcmp(argv[1], "residue_shares"))   // moduli on the large tile, on the small one, and the first of each
                 printf("%d %d %d %d %d\n", p.large.count, p.small.count, p.large.first, p.small.first, p.nmod);
-            else
+            else if (!strcmp(argv[1], "residue_fit")) {   // a[8]: bytes at hand; fits or not, moduli on the large tile, bytes taken
+                const bool held = fits && cg::rns_fit(&p, (unsigned long long)a[8]);
+                printf("%d %d %llu\n", held, held ? p.large.count : -1, held ? (unsigned long long)cg::rns_workspace_bytes(p) : 0ull);
+            } else
                 printf("%d %d %llu\n", fits ? p.tile : 0, p.nmod, fits ? (unsigned long long)cg::rns_workspace_bytes(p) : 0ull);
         } else {   // small: M N K accumulate
             cg::GemmParams p = {};
@@ -128,6 +131,24 @@ def test_every_modulus_runs_on_one_tile_and_the_residue_tests_reach_all_shares(r
         assert large >= 0 and small >= 0 and large + small == nmod and (first_large, first_small) == (0, large), row
         seen.add((large > 0, small > 0, row[4]))
     assert seen == {(large, small, gathered) for large, small in ((True, False), (False, True), (True, True)) for gathered in (0, 1)}
+
+
+def test_memory_for_the_small_tile_alone_is_enough_where_it_is_the_better_one(rules):
+    """A mix of both tiles pads the result's planes to multiples of 256; a call with a little less runs on the small tile alone."""
+    from tests import test_gpu_residue as t
+    rows = [(M, N, K, M, 0, 1, 1, 1, 1) for M, N, K in t.SHAPES + t.SMALL_TILE_SHAPES + [(893, 1949, 2505), (1403, 1870, 1271)]]
+    mixed = 0
+    for row, (tile, _, need), (large, *_) in zip(rows, rules("residues", rows), rules("residue_shares", rows)):
+        small = t.small_tile_bytes(*row[:4], 1)
+        ask = lambda nbytes: rules("residue_fit", [row[:8] + (nbytes,)])[0]
+        assert ask(need) == ask(need + 1) == (1, large, need), row
+        if tile == 128 and small < need:
+            mixed += 1
+            assert ask(need - 1) == ask(small) == (1, 0, small), row
+        else:
+            assert tile == 256 or small == need, row
+        assert ask(min(need, small) - 1) == (0, -1, 0) and (tile == 128 or ask(need - 1) == (0, -1, 0)), row
+    assert mixed >= 4
 
 
 # Taken or not, and whole calls in microseconds without residues and with them on either tile (256, 128).

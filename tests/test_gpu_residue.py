@@ -397,3 +397,38 @@ def test_captured(cg, wl):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(z, want)
+
+
+def small_tile_bytes(M, N, words, x_rows, taps):
+    """What the route takes with every modulus on the small tile: operands' planes, and the result's in whole tiles of 128."""
+    up = lambda v, a: -(-v // a) * a
+    nmod, line = 18 if taps * words <= 5500 else 19, -(-words // 64) * 128
+    return up((x_rows + 1) * line * nmod, 256) + up(N * taps * line * nmod, 256) + up(up(M, 128) * up(N, 128) * nmod, 256)
+
+
+def check_small_tile_scratch(plain, call, need, small):
+    """With that much memory, where the call asks for a little more, the residues still run: the result's planes that end there
+    are written, and nothing behind them.  With less they do not."""
+    assert small < need and small % 16 == 0
+    for nbytes, taken in ((need - 16, True), (small, True), (small - 16, False)):
+        buf = poisoned(need + 512)
+        got = call(buf[:nbytes // 8])
+        assert torch.equal(got, plain)
+        assert bool((buf[small // 8 - 64:small // 8] == 0x5A5A5A5A5A5A5A5A).all()) == (not taken), nbytes
+        assert bool((buf[nbytes // 8:] == 0x5A5A5A5A5A5A5A5A).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(1214, 1361, 957), (1167, 1361, 3048)])
+def test_scratch_of_the_small_tile_is_still_enough(cg, wl, M, N, K):
+    say(f"residue route with the small tile's scratch memory M={M} N={N} K={K}")
+    dev = [cg.to_device(wl.draw_ring((r, K), 9410 + i)) for i, r in enumerate((M, M, N, N))]
+    check_small_tile_scratch(cg.cg_share_matmul(*dev), lambda ws: cg.cg_share_matmul_ws(*dev, ws),
+                             cg.cg_share_matmul_workspace_bytes(M, N, K), small_tile_bytes(M, N, K, M, 1))
+
+
+def test_scratch_of_the_small_tile_is_still_enough_for_a_layer(cg, wl):
+    xs, ws = (4, 25, 25, 112), (624, 3, 3, 112)
+    say(f"residue route with the small tile's scratch memory x={xs} w={ws}")
+    dev = [cg.to_device(wl.draw_ring(s, 9420 + i)) for i, s in enumerate((xs, xs, ws, ws))]
+    check_small_tile_scratch(cg.cg_share_conv2d(*dev, pad=(1, 1)), lambda w: cg.cg_share_conv2d_ws(*dev, w, pad=(1, 1)),
+                             cg.cg_share_conv2d_workspace_bytes(xs, ws, (1, 1), (1, 1)), small_tile_bytes(4 * 625, 624, 112, 4 * 625, 9))
