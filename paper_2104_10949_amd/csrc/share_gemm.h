@@ -119,10 +119,10 @@ hipError_t launch_share_gemm_small(const GemmParams& p, hipStream_t stream);
 
 // Gradients of fully connected layers at small batch (share_gemm_small.hip): both operands stored transposed (A_TRANS, B_TRANS) and
 // one slice of K; few rows on the left, row-major with 16-byte loads, and the right operand stored transposed (A_LINEAR_VEC, B_TRANS),
-// with its modelled time in microseconds (0: does not apply).
+// where that applies and is modelled as the faster one.
 bool share_gemm_outer_applies(const GemmParams& p);
 hipError_t launch_share_gemm_outer(const GemmParams& p, hipStream_t stream);
-double share_gemm_rows_t_us(const GemmParams& p);
+bool share_gemm_rows_t_pays(const GemmParams& p);
 hipError_t launch_share_gemm_rows_t(const GemmParams& p, hipStream_t stream);
 
 // The same product of row-major x [M, K] and w [N, K] on the float64 matrix instruction with

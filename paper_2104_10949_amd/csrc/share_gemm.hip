@@ -48,7 +48,7 @@
 #include <type_traits>
 
 #include "share_digits.h"
-#include "share_gemm.h"
+#include "share_gemm_split.h"
 
 #ifdef CG_INST_GROUP
 #define CG_G0 (CG_INST_GROUP == 0)
@@ -1413,49 +1413,6 @@ static __global__ __launch_bounds__(256) void zero_tiles_kernel(const GemmParams
 template <class T, int AMODE, int BMODE>
 static hipError_t launch(const GemmParams& p, hipStream_t stream);
 
-// Blocks that run at one time: a block's LDS leaves room for one block per compute unit.
-static constexpr int ROUND_BLOCKS = 256;
-// A K range of a split holds at least this many slices.
-static constexpr int SPLIT_MIN_SLICES = 2;
-// Cost of the fixed part of a block (prologue, fold of the accumulators into z), in
-// units of one K slice of the main loop, with a plain store and with atomic adds.
-static constexpr double SPLIT_COST_PLAIN = 1.0, SPLIT_COST_ATOMIC = 2.0;
-// The streamed distribution must beat the classic one by this factor of modelled time to be used, by a little more where the
-// right operand comes in 8-byte loads (1000 x 777 x 1531, 0.858: 95 us streamed, 88 classic; of 250 odd products none is slower
-// than before with 0.84, and all together take 0.91 of the time).
-static constexpr double STREAM_MARGIN = 0.88, STREAM_MARGIN_SCALAR = 0.84;
-// A last round that is at most half full shares its tiles out over all compute units where that shortens it by this many slices
-// (a launch that clears the tiles and the atomic adds cost about two).
-static constexpr int TAIL_MIN_SAVING = 3;
-// Several rounds of unsplit tiles of at most this many slices are run as one round of blocks that
-// each walk through whole tiles.
-static constexpr int PERSIST_MAX_SLICES = 32;
-
-static int choose_ksplit(int64_t tiles, int nk) {
-    // A block's 160 KB of LDS leaves room for one block per compute unit, so a grid runs
-    // in rounds of 256 blocks and the last round costs as much as a full one.  Splitting
-    // K makes the blocks shorter, which fills the chip when the tiles alone cannot and
-    // shrinks the idle part of the last round otherwise.  The split count with the least
-    // modelled time wins: rounds * (slices per block + fixed cost per block).
-    const int units = ROUND_BLOCKS;
-    int64_t max_split = 8 * units / tiles;  // at most eight rounds' worth of blocks
-    if (max_split > nk / SPLIT_MIN_SLICES) max_split = nk / SPLIT_MIN_SLICES;
-    int best = 1;
-    double best_cost = 0;
-    for (int64_t ks = 1; ks <= (max_split < 1 ? 1 : max_split); ++ks) {
-        const int64_t per = (nk + ks - 1) / ks;
-        const int64_t eff = (nk + per - 1) / per;  // no empty splits
-        if (eff != ks) continue;
-        const int64_t rounds = (tiles * eff + units - 1) / units;
-        const double cost = (double)rounds * ((double)per + (eff > 1 ? SPLIT_COST_ATOMIC : SPLIT_COST_PLAIN));
-        if (ks == 1 || cost < best_cost * 0.97) {  // a split must pay for itself by a margin
-            best = (int)eff;
-            best_cost = cost;
-        }
-    }
-    return best;
-}
-
 // Tile-rows per launch-order group.  An XCD's run of `run` consecutive tiles covers
 // rows x cols tiles and fetches that many tile-rows of the left operand's tensor and
 // tile-columns of the right operand's (of the split's K range); the group height that
@@ -1540,102 +1497,18 @@ hipError_t launch_to_planes(const GemmParams& p, int64_t x_rows, int64_t x_k, hi
 }
 #endif
 
-// Modelled time of the classic distribution with `ks` splits, in K slices (see choose_ksplit).
-static double classic_cost(int64_t tiles, int nk, int ks) {
-    const int64_t per = (nk + ks - 1) / ks;
-    const int64_t rounds = (tiles * ks + ROUND_BLOCKS - 1) / ROUND_BLOCKS;
-    return (double)rounds * ((double)per + (ks > 1 ? SPLIT_COST_ATOMIC : SPLIT_COST_PLAIN));
-}
-
-// The streamed distribution is compiled for the address generators of the large layers only.
-template <int AMODE, int BMODE>
-struct CanStream {
-    static constexpr bool value = (AMODE == A_LINEAR_VEC && BMODE == B_VEC) || (AMODE == A_LINEAR_SCALAR && BMODE == B_SCALAR) ||
-                                  (AMODE == A_CONV_C32 && BMODE == B_VEC) ||
-                                  (AMODE == A_CONV_C32 && BMODE == B_FLIP_C32) || (AMODE == A_TRANS && BMODE == B_PATCH_T) ||
-                                  (AMODE == A_PATCH_T && BMODE == B_TRANS);
-};
-
-// The weight gradient's classic instantiation spills registers inside the loop (its streamed one does not,
-// and is 7 % faster on the same ranges over the VGG-shaped layers): only the streamed one is built.  The input
-// gradient keeps both: its unsplit tiles gain more from the classic order's neighbouring tiles per XCD.
-template <int AMODE, int BMODE>
-struct StreamOnly {
-    static constexpr bool value = (AMODE == A_TRANS && BMODE == B_PATCH_T) || (AMODE == A_PATCH_T && BMODE == B_TRANS);
-};
-
-// The split tail is compiled where a product of a few slices per tile and no streamed instantiation is ordinary work: general gathers
-// (first layers) and the gradients of fully connected layers.  An instantiation of its own: the selects that find a block's part
-// cost the others 0.3 - 0.5 us a call.  7x7 stem on 224 x 224 x 3, batch 8, 784 tiles of five slices: 87.5 -> 80 us; weight gradient
-// 4200 x 512 x 256, 264 tiles of eight: 62 -> 44.
-template <int AMODE, int BMODE>
-struct CanTail {
-    static constexpr bool value = AMODE == A_CONV_GEN && BMODE != B_FLIP_GEN;
-    static_assert(!value || !CanStream<AMODE, BMODE>::value, "a streamed instantiation spreads the slices itself");
-};
-template <>
-struct CanTail<A_TRANS, B_TRANS> {
-    static constexpr bool value = true;
-};
-
 template <class T, int AMODE, int BMODE>
 static hipError_t launch(const GemmParams& p, hipStream_t stream) {
     const int64_t tiles_m = (p.M + T::BM - 1) / T::BM, tiles_n = (p.N + T::BN - 1) / T::BN;
     const int64_t tiles = tiles_m * tiles_n;
     const int nk = (p.K + 31) / 32;
     GemmParams q = p;
-    q.ksplit = choose_ksplit(tiles, nk);
-    q.stream_per = 0;
-    unsigned grid = (unsigned)(tiles * q.ksplit);
-    // Streamed distribution: one block per compute unit, each taking an equal run of (tile, slice)
-    // units.  A block pays the fixed cost once per tile its run touches (about per/nk + 1 of them).
-    // Worth it when the classic grid leaves a round partly empty.
-    const int64_t units = tiles * nk;
-    if (CanStream<AMODE, BMODE>::value && units >= 3 * ROUND_BLOCKS && units < ((int64_t)1 << 40)) {
-        const int64_t per = (units + ROUND_BLOCKS - 1) / ROUND_BLOCKS;
-        const double streamed = (double)per + SPLIT_COST_ATOMIC * ((double)per / nk + 1.0);
-        constexpr double margin = BMODE == B_SCALAR ? STREAM_MARGIN_SCALAR : STREAM_MARGIN;
-        if (streamed < margin * classic_cost(tiles, nk, q.ksplit)) {
-            q.stream_per = per;
-            q.ksplit = 2;  // any value above 1: the folds add atomically into a zero-filled z
-            grid = (unsigned)((units + per - 1) / per);
-        }
-    }
-    // Whole tiles streamed: when the classic grid needs several rounds of unsplit tiles with a short K, one
-    // block per compute unit walks through an equal run of whole tiles instead.  The kernel's pipeline then
-    // runs on from tile to tile (no prologue, no block launch in between) and every tile is still stored
-    // plainly.  Measured: 3-9 % on layers of up to 16 slices; with a long K the fixed part of a tile does not
-    // matter and the classic order, which keeps the tiles an XCD runs at one time next to each other, is
-    // 1-2 % faster.
-    // Row-major left operands only: a patch gather re-reads the rows of neighbouring tiles, which hit in L2
-    // when the neighbours run at the same time and miss when one block takes them one after the other
-    // (measured on the 3x3 layers of the VGG-shaped step: twice the memory reads for 1-3 % of time).
-    if (CanStream<AMODE, BMODE>::value && (AMODE == A_LINEAR_VEC || AMODE == A_LINEAR_SCALAR) && q.stream_per == 0 && q.ksplit == 1 &&
-        tiles > ROUND_BLOCKS && nk <= PERSIST_MAX_SLICES) {
-        const int64_t tiles_per_block = (tiles + ROUND_BLOCKS - 1) / ROUND_BLOCKS;
-        q.stream_per = tiles_per_block * nk;
-        grid = (unsigned)((tiles + tiles_per_block - 1) / tiles_per_block);
-    }
-    // The weight gradient runs the streamed kernel also where the classic distribution is the better one: a
-    // run of one split's slices is that distribution, tile after tile instead of split after split.
-    if (StreamOnly<AMODE, BMODE>::value && q.stream_per == 0) {
-        q.stream_per = (nk + q.ksplit - 1) / q.ksplit;
-        grid = (unsigned)((units + q.stream_per - 1) / q.stream_per);
-    }
-    // Split tail: several rounds of unsplit tiles whose last one is at most half full
-    q.tail_tiles = 0;
-    const int64_t tail = tiles % ROUND_BLOCKS;
-    if (CanTail<AMODE, BMODE>::value && q.stream_per == 0 && q.ksplit == 1 && tiles > ROUND_BLOCKS && tail > 0 && tail <= ROUND_BLOCKS / 2) {
-        int64_t parts = ROUND_BLOCKS / tail < nk ? ROUND_BLOCKS / tail : nk;
-        const int64_t per = (nk + parts - 1) / parts;
-        parts = (nk + per - 1) / per;
-        if (nk - per >= TAIL_MIN_SAVING) {
-            q.tail_first = (int)(tiles - tail);
-            q.tail_tiles = (int)tail; q.tail_per = (int)per;
-            q.div_tail = make_fast_div((uint32_t)tail);
-            grid = (unsigned)(q.tail_first + tail * parts);
-        }
-    }
+    const WorkSplit split = split_work<AMODE, BMODE>(tiles, nk);
+    q.ksplit = split.ksplit;
+    q.stream_per = split.stream_per;
+    q.tail_first = split.tail_first; q.tail_tiles = split.tail_tiles; q.tail_per = split.tail_per;
+    q.div_tail = make_fast_div((uint32_t)(split.tail_tiles < 1 ? 1 : split.tail_tiles));
+    const unsigned grid = split.grid;
     constexpr bool MATRIX_PAIR =
         (AMODE == A_LINEAR_VEC || AMODE == A_LINEAR_SCALAR || AMODE == A_LINEAR_WIDE || AMODE == A_PLANES) &&
         (BMODE == B_VEC || BMODE == B_SCALAR || BMODE == B_WIDE || BMODE == B_PLANES);
@@ -1715,25 +1588,11 @@ hipError_t launch_share_gemm_group1(const GemmParams& p, int amode, int bmode, h
 }
 #endif
 #if CG_G2
-// Few rows against a transposed right operand: both kernels' modelled times, this file's in the terms of its launcher (slices in
-// rounds, rounds, megabytes of right operand; over the same 692 shapes nine in ten within 13 %).  The calls together 17.6 ms -> 13.96,
-// 13.94 with the better kernel each time; one of the 411 taken is slower, by 10 %.
-static bool few_rows_pay(const GemmParams& p) {
-    const double few = share_gemm_rows_t_us(p);
-    if (few == 0.0) return false;
-    const int64_t rows = (p.M + (int64_t)127) / 128, tiles = rows * ((p.N + (int64_t)63) / 64);
-    const int nk = (p.K + 31) / 32, ks = choose_ksplit(tiles, nk);
-    const double tiled = 2.42 * classic_cost(tiles, nk, ks) + (ks > 1 ? 0.4 : 0.0) +
-                         1.92 * (double)((tiles * ks + ROUND_BLOCKS - 1) / ROUND_BLOCKS) +
-                         0.124 * 16.0e-6 * (double)rows * (double)p.N * (double)p.K;
-    return few < 0.95 * tiled;
-}
-
 hipError_t launch_share_gemm_group2(const GemmParams& p, int amode, int bmode, hipStream_t stream, bool* found) {
     typedef DefaultStepTile T;
     *found = true;
     if (amode == A_TRANS && bmode == B_TRANS && share_gemm_outer_applies(p)) return launch_share_gemm_outer(p, stream);
-    if (amode == A_LINEAR_VEC && bmode == B_TRANS && few_rows_pay(p)) return launch_share_gemm_rows_t(p, stream);
+    if (amode == A_LINEAR_VEC && bmode == B_TRANS && share_gemm_rows_t_pays(p)) return launch_share_gemm_rows_t(p, stream);
     CG_CASE(A_LINEAR_VEC, B_TRANS);
     CG_CASE(A_LINEAR_SCALAR, B_TRANS);
     CG_CASE(A_TRANS, B_VEC);

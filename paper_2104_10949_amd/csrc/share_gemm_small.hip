@@ -17,7 +17,7 @@
 #include <stdint.h>
 
 #include "share_digits.h"
-#include "share_gemm.h"
+#include "share_gemm_split.h"
 
 namespace cg {
 namespace {
@@ -504,13 +504,27 @@ hipError_t launch_share_gemm_outer(const GemmParams& p, hipStream_t stream) {
 
 // Modelled time in microseconds, or 0 where the kernel does not apply: turns of a wave times rounds of the chip, and the right
 // operand once per group of rows (fitted over 692 shapes of M 2 .. 300, N 10 .. 16384, K 8 .. 8192, nine in ten within 8 %).
-double share_gemm_rows_t_us(const GemmParams& p) {
+static double rows_t_us(const GemmParams& p) {
     const int64_t nk = (p.K + (int64_t)31) / 32;
     if (p.lda != p.K || p.z_add || p.M > 512 || nk > 511 * 4 || p.N % 2 != 0 || p.N >= (1 << 21) || !pairs_aligned(p.w_a, p.w_b)) return 0.0;
     const int64_t groups = p.M <= 16 ? 1 : (p.M + 31) / 32, blocks = (p.N + (int64_t)31) / 32 * groups;
     const double turns = (double)((nk + 3) / 4), rounds = (double)((blocks + 255) / 256);
     const double mb = 16.0e-6 * (double)groups * (double)p.N * (double)p.K;
     return p.M <= 16 ? 1.1 + rounds * (1.87 * turns + 1.28) + 0.080 * mb : 1.2 + rounds * (2.69 * turns + 2.27) + 0.083 * mb;
+}
+
+// Few rows against a transposed right operand: both kernels' modelled times, the tiled one's in the terms of its launcher (slices in
+// rounds, rounds, megabytes of right operand; over the same 692 shapes nine in ten within 13 %).  The calls together 17.6 ms -> 13.96,
+// 13.94 with the better kernel each time; one of the 411 taken is slower, by 10 %.
+bool share_gemm_rows_t_pays(const GemmParams& p) {
+    const double few = rows_t_us(p);
+    if (few == 0.0) return false;
+    const int64_t rows = (p.M + (int64_t)127) / 128, tiles = rows * ((p.N + (int64_t)63) / 64);
+    const int nk = (p.K + 31) / 32, ks = choose_ksplit(tiles, nk);
+    const double tiled = 2.42 * classic_cost(tiles, nk, ks) + (ks > 1 ? 0.4 : 0.0) +
+                         1.92 * (double)((tiles * ks + ROUND_BLOCKS - 1) / ROUND_BLOCKS) +
+                         0.124 * 16.0e-6 * (double)rows * (double)p.N * (double)p.K;
+    return few < 0.95 * tiled;
 }
 
 hipError_t launch_share_gemm_rows_t(const GemmParams& p, hipStream_t stream) {

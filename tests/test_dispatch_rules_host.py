@@ -15,6 +15,10 @@ PROGRAM = r"""
 #include "prf.h"
 #include "share_gemm.h"
 #include "share_gemm_rns.h"
+#include "share_gemm_split.h"
+static void print_split(const cg::WorkSplit& s) {
+    printf("%d %lld %d %d %d %u\n", s.ksplit, (long long)s.stream_per, s.tail_first, s.tail_tiles, s.tail_per, s.grid);
+}
 int main(int argc, char** argv) {
     long long a[9];
     while (scanf("%lld %lld %lld %lld %lld %lld %lld %lld %lld", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6, a + 7, a + 8) == 9) {
@@ -27,17 +31,24 @@ int main(int argc, char** argv) {
             p.kh = (int)a[5]; p.kw = (int)a[6]; p.sh = (int)a[7]; p.sw = !strcmp(argv[1], "residue_fit") ? p.sh : (int)a[8];
             p.Ho = p.Wo = 1;
             const bool fits = cg::rns_plan(&p);
-            if (!strcmp(argv[1], "residue_shares"))   // moduli on the large tile, on the small one, and the first of each
-                printf("%d %d %d %d %d\n", p.large.count, p.small.count, p.large.first, p.small.first, p.nmod);
+            if (!strcmp(argv[1], "residue_shares"))   // moduli on the large tile, on the small one, the first of each; XCDs in step
+                printf("%d %d %d %d %d %d\n", p.large.count, p.small.count, p.large.first, p.small.first, p.nmod, p.by_rounds);
             else if (!strcmp(argv[1], "residue_fit")) {   // a[8]: bytes at hand; fits or not, moduli on the large tile, bytes taken
                 const bool held = fits && cg::rns_fit(&p, (unsigned long long)a[8]);
                 printf("%d %d %llu\n", held, held ? p.large.count : -1, held ? (unsigned long long)cg::rns_workspace_bytes(p) : 0ull);
             } else
                 printf("%d %d %llu\n", fits ? p.tile : 0, p.nmod, fits ? (unsigned long long)cg::rns_workspace_bytes(p) : 0ull);
-        } else {   // small: M N K accumulate
+        } else if (!strcmp(argv[1], "split_odd_rows")) {   // M N K
+            print_split(cg::split_work<cg::A_LINEAR_SCALAR, cg::B_SCALAR>((a[0] + 127) / 128 * ((a[1] + 63) / 64), (int)((a[2] + 31) / 32)));
+        } else if (!strcmp(argv[1], "split_gather")) {
+            print_split(cg::split_work<cg::A_CONV_GEN, cg::B_SCALAR>((a[0] + 127) / 128 * ((a[1] + 63) / 64), (int)((a[2] + 31) / 32)));
+        } else if (!strcmp(argv[1], "split_transposed")) {
+            print_split(cg::split_work<cg::A_TRANS, cg::B_TRANS>((a[0] + 127) / 128 * ((a[1] + 63) / 64), (int)((a[2] + 31) / 32)));
+        } else {   // small, outer, rows_t: M N K accumulate
             cg::GemmParams p = {};
             p.M = (int)a[0]; p.N = (int)a[1]; p.K = p.lda = (int)a[2]; p.z_add = (int)a[3];
-            printf("%d\n", cg::share_gemm_small_applies(p) ? 1 : 0);
+            printf("%d\n", (!strcmp(argv[1], "outer") ? cg::share_gemm_outer_applies(p) :
+                            !strcmp(argv[1], "rows_t") ? cg::share_gemm_rows_t_pays(p) : cg::share_gemm_small_applies(p)) ? 1 : 0);
         }
     }
 }
@@ -127,7 +138,7 @@ def test_every_modulus_runs_on_one_tile_and_the_residue_tests_reach_all_shares(r
     layers = [(xs, ws, (s, s), (p, p)) for xs, ws, s, p in t.CONVS] + t.GATHERS
     rows = [(M, N, K, M, 0, 1, 1, 1, 1) for M, N, K in t.SHAPES + t.SMALL_TILE_SHAPES] + [_residue_row(*l) for l in layers]
     seen = set()
-    for row, (large, small, first_large, first_small, nmod) in zip(rows, rules("residue_shares", rows)):
+    for row, (large, small, first_large, first_small, nmod, _) in zip(rows, rules("residue_shares", rows)):
         assert large >= 0 and small >= 0 and large + small == nmod and (first_large, first_small) == (0, large), row
         seen.add((large > 0, small > 0, row[4]))
     assert seen == {(large, small, gathered) for large, small in ((True, False), (False, True), (True, True)) for gathered in (0, 1)}
@@ -149,6 +160,53 @@ def test_memory_for_the_small_tile_alone_is_enough_where_it_is_the_better_one(ru
             assert tile == 256 or small == need, row
         assert ask(min(need, small) - 1) == (0, -1, 0) and (tile == 128 or ask(need - 1) == (0, -1, 0)), row
     assert mixed >= 4
+
+
+def test_gradients_of_small_batches_run_on_their_own_kernels(rules):
+    from tests import test_gpu_fc_gradients as t
+    assert all(r == (1,) for r in rules("outer", t.OUTER))
+    assert all(r == (1,) for r in rules("rows_t", t.ROWS + t.LONG_ROWS))
+    assert all(r == (0,) for r in rules("outer", [s[:3] for s in t.OTHERS if s[3]]))
+    assert all(r == (0,) for r in rules("rows_t", [s[:3] for s in t.OTHERS if not s[3]]))
+    # one and two row blocks; a single turn of a wave, several and waves with one turn less; groups of rows, the last one ragged
+    seen = {(M > 16, min(2, (-(-K // 32) + 3) // 4), -(-K // 32) % 4 != 0) for M, N, K in t.ROWS + t.LONG_ROWS}
+    assert seen >= {(two, turns, uneven) for two in (False, True) for turns in (1, 2) for uneven in (False, True)} - {(True, 1, False), (False, 1, False)}
+    assert any(M > 64 and M % 32 and -(-K // 32) > 4 for M, N, K in t.ROWS)
+
+
+def test_odd_rows_reach_every_distribution(rules):
+    """Unsplit, split over blocks, whole tiles walked, and runs of slices that begin and end inside a tile."""
+    from tests import test_gpu_small_products as t
+    kinds = {}
+    for (M, N, K), (ksplit, per, *_) in zip(t.ODD + t.ODD_STREAMED, rules("split_odd_rows", t.ODD + t.ODD_STREAMED)):
+        nk = -(-K // 32)
+        kinds.setdefault("classic" if per == 0 and ksplit == 1 else "split" if per == 0 else "tiles" if ksplit == 1 else "runs", []).append((M, N, K))
+        if per and ksplit == 1:
+            assert per % nk == 0
+    assert set(kinds) == {"classic", "split", "tiles", "runs"} and kinds["runs"] == t.ODD_STREAMED
+    for M, N, K in t.ODD_STREAMED:
+        per = rules("split_odd_rows", [(M, N, K)])[0][1]
+        assert per % -(-K // 32) and -(-K // 32) % per
+
+
+def test_split_tails_reach_every_form(rules):
+    """tail tiles 1 .. 128, parts of one slice and of several, a last part shorter than the others, fewer parts than there is room for"""
+    from tests import test_gpu_small_products as t
+    layers = []
+    for xs, ws, st, pd in t.TAIL_LAYERS:
+        M, N, C, _, _, kh, kw, _, _ = _residue_row(xs, ws, st, pd)
+        layers.append((M, N, C * kh * kw))
+    for what, shapes in (("split_gather", layers), ("split_transposed", t.TAIL_GRADIENTS)):
+        seen = set()
+        for (M, N, K), (ksplit, stream_per, first, tail, per, grid) in zip(shapes, rules(what, shapes)):
+            tiles, nk = -(-M // 128) * -(-N // 64), -(-K // 32)
+            parts = -(-nk // per)
+            assert ksplit == 1 and stream_per == 0 and first == tiles - tail and first % 256 == 0, (M, N, K)
+            assert (parts - 1) * per < nk <= parts * per and grid == first + tail * parts <= first + 256, (M, N, K)
+            seen |= {"one slice" if per == 1 else "several slices", "uneven" if nk % per else "even"}
+            seen |= {"half a round"} if tail == 128 else set()
+            seen |= {"room left"} if parts < min(nk, 256 // tail) else set()
+        assert seen == {"one slice", "several slices", "uneven", "even", "half a round", "room left"}, what
 
 
 # Taken or not, and whole calls in microseconds without residues and with them on either tile (256, 128).

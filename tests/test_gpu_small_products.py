@@ -63,8 +63,9 @@ def test_blocks_of_eight(cg, ro, wl, M, N, K):
 
 
 # odd K and operands at odd words: pairs of the left operand that reach into the next row, the last of them into the end of the
-# tensor; split over blocks, streamed over tiles of unequal slices, whole tiles streamed
+# tensor; unsplit, split over blocks, whole tiles streamed, and (ODD_STREAMED) runs of slices that begin and end inside a tile
 ODD = [(1, 130, 33), (129, 65, 31), (1000, 77, 1531), (700, 1030, 2051), (40000, 64, 33), (128, 64, 1), (257, 700, 95)]
+ODD_STREAMED = [(1, 5975, 591), (1568, 256, 2305), (16507, 127, 1055)]
 
 
 @pytest.mark.parametrize("M,N,K", ODD)
@@ -83,10 +84,27 @@ def test_rows_of_odd_length(cg, ro, wl, M, N, K, at):
     assert np.array_equal(cg.to_host(got[rows].contiguous()), want)
 
 
-# more than one round of unsplit tiles whose last one is shared out: first layers and a weight gradient, one tile and half a round
-# of them left over, plainly stored and added
+@pytest.mark.parametrize("M,N,K", ODD_STREAMED)
+@pytest.mark.parametrize("at", [0, 1])
+def test_rows_of_odd_length_streamed(cg, ro, wl, M, N, K, at):
+    test_rows_of_odd_length(cg, ro, wl, M, N, K, at)
+
+
+@pytest.mark.parametrize("M,N,K", ODD_STREAMED)
+def test_rows_of_odd_length_streamed_and_added(cg, wl, M, N, K):
+    say(f"odd rows added M={M} N={N} K={K}")
+    dev = [cg.to_device(wl.draw_ring((r, K), 9660 + i)) for i, r in enumerate((M, M, N, N))]
+    base = cg.to_device(wl.draw_ring((M, N), 9664))
+    got = cg.cg_share_matmul_acc(*dev, base.clone())
+    assert torch.equal(got, base + cg.cg_share_matmul(*dev))   # (the product itself: see above)
+
+
+# more than one round of unsplit tiles whose last one is shared out: first layers and a weight gradient, one tile to half a round
+# of them left over, in parts of one slice or several, the last one shorter; plainly stored and added
 TAIL_LAYERS = [((3, 105, 105, 5), (64, 5, 5, 5), (1, 1), (2, 2)), ((1, 104, 106, 3), (130, 7, 7, 3), (1, 1), (3, 3)),
-               ((1, 182, 181, 7), (64, 5, 5, 7), (1, 1), (2, 2))]
+               ((1, 182, 181, 7), (64, 5, 5, 7), (1, 1), (2, 2)), ((3, 128, 128, 10), (64, 5, 5, 10), (1, 1), (2, 2)),
+               ((1, 213, 213, 11), (64, 5, 5, 11), (1, 1), (2, 2)), ((1, 204, 204, 24), (60, 3, 3, 24), (1, 1), (1, 1)),
+               ((1, 198, 198, 27), (61, 3, 3, 27), (1, 1), (1, 1))]
 
 
 @pytest.mark.parametrize("xs,ws,st,pd", TAIL_LAYERS)
@@ -104,7 +122,11 @@ def test_last_round_of_a_first_layer(cg, ro, wl, xs, ws, st, pd):
     assert np.array_equal(cg.to_host(acc), base + want)
 
 
-@pytest.mark.parametrize("M,N,K", [(4200, 512, 140), (257 * 128, 64, 129), (128 * 64 + 1, 256, 200)])
+TAIL_GRADIENTS = [(4200, 512, 140), (257 * 128, 64, 129), (128 * 64 + 1, 256, 200), (3071, 1023, 250), (11387, 256, 285),
+                  (20864, 128, 224), (307 * 128 - 1, 64, 256)]
+
+
+@pytest.mark.parametrize("M,N,K", TAIL_GRADIENTS)
 def test_last_round_of_a_weight_gradient(cg, ro, wl, M, N, K):
     say(f"split tail matmul_t M={M} N={N} K={K}")
     ops = [wl.draw_ring((K, r), 9695 + i) for i, r in enumerate((M, M, N, N))]
