@@ -144,6 +144,22 @@ def test_every_modulus_runs_on_one_tile_and_the_residue_tests_reach_all_shares(r
     assert seen == {(large, small, gathered) for large, small in ((True, False), (False, True), (True, True)) for gathered in (0, 1)}
 
 
+def test_large_right_operands_are_taken_one_modulus_at_a_time(rules):
+    """... and the residue tests reach that with every share of the tiles, of patches and with a flipped filter."""
+    from paper_2104_10949_amd import binding as b
+    from tests import test_gpu_residue as t
+    forward = [_residue_row(*l) for l in t.IN_STEP]
+    # an input gradient is a forward layer of the gradient, its filter the right operand
+    backward = [_residue_row(xs[:3] + (ws[0],), (xs[3],) + ws[1:3] + (ws[0],), (1, 1), pd) for xs, ws, pd in t.IN_STEP_DGRADS]
+    needs = [b.cg_share_conv2d_workspace_bytes(*l) for l in t.IN_STEP] + \
+            [b.cg_share_conv2d_dgrad_workspace_bytes(xs, ws, (1, 1), pd) for xs, ws, pd in t.IN_STEP_DGRADS]
+    shares = rules("residue_shares", forward + backward)
+    assert needs == [r[2] for r in rules("residues", forward + backward)]   # the route is taken
+    assert all(s[5] for s in shares)
+    every = {(True, False), (False, True), (True, True)}
+    assert {(s[0] > 0, s[1] > 0) for s in shares[:3]} == {(s[0] > 0, s[1] > 0) for s in shares[3:]} == every
+
+
 def test_memory_for_the_small_tile_alone_is_enough_where_it_is_the_better_one(rules):
     """A mix of both tiles pads the result's planes to multiples of 256; a call with a little less runs on the small tile alone."""
     from tests import test_gpu_residue as t

@@ -118,7 +118,7 @@ def test_conv(cg, ro, wl, xs, ws, stride, pad):
 
 def test_longest_contraction(cg):
     """K at the end of the route, words whose residues modulo 256 are -128 on both sides (the inverse multiplied into the
-    right one is odd): 2 * 65000 products of 2^14 and the 2^15 that the accumulators start from."""
+    right one is odd): 2 * 65000 products of 2^14, 0.992 of what an accumulator holds."""
     M, N, K, word = 2048, 2048, 65000, 0x7F7F7F7F7F7F7F80
     say(f"residue route K={K}, largest accumulators")
     need = cg.cg_share_matmul_workspace_bytes(M, N, K)
@@ -197,6 +197,18 @@ def test_gathers(cg, ro, wl, xs, ws, st, pd):
         assert np.array_equal(cg.to_host(got[image:image + 1, :, :, lo:lo + 40].contiguous()), want)
 
 
+# right operands so large that all XCDs take one modulus at a time: the small tile, the large one, both
+IN_STEP = [((2, 9, 22, 481), (2562, 3, 3, 481), (1, 1), (1, 1)), ((2, 23, 12, 508), (2286, 3, 3, 508), (1, 1), (1, 1)),
+           ((3, 11, 14, 638), (1898, 3, 3, 638), (1, 1), (1, 1))]
+IN_STEP_DGRADS = [((3, 22, 8, 578), (876, 5, 5, 578), (2, 2)), ((3, 11, 16, 2199), (538, 3, 3, 2199), (1, 1)),
+                  ((4, 18, 9, 2332), (474, 3, 3, 2332), (1, 1))]
+
+
+@pytest.mark.parametrize("xs,ws,st,pd", IN_STEP)
+def test_gathers_of_one_modulus_at_a_time(cg, ro, wl, xs, ws, st, pd):
+    test_gathers(cg, ro, wl, xs, ws, st, pd)
+
+
 # the input gradient of unit-stride layers: 18 and 19 moduli, channel counts of any kind, padding beyond the window, windows that
 # differ along the axes, and the 1 x 1 layer, which is a product of rows
 DGRADS = [((32, 16, 16, 256), (256, 3, 3, 256), (1, 1)), ((5, 33, 21, 130), (200, 3, 5, 130), (0, 2)),
@@ -225,23 +237,48 @@ def test_input_gradient(cg, ro, wl, xs, ws, pd):
     assert np.array_equal(cg.to_host(got[-1:].contiguous()), want)
 
 
-def test_input_gradient_without_scratch_of_its_own(cg, wl):
-    """Captured, on a named stream or beyond the limit the call takes no memory; a graph's replays follow the operands."""
+@pytest.mark.parametrize("xs,ws,pd", IN_STEP_DGRADS)
+def test_input_gradient_of_one_modulus_at_a_time(cg, ro, wl, xs, ws, pd):
+    test_input_gradient(cg, ro, wl, xs, ws, pd)
+
+
+def test_input_gradient_without_scratch_of_its_own(cg, wl, monkeypatch):
+    """Captured, on a named stream, beyond the limit or where the allocator refuses the call keeps no memory; a graph's replays
+    follow the operands."""
     xs, ws, pd = (32, 16, 16, 256), (256, 3, 3, 256), (1, 1)
-    say("input gradient captured and on a named stream")
+    say("input gradient captured, on a named stream, beyond the limit and refused")
     dev = [cg.to_device(wl.draw_ring(s, 9270 + i)) for i, s in enumerate((xs, xs, ws, ws))]
     want = cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd)
     dx = torch.empty_like(want)
     torch.cuda.synchronize()
+    need = cg.cg_share_conv2d_dgrad_workspace_bytes(xs, ws, (1, 1), pd)
+
+    def taken(**kw):
+        before = torch.cuda.memory_allocated()
+        torch.cuda.reset_peak_memory_stats()
+        cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd, dx_i=dx, **kw)
+        return torch.cuda.max_memory_allocated() - before
+
+    assert taken() >= need   # what the others do without
     side = torch.cuda.Stream()
-    before = torch.cuda.memory_allocated()
-    torch.cuda.reset_peak_memory_stats()
-    cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd, dx_i=dx, stream=side)
+    assert taken(stream=side) == 0
     side.synchronize()
-    assert torch.equal(dx, want) and torch.cuda.max_memory_allocated() < before + (64 << 20)
+    assert torch.equal(dx, want)
+    with monkeypatch.context() as m:
+        m.setattr(cg, "SCRATCH_LIMIT", need - 1)
+        dx.fill_(77)
+        assert taken() == 0 and torch.equal(dx, want)
+    with monkeypatch.context() as m:   # taken by someone else after it was seen free
+        def refuse(*a, **kw):
+            raise torch.OutOfMemoryError("no memory")
+        m.setattr(torch, "empty", refuse)
+        dx.fill_(77)
+        assert taken() == 0
+    assert torch.equal(dx, want)
+    torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        cg.cg_share_conv2d_dgrad(*dev, xs, pad=pd, dx_i=dx)
+        assert taken() == 0
     for i in range(3):
         for t in dev:
             t.add_(i + 1)
