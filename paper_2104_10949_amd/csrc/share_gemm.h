@@ -28,7 +28,7 @@ constexpr int MAX_MASK_TAPS = 32;
 // How the left operand's words are addressed.
 enum AMode {
     A_LINEAR_VEC = 0,     // row-major [M, lda], 16-byte loads (lda even, 16-byte aligned base)
-    A_LINEAR_SCALAR = 1,  // row-major [M, lda], 8-byte loads
+    A_LINEAR_SCALAR = 1,  // row-major [M, lda], any lda and any 8-byte aligned base, 16-byte loads all the same
     A_CONV_C32 = 2,       // NHWC patch gather, Cin % 32 == 0, at most MAX_MASK_TAPS taps, 16-byte loads
     A_CONV_GEN = 3,       // NHWC patch gather, any Cin, 8-byte loads
     A_TRANS = 4,          // stored transposed, [K, M] with M contiguous, 8-byte loads

@@ -128,31 +128,14 @@ __device__ __forceinline__ u4 add64x2(u4 a, u4 b) {
 // still reads zeros: invalid rows need no per-load select.
 // ---------------------------------------------------------------------------
 
-// Row-major [rows, ld] operand, 16-byte loads (ld even, base 16-byte aligned).
+// Row-major [rows, ld] operand, 16-byte loads.  On the right ld is even and the base 16-byte aligned (B_VEC).  On the left any ld and any
+// 8-byte-aligned base will do (A_LINEAR_SCALAR): the memory wants a multiple of four bytes, a view's range is checked word by word, and
+// the next row's first word, which the last pair of an odd row brings along, meets a zero of the right operand (LinearScalar and
+// TransScalar have one at k = K).  Against 8-byte loads on the left (16 of a step's 24, and addresses that spilled): 4096 x 4096 x 1001 991 ->
+// 917 us, 300 x 4001 x 2049 200 -> 184.
 struct LinearVec {
     u32 off0;  // byte offset of word k = 16*jh + 2*q of the row inside the view, or OOB
     u32 kq;    // 16*jh + 2*q
-    __device__ __forceinline__ void init(const GemmParams&, int, int row_local, int rows_left, u32 ld,
-                                         int q, int jh) {
-        kq = 16 * jh + 2 * q;
-        off0 = row_local < rows_left ? (u32)row_local * ld * 8u + kq * 8u : OOB;
-    }
-    __device__ __forceinline__ void load(const GemmParams&, __amdgpu_buffer_rsrc_t r, int ks, u32 K,
-                                         u4 out[2]) const {
-        const u32 off = off0 + 256u * ks;
-        const u32 k = 32u * ks + kq;
-        out[0] = __builtin_amdgcn_raw_buffer_load_b128(r, k < K ? off : OOB, 0, 0);
-        out[1] = __builtin_amdgcn_raw_buffer_load_b128(r, k + 8u < K ? off + 64u : OOB, 0, 0);
-    }
-};
-
-// Row-major left operand with any ld and any 8-byte-aligned base, 16-byte loads all the same (the memory wants a multiple of four
-// bytes, and a view's range is checked word by word).  With an odd K the last pair of a row brings the next row's first word
-// along: the right operand has a zero there (LinearScalar, TransScalar), so it adds nothing.  Against 8-byte loads (16 of a step's 24,
-// and addresses that spilled): 4096 x 4096 x 1001 991 -> 917 us, 300 x 4001 x 2049 200 -> 184.
-struct LinearPair {
-    u32 off0;
-    u32 kq;
     __device__ __forceinline__ void init(const GemmParams&, int, int row_local, int rows_left, u32 ld,
                                          int q, int jh) {
         kq = 16 * jh + 2 * q;
@@ -812,13 +795,12 @@ __device__ __forceinline__ void share_gemm_body(const GemmParams p) {
     constexpr bool B_TR = BMODE == B_TRANS || BMODE == B_FLIP_C32 || BMODE == B_FLIP_GEN || BMODE == B_PATCH_T;
     // ---- per-thread units.  Row-major operands put the four 16-byte quarters of a
     // 64-byte run on consecutive lanes; transposed operands put consecutive rows there.
-    typedef typename std::conditional<AMODE == A_LINEAR_VEC, LinearVec,
+    typedef typename std::conditional<AMODE == A_LINEAR_VEC || AMODE == A_LINEAR_SCALAR, LinearVec,
             typename std::conditional<AMODE == A_LINEAR_WIDE, LinearWide,
-            typename std::conditional<AMODE == A_LINEAR_SCALAR, LinearPair,
             typename std::conditional<AMODE == A_CONV_C32, ConvC32,
             typename std::conditional<AMODE == A_TRANS, TransScalar,
             typename std::conditional<AMODE == A_PATCH_T, PatchTrans,
-            typename std::conditional<AMODE == A_CONV_DIL, ConvDil, ConvGen>::type>::type>::type>::type>::type>::type>::type AGen;
+            typename std::conditional<AMODE == A_CONV_DIL, ConvDil, ConvGen>::type>::type>::type>::type>::type>::type AGen;
     typedef typename std::conditional<BMODE == B_VEC, LinearVec,
             typename std::conditional<BMODE == B_WIDE, LinearWide,
             typename std::conditional<BMODE == B_SCALAR, LinearScalar,
@@ -1594,7 +1576,7 @@ hipError_t launch_share_gemm_group2(const GemmParams& p, int amode, int bmode, h
     if (amode == A_TRANS && bmode == B_TRANS && share_gemm_outer_applies(p)) return launch_share_gemm_outer(p, stream);
     if (amode == A_LINEAR_VEC && bmode == B_TRANS && share_gemm_rows_t_pays(p)) return launch_share_gemm_rows_t(p, stream);
     CG_CASE(A_LINEAR_VEC, B_TRANS);
-    CG_CASE(A_LINEAR_SCALAR, B_TRANS);
+    if (amode == A_LINEAR_SCALAR && bmode == B_TRANS) return launch<T, A_LINEAR_VEC, B_TRANS>(p, stream);   // the same loads
     CG_CASE(A_TRANS, B_VEC);
     CG_CASE(A_TRANS, B_SCALAR);
     CG_CASE(A_TRANS, B_TRANS);
