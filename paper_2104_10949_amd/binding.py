@@ -259,7 +259,8 @@ def _scratch_fits(nbytes: int, device) -> bool:
     """Whether the allocator can take nbytes without giving anything up for it.  Where memory is short it synchronises and
     releases every cached block before it says so, on each call anew; a program near the card's capacity, or one that has limited
     its own share, therefore is not asked for memory at all.  What is left free is for the blocks that the cache keeps per stream and
-    for the program's own next allocations, which must not meet the same release because of this one.  (6 us of host time.)"""
+    for the program's own next allocations, which must not meet the same release because of this one.  (6 us of host time, 16 in a call that
+    the GPU waits for: 16 x 16 x 256 -> 256 at batch 32, alone, 190 -> 206 us, 265 without scratch memory.)"""
     if torch.cuda.get_per_process_memory_fraction(device) < 1.0:
         return False
     free, total = torch.cuda.mem_get_info(device)

@@ -146,7 +146,17 @@ __device__ __forceinline__ void planes_part(const u64* __restrict__ a, const u64
     const u32 out_row = FLIP ? row - major * out_rows : major, tap = FLIP ? major : row - major * taps;
     const size_t at = FLIP ? ((size_t)k * taps + (taps - 1u - tap)) * out_rows + out_row : (size_t)row * (size_t)words + (size_t)k;
     const size_t pitch = FLIP ? (size_t)taps * out_rows : 1;
-    if (!FLIP && vec) {   // an even number of words: both of a pair are there or none
+    // (a whole slice apart from the last one of a row: with a test around every load the loads wait for one another, and converting a filter
+    // of 848 x 3 x 3 x 1104 takes 139 us instead of 113)
+    if (!FLIP && vec && row < rows && slice * 64u + 64u <= (u32)words) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const ulonglong2 ta = *reinterpret_cast<const ulonglong2*>(a + at + 16 * j);
+            const ulonglong2 tb = *reinterpret_cast<const ulonglong2*>(b + at + 16 * j);
+            va[2 * j] = ta.x; va[2 * j + 1] = ta.y;
+            vb[2 * j] = tb.x; vb[2 * j + 1] = tb.y;
+        }
+    } else if (!FLIP && vec) {   // an even number of words: both of a pair are there or none
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool in = row < rows && k + 16 * j < words;
