@@ -606,12 +606,12 @@ bool rns_plan(RnsParams* p) {
     p->x_plane = x_plane;
     p->w_plane = w_plane;
     // With one size of tile for all moduli: the less modelled time, in microseconds, by which the caller's rule decides
-    // (measured before the shares below, which only shorten it).  A step is a tap of a slice.  The chip takes 256 of the large tile's
+    // (fitted to the kernels as they were before the shares below and before reads without bank conflicts, 3 - 6 % slower).  A step is a tap of a slice.  The chip takes 256 of the large tile's
     // blocks at a time and 512 of the small one's; a part of the time goes with the rounds and a part with the blocks (a
     // compute unit with one small block runs it faster).  Strided layers leave half of every line they gather unused.
     // The residues that are read once (those of a matrix, of a filter) come on top.  Small against large tile, whole
-    // calls: 423 / 369 us at 2048^3, 374 / 342 us at 1023 x 2047 x 3001, but 89 / 122 us at 1000 x 777 x 1531; 3x3 layer
-    // 16 x 16 x 256 -> 256 at batch 32 200 / 210 us, the 5x5 one 480 / 468 us.  Coefficients: least squares over whole calls with either
+    // calls: 423 / 366 us at 2048^3, 359 / 330 us at 1023 x 2047 x 3001, but 83 / 102 us at 1000 x 777 x 1531; 3x3 layer
+    // 16 x 16 x 256 -> 256 at batch 32 189 / 193 us, the 5x5 one 472 / 446 us.  Coefficients: least squares over whole calls with either
     // tile forced, 1300 products (M, N 65 .. 16384, K 64 .. 65000) and 1900 layers (1 .. 64 images of 4 x 4 .. 128 x 128, 16 .. 2048
     // channels, windows of 1 .. 7, strides of 1 .. 3); eight in ten within 6 % for the large tile, 20 % for the small one.
     struct Shape { int edge, slots; double round_step, block_step, fixed, per_mb; };
@@ -652,12 +652,17 @@ bool rns_plan(RnsParams* p) {
         return steps * (((double)rounds - (half ? 0.4 : 0.0)) * t.round_step + (double)blocks / slots * t.block_step) +
                (double)rounds * t.fixed + once_mb / p->nmod * part.count * t.per_mb;
     };
-    int best_large = 0;
-    best = 0.0;
-    for (int large = 0; large <= p->nmod; ++large) {
+    auto modelled = [&](int large) {
         set_parts(p, large);
-        const double us = cost(p->large, splits[kind][0], 256) + cost(p->small, splits[kind][1], 512);
-        if (large > 0 && us >= best) continue;
+        return cost(p->large, splits[kind][0], 256) + cost(p->small, splits[kind][1], 512);
+    };
+    // Another share than all moduli on the better tile must be modelled 7 % faster: 900 layers and 250 products by that ratio, measured
+    // against all on one tile, 0.91 - 0.98 on average up to 0.92, 0.97 - 1.015 and up to 1.3 times the time above.
+    int best_large = p->tile == 256 ? p->nmod : 0;
+    best = 0.93 * modelled(best_large);
+    for (int large = 0; large <= p->nmod; ++large) {
+        const double us = modelled(large);
+        if (us >= best) continue;
         best = us;
         best_large = large;
     }

@@ -133,7 +133,9 @@ def test_the_residue_tests_reach_every_instantiation(rules):
 
 
 def test_every_modulus_runs_on_one_tile_and_the_residue_tests_reach_all_shares(rules):
-    """All moduli on the large tile, all on the small one, and both sizes in one call, of rows and of patches."""
+    """All moduli on the large tile, all on the small one, and both sizes in one call, of rows and of patches; 2048^3, whose best share
+    is modelled 3 % faster than the large tile alone, stays on that."""
+    assert rules("residue_shares", [(2048, 2048, 2048, 2048, 0, 1, 1, 1, 1)])[0][:2] == (18, 0)
     from tests import test_gpu_residue as t
     layers = [(xs, ws, (s, s), (p, p)) for xs, ws, s, p in t.CONVS] + t.GATHERS
     rows = [(M, N, K, M, 0, 1, 1, 1, 1) for M, N, K in t.SHAPES + t.SMALL_TILE_SHAPES] + [_residue_row(*l) for l in layers]
@@ -175,7 +177,7 @@ def test_memory_for_the_small_tile_alone_is_enough_where_it_is_the_better_one(ru
         else:
             assert tile == 256 or small == need, row
         assert ask(min(need, small) - 1) == (0, -1, 0) and (tile == 128 or ask(need - 1) == (0, -1, 0)), row
-    assert mixed >= 4
+    assert mixed >= 3
 
 
 def test_gradients_of_small_batches_run_on_their_own_kernels(rules):
