@@ -95,10 +95,6 @@ struct GemmParams {
     // only at run time is some thirty dependent instructions.
     FastDiv div_tiles;          // tiles of the launch (classic distribution: block -> (split, tile))
     int per_split;              // slices per K range of the classic distribution
-    // Classic distribution, unsplit: the tiles from tail_first on (launch order) are those of a last round that would be
-    // partly empty; each is shared by several blocks of tail_per slices, which add into cleared elements.
-    int tail_first, tail_tiles, tail_per;   // (none: tail_tiles 0)
-    FastDiv div_tail;           // tail_tiles
     FastDiv div_per_group;      // group_m * tile columns
     FastDiv div_group, div_last_group;   // tile-rows of a full group / of the last, shorter one (or of a full one)
     FastDiv div_taps, div_tap_kw;        // kh * kw and kw, for the tap cursor

@@ -709,7 +709,7 @@ struct Walker {
 };
 
 // DIST: the classic work distribution, the streamed one (see run_index) or the classic one with a split tail (see
-// GemmParams::tail_first); the classic instantiations have exactly
+// TailSplit); the classic instantiations have exactly
 // one tile per block and compiles to straight-line set-up code.
 // The kernel's body takes its parameters as a copy of the kernel argument: the compiler then reads every field once,
 // ahead of the loop, instead of fetching fields from the argument buffer inside it (measured on the general patch
@@ -717,7 +717,7 @@ struct Walker {
 enum Distribution { CLASSIC = 0, STREAMED = 1, CLASSIC_TAIL = 2 };
 
 template <class T, int AMODE, int BMODE, int DIST>
-__device__ __forceinline__ void share_gemm_body(const GemmParams p) {
+__device__ __forceinline__ void share_gemm_body(const GemmParams p, const TailSplit tail) {
     constexpr bool STREAM = DIST == STREAMED;
     constexpr int AU = T::A_UNITS, BU = T::B_UNITS;
     __shared__ __attribute__((aligned(16))) char lds[T::LDS_BYTES];
@@ -748,11 +748,11 @@ __device__ __forceinline__ void share_gemm_body(const GemmParams p) {
     } else {
         int split, logical, per_split = p.per_split;
         if constexpr (DIST == CLASSIC_TAIL) {   // (written as selects: a block's first load waits for all of this)
-            in_tail = (int)blockIdx.x >= p.tail_first;
-            const int at = in_tail ? (int)blockIdx.x - p.tail_first : run_index(p.tail_first);
-            split = in_tail ? (int)fast_div((u32)at, p.div_tail) : 0;
-            logical = at + (in_tail ? p.tail_first - split * p.tail_tiles : 0);
-            per_split = in_tail ? p.tail_per : per_split;
+            in_tail = (int)blockIdx.x >= tail.first;
+            const int at = in_tail ? (int)blockIdx.x - tail.first : run_index(tail.first);
+            split = in_tail ? (int)fast_div((u32)at, tail.div) : 0;
+            logical = at + (in_tail ? tail.first - split * tail.tiles : 0);
+            per_split = in_tail ? tail.per : per_split;
         } else {
             const int run = run_index(nb * p.ksplit);
             split = (int)fast_div((u32)run, p.div_tiles);
@@ -1290,7 +1290,12 @@ __device__ __forceinline__ void share_gemm_body(const GemmParams p) {
 
 template <class T, int AMODE, int BMODE, int DIST>
 __global__ __launch_bounds__(T::NT, 1) void share_gemm_kernel(const GemmParams p) {
-    share_gemm_body<T, AMODE, BMODE, DIST>(p);
+    share_gemm_body<T, AMODE, BMODE, DIST>(p, TailSplit{});
+}
+
+template <class T, int AMODE, int BMODE>
+__global__ __launch_bounds__(T::NT, 1) void share_gemm_tail_kernel(const GemmParams p, const TailSplit tail) {
+    share_gemm_body<T, AMODE, BMODE, CLASSIC_TAIL>(p, tail);
 }
 
 // ===========================================================================
@@ -1383,9 +1388,9 @@ __global__ __launch_bounds__(256) void zero_fill_kernel(u64* z, size_t n) {
 
 // z = 0 in the tiles of a split tail
 template <class T>
-static __global__ __launch_bounds__(256) void zero_tiles_kernel(const GemmParams p) {
+static __global__ __launch_bounds__(256) void zero_tiles_kernel(const GemmParams p, int first) {
     int tm, tn;
-    logical_to_tile(p, (p.M + T::BM - 1) / T::BM, (p.N + T::BN - 1) / T::BN, p.tail_first + (int)blockIdx.x, tm, tn);
+    logical_to_tile(p, (p.M + T::BM - 1) / T::BM, (p.N + T::BN - 1) / T::BN, first + (int)blockIdx.x, tm, tn);
     for (int e = threadIdx.x; e < T::BM * T::BN; e += 256) {
         const int row = tm * T::BM + e / T::BN, col = tn * T::BN + e % T::BN;
         if (row < p.M && col < p.N) p.z[(u64)row * (u64)p.N + (u64)col] = 0;
@@ -1488,8 +1493,6 @@ static hipError_t launch(const GemmParams& p, hipStream_t stream) {
     const WorkSplit split = split_work<AMODE, BMODE>(tiles, nk);
     q.ksplit = split.ksplit;
     q.stream_per = split.stream_per;
-    q.tail_first = split.tail_first; q.tail_tiles = split.tail_tiles; q.tail_per = split.tail_per;
-    q.div_tail = make_fast_div((uint32_t)(split.tail_tiles < 1 ? 1 : split.tail_tiles));
     const unsigned grid = split.grid;
     constexpr bool MATRIX_PAIR =
         (AMODE == A_LINEAR_VEC || AMODE == A_LINEAR_SCALAR || AMODE == A_LINEAR_WIDE || AMODE == A_PLANES) &&
@@ -1514,12 +1517,12 @@ static hipError_t launch(const GemmParams& p, hipStream_t stream) {
     if (q.ksplit > 1)
         if (hipError_t e = launch_zero_fill(q, stream)) return e;
     if constexpr (CanTail<AMODE, BMODE>::value) {
-        if (q.tail_tiles > 0) {
+        if (split.tail.tiles > 0) {
             if (!q.z_add && !q.z_prezeroed) {
-                hipLaunchKernelGGL((zero_tiles_kernel<T>), dim3((unsigned)q.tail_tiles), dim3(256), 0, stream, q);
+                hipLaunchKernelGGL((zero_tiles_kernel<T>), dim3((unsigned)split.tail.tiles), dim3(256), 0, stream, q, split.tail.first);
                 if (hipError_t e = hipGetLastError()) return e;
             }
-            hipLaunchKernelGGL((share_gemm_kernel<T, AMODE, BMODE, CLASSIC_TAIL>), dim3(grid), dim3(T::NT), 0, stream, q);
+            hipLaunchKernelGGL((share_gemm_tail_kernel<T, AMODE, BMODE>), dim3(grid), dim3(T::NT), 0, stream, q, split.tail);
             return hipGetLastError();
         }
     }

@@ -17,9 +17,10 @@ PROGRAM = r"""
 #include "share_gemm_rns.h"
 #include "share_gemm_split.h"
 static void print_split(const cg::WorkSplit& s) {
-    printf("%d %lld %d %d %d %u\n", s.ksplit, (long long)s.stream_per, s.tail_first, s.tail_tiles, s.tail_per, s.grid);
+    printf("%d %lld %d %d %d %u\n", s.ksplit, (long long)s.stream_per, s.tail.first, s.tail.tiles, s.tail.per, s.grid);
 }
 int main(int argc, char** argv) {
+    if (!strcmp(argv[1], "argument_bytes")) printf("%zu\n", sizeof(cg::GemmParams));
     long long a[9];
     while (scanf("%lld %lld %lld %lld %lld %lld %lld %lld %lld", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6, a + 7, a + 8) == 9) {
         if (!strcmp(argv[1], "prf")) {
@@ -205,6 +206,11 @@ def test_odd_rows_reach_every_distribution(rules):
     for M, N, K in t.ODD_STREAMED:
         per = rules("split_odd_rows", [(M, N, K)])[0][1]
         assert per % -(-K // 32) and -(-K // 32) % per
+
+
+def test_arguments_of_the_tiled_kernels_take_six_lines(rules):
+    """A block's first load waits for them; a seventh line of 64 bytes cost 0.2 us a call."""
+    assert rules("argument_bytes", [])[0][0] <= 6 * 64
 
 
 def test_split_tails_reach_every_form(rules):
