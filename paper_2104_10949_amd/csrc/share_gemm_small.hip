@@ -514,8 +514,10 @@ static double rows_t_us(const GemmParams& p) {
 }
 
 // Few rows against a transposed right operand: both kernels' modelled times, the tiled one's in the terms of its launcher (slices in
-// rounds, rounds, megabytes of right operand; over the same 692 shapes nine in ten within 13 %).  The calls together 17.6 ms -> 13.96,
-// 13.94 with the better kernel each time; one of the 411 taken is slower, by 10 %.
+// rounds, rounds, megabytes of right operand; over the same 692 shapes nine in ten within 13 %).  With one block of rows the kernel must be
+// modelled 14 % faster: of 1379 other shapes the 14 between that and 5 % took 1.0 of the tiled kernel's time, up to 1.10 (4 x 1766 x 576
+// 12.4 -> 13.7 us), the 789 of up to 16 rows beyond it 18.0 ms -> 10.8, at most 0.94 each, the 576 of more rows
+// 6.95 -> 5.24, one of them, by 5 % (30 x 13090 x 284 30.3 -> 31.7).
 bool share_gemm_rows_t_pays(const GemmParams& p) {
     const double few = rows_t_us(p);
     if (few == 0.0) return false;
@@ -524,7 +526,7 @@ bool share_gemm_rows_t_pays(const GemmParams& p) {
     const double tiled = 2.42 * classic_cost(tiles, nk, ks) + (ks > 1 ? 0.4 : 0.0) +
                          1.92 * (double)((tiles * ks + ROUND_BLOCKS - 1) / ROUND_BLOCKS) +
                          0.124 * 16.0e-6 * (double)rows * (double)p.N * (double)p.K;
-    return few < 0.95 * tiled;
+    return few < (p.M <= 16 ? 0.86 : 0.95) * tiled;
 }
 
 hipError_t launch_share_gemm_rows_t(const GemmParams& p, hipStream_t stream) {

@@ -187,6 +187,8 @@ def test_gradients_of_small_batches_run_on_their_own_kernels(rules):
     assert all(r == (1,) for r in rules("rows_t", t.ROWS + t.LONG_ROWS))
     assert all(r == (0,) for r in rules("outer", [s[:3] for s in t.OTHERS if s[3]]))
     assert all(r == (0,) for r in rules("rows_t", [s[:3] for s in t.OTHERS if not s[3]]))
+    # one block of rows where the tiled kernel measured as fast or faster
+    assert all(r == (0,) for r in rules("rows_t", [(4, 1132, 624), (4, 1874, 694), (4, 1766, 576), (1, 1626, 894)]))
     # one and two row blocks; a single turn of a wave, several and waves with one turn less; groups of rows, the last one ragged
     seen = {(M > 16, min(2, (-(-K // 32) + 3) // 4), -(-K // 32) % 4 != 0) for M, N, K in t.ROWS + t.LONG_ROWS}
     assert seen >= {(two, turns, uneven) for two in (False, True) for turns in (1, 2) for uneven in (False, True)} - {(True, 1, False), (False, 1, False)}
