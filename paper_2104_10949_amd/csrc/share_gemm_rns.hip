@@ -656,12 +656,19 @@ bool rns_plan(RnsParams* p) {
         set_parts(p, large);
         return cost(p->large, splits[kind][0], 256) + cost(p->small, splits[kind][1], 512);
     };
-    // Another share than all moduli on the better tile must be modelled 7 % faster: 900 layers and 250 products by that ratio, measured
-    // against all on one tile, 0.91 - 0.98 on average up to 0.92, 0.97 - 1.015 and up to 1.3 times the time above.
+    // Both tiles in one call take 3 us and 3 % more than modelled (one launch more, and the last blocks of the first leave compute units
+    // idle), and the other tile alone must be modelled 1 % faster than the one of the rule above: of 2250 calls with the modelled share, all
+    // moduli on the large tile and all on the small one measured, the choice takes 1.004 of the best of the three on average (1.005 by
+    // modelled time alone, 1.012 with one tile).  Of 900 other layers and 300 products against the code before there were shares four are
+    // more than 2 % slower, at most 4 % (by modelled time alone 6 of 900, up to 26 %); all together take 0.94 of its time.
     int best_large = p->tile == 256 ? p->nmod : 0;
-    best = 0.93 * modelled(best_large);
-    for (int large = 0; large <= p->nmod; ++large) {
-        const double us = modelled(large);
+    best = modelled(best_large);
+    if (const double other = modelled(p->nmod - best_large); other < 0.99 * best) {
+        best = other;
+        best_large = p->nmod - best_large;
+    }
+    for (int large = 1; large < p->nmod; ++large) {
+        const double us = 1.03 * modelled(large) + 3.0;
         if (us >= best) continue;
         best = us;
         best_large = large;
