@@ -694,8 +694,9 @@ Residues plan_residues(const Plan& pl) {
     // pay.  Residues: 16 + 2 * nmod bytes per word pair converted at 4.9 TB/s (4.0 with 8-byte loads), 2 * nmod + 8 per output
     // combined at 8.5 TB/s (measured up to 16384 x 16384 outputs), the product as rns_plan models it, and 12
     // microseconds for three launches that do not fill the chip at both ends.  They must win by a margin to be preferred,
-    // a little more on strided layers, where the model scatters most: of 1900 random layers and 1300 products other than
-    // those of the fit, none that is taken is more than 2 % slower than without residues.
+    // a little more on strided layers, where the model scatters most.  The coefficients are those of the kernels before the residues' product got
+    // 6 to 12 % faster; with them as they are now, of 2000 random calls that are taken seven are more than 2 % slower than without
+    // residues (2 to 9 %, one 19 %), and all together take 1925 -> 1125 ms; some that are not taken would gain.
     const double up_m = (double)((p.M + (int64_t)127) / 128 * 128), up_n = (double)((p.N + (int64_t)63) / 64 * 64);
     const double inside = conv ? (p.H < p.kh ? (double)p.H / p.kh : 1.0) * (p.W < p.kw ? (double)p.W / p.kw : 1.0) : 1.0;
     // (an input gradient reads its filter across the rows: 1.1 of the forward layer's time with the gather of 32 channels)

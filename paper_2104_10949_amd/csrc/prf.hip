@@ -26,8 +26,8 @@
 // caching, Bernstein and Schwabe, "New AES software speed records", 2008).  A block is
 // 5 + 7*16 + 16 = 133 lookups instead of 160.
 //
-// Bound: the LDS (133 lookups of two cycles per wave, stream and block of AES, 87 of the 119 us of the measured call),
-// with the vector ALU behind it (about 215 instructions per AES block, 128 of them lookup addresses; 290 with two tables,
+// Bound: the LDS (133 lookups of two cycles per wave, stream and block of AES, 87 of the 119 us of the measured call; by
+// the counters busy 72 % of the cycles), with the vector ALU behind it (59 %; about 215 instructions per AES block, 128 of them lookup addresses; 290 with two tables,
 // whose columns needed a rotation, 64 copies each).  Measured: the truncation step with both streams on
 // 2^23 words 167 -> 126 us (of that 30 us by the shared rounds and short-call launch shape, 8 us by keys in
 // registers and three-input xors), 128.5 -> 119.6 by four tables; a zero share of 2^15 words 8.7 -> 5.9 us (all compute units

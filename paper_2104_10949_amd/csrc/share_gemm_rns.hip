@@ -15,9 +15,9 @@
 // Exact matrix products through int8 products modulo such numbers and the Chinese remainder theorem are a published
 // method (Ozaki, Uchino and Imamura, "Ozaki Scheme II", 2025, there for floating-point products).
 //
-// Measured on MI355X, whole calls, the better of the plain kernel and the digit planes against residues: 4096^3 3450 -> 2140 us,
-// 2048^3 456 -> 367, 3072 x 3072 x 1024 517 -> 418; 3x3 layers at batch 32: 16 x 16 x 256 -> 256 254 -> 179, 8 x 8 x 512 -> 512
-// 262 -> 181, the 5x5 one 628 -> 425.  At 4096^3: conversion 330 us (52 bytes per word pair at 5.2 TB/s: memory), product
+// Measured on MI355X in one run, whole calls, the better of the plain kernel and the digit planes against residues: 4096^3 3444 -> 2142 us
+// (2115 - 2237 over several cards), 2048^3 451 -> 361, 3072 x 3072 x 1024 525 -> 411; 3x3 layers at batch 32: 16 x 16 x 256 -> 256
+// 247 -> 177 (175 - 187), 8 x 8 x 512 -> 512 252 -> 181, the 5x5 one 644 -> 420.  At 4096^3: conversion 330 us (52 bytes per word pair at 5.2 TB/s: memory), product
 // 1700-1780 us (the matrix pipes are busy 83 % of the cycles, at the clock that random operands leave), combination 90 us.
 // Where operands or outputs are large against M*N*K, or the grid leaves most of a round empty, the three passes cost
 // more than they save; the caller's rule compares both.
@@ -398,7 +398,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void rns_gemm_kernel(RnsParams p) 
         __builtin_amdgcn_sched_barrier(0);
         landed();
         if (CONV && !second) window();
-        // one request at most between two products: what a wave issues in a run keeps its matrix core waiting
+        // the requests spread over the products, one at most between two on the large tile (the small one's rows are too short for
+        // that: two fragments after the first product): what a wave issues in a run keeps its matrix core waiting
 #pragma unroll
         for (int i = 0; i < ROWS; ++i) {
 #pragma unroll

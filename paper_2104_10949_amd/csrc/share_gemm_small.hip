@@ -24,13 +24,16 @@ namespace {
 
 constexpr int SMALL_WAVES = 8;        // waves of a block: two per SIMD, 256 registers each
 constexpr int SMALL_MAX_SLICES = 511 * SMALL_WAVES;  // a wave's i32 accumulators stay exact for 511 slices (see share_gemm.hip)
-// Which products the launcher takes (measured against share_gemm_kernel at M = 8, 32, 64, N = 64 .. 4096,
-// K = 128 .. 25088): with one 16-row block every shape up to the slice limit (4.4 us against 13 us at K = 128,
-// 281 against 379 us at 8 x 4096 x 25088); with two to four row blocks the right operand is read once per row
+// Which products the launcher takes.  The lines were measured with blocks of 16 x 16 only and sums through LDS atomics; with the kernels
+// as they are (1160 calls on both sides) they hold for the plain call, and lie low: two rounds win up to 15 slices (0.91 of the tiled kernel's
+// time, 1.01 at worst), four rounds with three and four (0.93), 17 .. 64 rows up to 6000 units (0.93).  The call that adds to z takes 0.94 at
+// 4600 units, single shapes up to 1.28.
+// Measured against share_gemm_kernel at M = 8, 32, 64, N = 64 .. 4096, K = 128 .. 25088: with one 16-row block every shape up to the
+// slice limit (3.5 us against 11 us at K = 128, 285 against 369 us at 8 x 4096 x 25088); with two to four row blocks the right operand is read once per row
 // block, and the tiled kernel wins from about 4600 (16 x 16 block, slice) units on.
 // With more than 64 rows the same unit line holds and the rounds of the chip set a second one (a block fills a compute
 // unit; 1030 shapes with M = 65 .. 12288, N = 10 .. 2448, K = 32 .. 14720, whole calls against share_gemm_kernel).  Up to
-// 256 blocks: 128 x 128 x 784 14.6 -> 9.6 us, 256 x 256 x 128 11.7 -> 4.5, 1024 x 64 x 512 14.3 -> 9.2.  Two rounds: won up to
+// 256 blocks: 128 x 128 x 784 14.5 -> 8.8 us, 256 x 256 x 128 11.8 -> 4.1, 1024 x 64 x 512 14.0 -> 8.3.  Two rounds: won up to
 // 13 slices (0.95 of the tiled kernel's time at worst, 1.04 at 14).  Three: a single slice is not worth three folds
 // (12288 x 16 x 32 6.6 -> 8.1 us), two and more are (0.91 of the time at 12288 x 16 x 64).  A fourth round never pays (512 x 512 x 64
 // 9.7 -> 10.9).  The tiled kernel needs no clearing launch when it adds to z, so those lines lie lower: 11 slices in two
@@ -469,8 +472,8 @@ hipError_t launch_share_gemm_small(const GemmParams& p, hipStream_t stream) {
                            dim3(SMALL_WAVES * 64), 0, stream, p);
     };
     // Blocks of 8 rows and columns leave half of the matrix instruction's rows and columns to words that nobody stores, but a
-    // compute unit's loads, which are what such a call waits for, are those of half as many rows: 32 x 512 x 512 7.23 -> 6.58 us,
-    // 128 x 128 x 784 9.5 -> 8.5, 8 x 1000 x 512 7.3 -> 5.9 (of it 0.2 us by sums that meet without LDS atomics).
+    // compute unit's loads, which are what such a call waits for, are those of half as many rows: 32 x 512 x 512 7.3 -> 6.5 us,
+    // 128 x 128 x 784 9.6 -> 8.8, 8 x 1000 x 512 7.3 -> 6.0 (of it 0.2 us by sums that meet without LDS atomics).
     const int64_t m8 = ((int64_t)p.M + 7) / 8, n8 = ((int64_t)p.N + 7) / 8;
     if (ksplit == 1 && m8 * n8 <= SMALL_ROUND_BLOCKS) launch(share_gemm_small_kernel<8, 8>, 8, 8);
     else if (ksplit == 1 && m8 * tiles_n <= SMALL_ROUND_BLOCKS) launch(share_gemm_small_kernel<8, 16>, 8, 16);

@@ -15,8 +15,9 @@ constexpr int SPLIT_MIN_SLICES = 2;
 // units of one K slice of the main loop, with a plain store and with atomic adds.
 constexpr double SPLIT_COST_PLAIN = 1.0, SPLIT_COST_ATOMIC = 2.0;
 // The streamed distribution must beat the classic one by this factor of modelled time to be used, by a little more where the
-// right operand comes in 8-byte loads (1000 x 777 x 1531, 0.858: 95 us streamed, 88 classic; of 250 odd products none is slower
-// than before with 0.84, and all together take 0.91 of the time).
+// right operand comes in 8-byte loads: the model has the fold of a run's second tile but not its prologue, which waits longer for those
+// (1000 x 777 x 1531, 0.858: 95 us streamed, 88 classic; of 700 odd products none is more than 2 % slower than with 8-byte loads on both
+// sides and no streaming, and all together take 0.885 of the time).
 constexpr double STREAM_MARGIN = 0.88, STREAM_MARGIN_SCALAR = 0.84;
 // A last round that is at most half full shares its tiles out over all compute units where that shortens it by this many slices
 // (a launch that clears the tiles and the atomic adds cost about two).

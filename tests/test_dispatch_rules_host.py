@@ -235,30 +235,35 @@ def test_split_tails_reach_every_form(rules):
         assert seen == {"one slice", "several slices", "uneven", "even", "half a round", "room left"}, what
 
 
-# Taken or not, and whole calls in microseconds without residues and with them on either tile (256, 128).
-LAYERS = [(((15, 69, 69, 896), (144, 5, 5, 896), (2, 2), (2, 2)), 0, 4096, 3653, 4376),
-          (((4, 101, 101, 1024), (352, 3, 3, 1024), (1, 2), (1, 1)), 1, 3833, 3221, 3344),
-          (((13, 5, 5, 1136), (1008, 7, 7, 1136), (1, 1), (3, 3)), 0, 1309, 1846, 1638),
-          (((20, 13, 13, 1296), (224, 5, 5, 1296), (2, 2), (2, 2)), 0, 608, 776, 689),
-          (((35, 4, 4, 1104), (496, 7, 7, 1104), (1, 1), (3, 3)), 0, 1032, 1119, 1119),
-          (((32, 16, 16, 256), (256, 3, 3, 256), (1, 1), (1, 1)), 1, 254, 211, 204),
-          (((32, 8, 8, 512), (512, 3, 3, 512), (1, 1), (1, 1)), 1, 262, 246, 209),
-          (((32, 32, 32, 128), (128, 3, 3, 128), (1, 1), (1, 1)), 1, 266, 356, 237),
-          (((32, 64, 64, 64), (64, 3, 3, 64), (1, 1), (1, 1)), 0, 282, 841, 516),
-          (((32, 64, 64, 64), (128, 3, 3, 64), (1, 1), (1, 1)), 0, 527, 875, 555)]
-PRODUCTS = [((7548, 529, 23105), 1, 6981, 6473, 8531), ((423, 2509, 10029), 0, 859, 823, 903), ((734, 1713, 3433), 1, 326, 282, 314),
-            ((1000, 777, 1531), 0, 113, 117, 95), ((4096, 4096, 4096), 1, 3447, 2190, 2779), ((2048, 2048, 2048), 1, 456, 372, 418),
-            ((2048, 2048, 512), 0, 129, 141, 137), ((1024, 1024, 1024), 0, 83, 94, 84), ((512, 4096, 4096), 0, 469, 478, 521)]
+# Taken or not, moduli on the large tile, and whole calls in microseconds without residues and with them: as they run, all moduli on the
+# large tile, all on the small one.
+LAYERS = [(((15, 69, 69, 896), (144, 5, 5, 896), (2, 2), (2, 2)), 0, None, 4301, 3652, 3641, 4527),
+          (((4, 101, 101, 1024), (352, 3, 3, 1024), (1, 2), (1, 1)), 1, 17, 3996, 3181, 3196, 3489),
+          (((13, 5, 5, 1136), (1008, 7, 7, 1136), (1, 1), (3, 3)), 0, None, 1334, 1683, 1822, 1677),
+          (((20, 13, 13, 1296), (224, 5, 5, 1296), (2, 2), (2, 2)), 0, None, 597, 662, 759, 660),
+          (((35, 4, 4, 1104), (496, 7, 7, 1104), (1, 1), (3, 3)), 0, None, 1041, 1125, 1278, 1127),
+          (((32, 16, 16, 256), (256, 3, 3, 256), (1, 1), (1, 1)), 1, 16, 247, 177, 195, 191),
+          (((32, 8, 8, 512), (512, 3, 3, 512), (1, 1), (1, 1)), 1, 16, 252, 181, 224, 197),
+          (((32, 32, 32, 128), (128, 3, 3, 128), (1, 1), (1, 1)), 1, 0, 260, 231, 355, 233),
+          (((32, 64, 64, 64), (64, 3, 3, 64), (1, 1), (1, 1)), 0, None, 280, 493, 815, 500),
+          (((32, 64, 64, 64), (128, 3, 3, 64), (1, 1), (1, 1)), 0, None, 527, 547, 879, 552)]
+PRODUCTS = [((7548, 529, 23105), 1, 19, 6225, 6191, 6193, 8962), ((423, 2509, 10029), 0, None, 751, 776, 775, 835),
+            ((734, 1713, 3433), 1, 12, 276, 264, 266, 304), ((1000, 777, 1531), 0, None, 96, 84, 105, 84),
+            ((4096, 4096, 4096), 1, 18, 3444, 2142, 2143, 2609), ((2048, 2048, 2048), 1, 18, 451, 361, 361, 416),
+            ((2048, 2048, 512), 0, None, 121, 132, 129, 124), ((1024, 1024, 1024), 0, None, 72, 72, 81, 73),
+            ((512, 4096, 4096), 0, None, 477, 441, 471, 523)]
 
 
-def test_residues_and_their_tile_are_chosen_where_they_measured_faster(rules):
+def test_residues_and_their_tiles_are_chosen_where_they_measured_faster(rules):
+    """(Three of those that are not taken would be faster with residues: the rule is fitted to a slower product.)"""
     from paper_2104_10949_amd import binding as b
     rows = [_residue_row(*l) for l, *_ in LAYERS] + [(M, N, K, M, 0, 1, 1, 1, 1) for (M, N, K), *_ in PRODUCTS]
     needs = [b.cg_share_conv2d_workspace_bytes(*l) for l, *_ in LAYERS] + [b.cg_share_matmul_workspace_bytes(*p) for p, *_ in PRODUCTS]
-    for (what, taken, without, large, small), need, (tile, _, nbytes) in zip(LAYERS + PRODUCTS, needs, rules("residues", rows)):
+    for (what, taken, share, without, runs, large, small), need, (_, _, nbytes), got in \
+            zip(LAYERS + PRODUCTS, needs, rules("residues", rows), rules("residue_shares", rows)):
         assert (need == nbytes) == bool(taken), what
         if taken:
-            assert (large if tile == 256 else small) <= 1.05 * min(without, large, small), what
+            assert got[0] == share and runs <= 1.02 * min(without, large, small), what
 
 
 def test_residue_kernels_keep_their_accumulators_in_registers(tmp_path):
